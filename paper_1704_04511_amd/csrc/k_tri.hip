@@ -29,6 +29,8 @@
 // stored as LAPACK's zhetrd (lower) stores them: v(k+2:n) in column k of the
 // column-major matrix Vst below the subdiagonal, tau(k), diagonal D, real
 // subdiagonal E.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -73,15 +75,22 @@ SLRX_DEV double dpp_mov(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, RM, 0xf, false);
   return __hiloint2double(hi, lo);
 }
+// The same for a control that gives every lane a source (no previous value to keep).
+template <int CTRL>
+SLRX_DEV double dpp_all(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
 
 // Sum over the 64 lanes of a wave in a fixed tree (pairs, quads, half rows,
 // rows, then rows 0+1 and 2+3 and the two halves); every lane gets the total.
 // Call with all 64 lanes active.
 SLRX_DEV double wave_total(double v) {
-  v += dpp_mov<0xB1, 0xf>(v);   // quad_perm [1,0,3,2]
-  v += dpp_mov<0x4E, 0xf>(v);   // quad_perm [2,3,0,1]
-  v += dpp_mov<0x141, 0xf>(v);  // row_half_mirror
-  v += dpp_mov<0x140, 0xf>(v);  // row_mirror
+  v += dpp_all<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_all<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_all<0x141>(v);  // row_half_mirror
+  v += dpp_all<0x140>(v);  // row_mirror
   v += dpp_mov<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
   v += dpp_mov<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
@@ -273,212 +282,268 @@ __global__ __launch_bounds__(kTriNT) void k_tri_col(TriArgs a, int rows) {
   if (tid < nrow) pout[row0 + tid] = sum4(&xc[0][tid], kTriRMax);
 }
 
-// The last kTriTail columns in one launch, one workgroup of kTailNT threads per
-// problem with the trailing block (rows and columns k0..n-1, at most
-// kTriTail x kTriTail) in registers: thread t holds row i = t / 4 at the columns
-// j = t % 4 + 4 c, c < kTriTail / 4, zero beyond the block.  First the pending update of reflector
-// k0-1 is applied, then each column is reduced as in k_tri_col (same reflector
-// convention, same outputs): the wave holding row k forms reflector k from it
-// (the block is Hermitian, so column k below the diagonal is the conjugate of
-// row k) and publishes v; every row forms its entry of p = A v (four lanes, a
-// fixed DPP tree) and p^H v is summed over the waves in order; then the rank-2
-// update runs on the registers, written as
-//   A - v w^H - w v^H = A - conj(tau) v p^H - (tau p + 2 Re(c d) v) v^H
-// for w = tau p + c d v, c = -|tau|^2 / 2, d = p^H v (real for a Hermitian A).
-// v and p are zero outside rows k+1.., so the update leaves the finished rows
-// and columns unchanged without masks (slots are skipped in chunks of eight,
-// whose loads the compiler can then issue together); v and p are
-// double-buffered by column parity, which leaves two barriers per column.  The
-// outputs stay in LDS until the end (a barrier would otherwise wait for each
-// column's global stores).
+// The last columns (a trailing block of at most kTriTail rows) in one launch, one
+// workgroup of kTailNT threads per problem with the block in registers.  A column
+// is a serial chain (the reflector's norm, square root and divisions, then the row
+// products), so the layout is chosen to shorten it: the workgroup is 8 half-waves
+// of 32 lanes; half-wave h holds the rows h + 8 r (dealt out so that the work
+// stays balanced as the block shrinks), lane l of it the columns l + 32 c.  Every
+// half-wave forms the reflector redundantly from p and row k in LDS, with the same
+// arithmetic and so the same bits: its two sums stay within 32 lanes and the only
+// barrier of a column is the one that publishes p and the next row.  The operands
+// of the rank-2 update are in registers, one per column slot.  Per column:
+//   1. d = Re p^H v of the pending reflector (real for a Hermitian block),
+//      w = tau p + c d v, c = -|tau|^2 / 2, column k = conj(row k) - v conj(w_k) - w conj(v_k);
+//   2. reflector k from it as in k_tri_col;
+//   3. the rows: the pending rank-2 update, p_i = sum_j A_ij v_j.
+// v and p are zero outside the trailing block, so the update needs no masks; rows
+// and column slots left of it are skipped.  The outputs stay in LDS until the end
+// (a barrier would otherwise wait for each column's global stores).
+// What bounds it is the issue of its instructions on one CU (about 1100, 770 and 480
+// per wave and column with three, two and one live column slots; four waves, one per
+// SIMD, since every wave repeats the reflector): 75 columns take 160 us and 96 take
+// 185 us, against 229 and 281 us for four lanes per row reading v and p from LDS for
+// every entry, with two barriers per column; with eight waves 179 and 212 us.
 constexpr int kTriTail = 96;
-constexpr int kTailNT = 384;
-constexpr int kTailLanes = 4;                   // lanes per row
-constexpr int kTailC = kTriTail / kTailLanes;   // columns per thread
-constexpr int kTailRowsW = 64 / kTailLanes;     // rows per wave
-constexpr int kTailChunk = 8;                   // column slots skipped or processed together
-static_assert(kTailLanes == 4, "row sums are quad sums (sum_quad)");
-static_assert(kTailNT / kTailLanes == kTriTail, "one row of the block per kTailLanes threads");
-static_assert(kTailC % kTailChunk == 0 && kTailNT % 64 == 0, "whole chunks and waves");
+constexpr int kTailNT = 256;
+constexpr int kTailH = kTailNT / 32;  // half-waves
 // packed reflectors of the block: column kk's entries kk+1..L-1 at voff(kk)
 __host__ __device__ inline int tail_voff(int L, int kk) { return kk * (2 * L - kk - 1) / 2; }
 inline size_t tail_lds(int L) { return (size_t)tail_voff(L, L - 1) * sizeof(double2); }
 
-// Sum over each aligned quad of lanes (fixed order); every lane of the quad
-// gets its total.  Call with all 64 lanes active.
-SLRX_DEV double sum_quad(double v) {
-  v += dpp_mov<0xB1, 0xf>(v);  // quad_perm [1,0,3,2]
-  v += dpp_mov<0x4E, 0xf>(v);  // quad_perm [2,3,0,1]
+// The two values of lanes 16 apart within a half-wave, added: the even row of 16
+// lanes gets the sums of x over both rows, the odd row those of y
+// (v_permlane16_swap exchanges the odd row of its first operand with the even row
+// of the second).
+SLRX_DEV double pair_rows(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(y), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// Sum over each row of 16 lanes (a fixed tree); every lane of the row gets it.
+SLRX_DEV double row_total(double v) {
+  v += dpp_all<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_all<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_all<0x141>(v);  // row_half_mirror
+  v += dpp_all<0x140>(v);  // row_mirror
   return v;
 }
-SLRX_DEV double2 sum_quad2(double2 v) { return make_double2(sum_quad(v.x), sum_quad(v.y)); }
-// LDS writes of a wave made visible to its other lanes (a wave executes its LDS
-// accesses in order; the fences keep the compiler from moving them across).
-SLRX_DEV void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Sum over each half-wave of 32 lanes; every lane of it gets the total.
+SLRX_DEV double half_total(double v) { return row_total(pair_rows(v, v)); }
+
+// e - x conj(y) and e + x y, in fused steps.
+SLRX_DEV double2 sub_conj(double2 e, double2 x, double2 y) {
+  return make_double2(fma(-x.y, y.y, fma(-x.x, y.x, e.x)), fma(x.x, y.y, fma(-x.y, y.x, e.y)));
 }
-SLRX_DEV double readlane_d(double x, int l) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), l);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
-  return __hiloint2double(hi, lo);
+SLRX_DEV double2 add_mul(double2 e, double2 x, double2 y) {
+  return make_double2(fma(-x.y, y.y, fma(x.x, y.x, e.x)), fma(x.y, y.x, fma(x.x, y.y, e.y)));
 }
 
-__global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0) {
-  extern __shared__ double2 vl[];  // reflectors, packed (tail_voff)
-  __shared__ double2 vs[2][kTriTail], ps[2][kTriTail];
-  __shared__ double2 xrow[kTriTail];  // row k, exchanged within the wave holding it
-  __shared__ double2 tl[kTriTail];
-  __shared__ double Dl[kTriTail], El[kTriTail];
-  __shared__ double2 red[kTailNT / 64];
-  __shared__ double2 tau_s[2];
-  const int n = a.n, L = n - k0;
-  const int b = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int i = tid / kTailLanes, q = tid % kTailLanes;
-  const double2* Aw = a.Aw + (size_t)b * a.strideA;
+// State of the last-columns kernel that lives across columns (registers) and its LDS.
+template <int C>
+struct TailState {
+  double2 A[4 * C][C], v[C], tau;
+};
+struct TailLds {
+  // by column parity: v and p of the pending reflector, the row of the next column
+  double2 vs[2][kTriTail], ps[2][kTriTail], rows[2][kTriTail];
+  double2 tl[kTriTail];
+  double Dl[kTriTail], El[kTriTail];
+};
+
+// Columns kk0 .. kk1-1 of the block, all with their first live column slot CS
+// ((kk + 1) / 32 == CS), so that dead slots and rows cost no registers or branches.
+template <int C, int CS>
+SLRX_DEV void tail_columns(TailState<C>& st, TailLds& q, double2* vl, int L, int kk0, int kk1) {
+  constexpr int R = 4 * C, R0 = CS > 0 ? 4 * CS - 1 : 0;  // rows before R0 are finished and cleared
+  const int tid = threadIdx.x, lane = tid & 31, h = tid >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double2 zero = make_double2(0.0, 0.0);
-  double2 A[kTailC];
-#pragma unroll
-  for (int c = 0; c < kTailC; ++c) {
-    const int j = q + kTailLanes * c;
-    A[c] = (i < L && j < L) ? Aw[(size_t)(k0 + i) * n + k0 + j] : zero;
-  }
-  // the rank-2 update of one reflector from v and p in LDS slot s; columns from slot c0
-  auto rank2 = [&](int s, double2 t, double2 d, double2 vi, double2 pi, int c0) __attribute__((always_inline)) {
-    const double2 al = dmul(dconj(t), vi);                                    // conj(tau) v_i
-    const double2 be = dadd(dmul(t, pi), dscale(vi, -(t.x * t.x + t.y * t.y) * d.x));  // tau p_i + 2 Re(c d) v_i
-#pragma unroll
-    for (int h = 0; h < kTailC / kTailChunk; ++h) {
-      if (kTailChunk * h + kTailChunk - 1 < c0) continue;  // chunks of slots left of the block
-#pragma unroll
-      for (int u = 0; u < kTailChunk; ++u) {
-        const int c = kTailChunk * h + u, j = q + kTailLanes * c;
-        const double2 pj = ps[s][j], vj = vs[s][j];
-        A[c] = dsub(A[c], dadd(dmul(al, dconj(pj)), dmul(be, dconj(vj))));
-      }
-    }
-  };
-  // p^H v from the rows' terms: per wave in a fixed tree, then the waves in order
-  auto wave_sums = [&](double2 part) __attribute__((always_inline)) {
-    part = wave_total2(part);
-    if (lane == 0) red[wave] = part;
-    __syncthreads();
-    double2 d = red[0];
-#pragma unroll
-    for (int w = 1; w < kTailNT / 64; ++w) d = dadd(d, red[w]);
-    return d;
-  };
-  if (k0 > 0) {  // pending update of reflector k0-1 (v, p from the last column launch)
-    const double2* vprev = a.vbuf[(k0 + 1) & 1] + (size_t)b * n + k0;
-    const double2* pprev = a.pbuf[(k0 + 1) & 1] + (size_t)b * n + k0;
-    if (tid < kTriTail) {
-      vs[1][tid] = tid < L ? vprev[tid] : zero;
-      ps[1][tid] = tid < L ? pprev[tid] : zero;
-    }
-    const double2 vi = i < L ? vprev[i] : zero, pi = i < L ? pprev[i] : zero;
-    const double2 d = wave_sums(q == 0 ? dcmul(pi, vi) : zero);  // its barrier also publishes vs, ps
-    rank2(1, a.tau[(size_t)b * n + k0 - 1], d, vi, pi, 0);
-    __syncthreads();
-  }
-  for (int kk = 0; kk < L - 1; ++kk) {
+  for (int kk = kk0; kk < kk1; ++kk) {
     const int s = kk & 1;
-    const int c1 = (kk + 1) / kTailLanes;  // first column slot that can be in the trailing block
-    // 1. reflector kk from row kk (x_j = conj A(kk, j), j >= kk + 2; alpha = conj A(kk, kk + 1))
-    if (wave == kk / kTailRowsW) {
-      const bool mine = i == kk;
-      double xn = 0.0;
-      if (mine) {
+    // 1. the pending w, column kk, its norm below kk + 1
+    double2 p[C], w[C], col[C];
 #pragma unroll
-        for (int c = 0; c < kTailC; ++c) {
-          const int j = q + kTailLanes * c;
-          if (j >= kk + 2) xn += A[c].x * A[c].x + A[c].y * A[c].y;
-          xrow[j] = A[c];
-        }
-      }
-      xn = sum_quad(xn);
-      wave_sync();  // row kk in xrow for the whole wave
-      const double xn2 = readlane_d(xn, (kk % kTailRowsW) * kTailLanes);
-      const double2 alpha = dconj(xrow[kk + 1]);
-      const double dk = xrow[kk].x;
-      double beta;
-      double2 tau, scale;
-      if (xn2 == 0.0 && alpha.y == 0.0) {
-        tau = zero;
-        beta = alpha.x;
-        scale = zero;
-      } else {
-        const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn2);
-        beta = alpha.x >= 0.0 ? -nrm : nrm;
-        tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
-        const double2 den = make_double2(alpha.x - beta, alpha.y);  // scale = 1 / (alpha - beta)
-        const double dd = den.x * den.x + den.y * den.y;
-        scale = make_double2(den.x / dd, -den.y / dd);
-      }
-      // v from the row in xrow: lane l writes entries l, l + 64, .. (every slot)
+    for (int c = CS; c < C; ++c) {
+      p[c] = q.ps[s][lane + 32 * c];
+      col[c] = q.rows[s][lane + 32 * c];
+    }
+    const double2 pk = q.ps[s][kk], vk = q.vs[s][kk], pk1 = q.ps[s][kk + 1], vk1 = q.vs[s][kk + 1];
+    const double2 rk1 = q.rows[s][kk + 1];
+    const double rk = q.rows[s][kk].x;
+    // v and p of the pending reflector at kk itself, which slot CS may no longer hold
+    double d = (kk & 31) == 31 && lane == 0 ? pk.x * vk.x + pk.y * vk.y : 0.0;
+#pragma unroll
+    for (int c = CS; c < C; ++c) d = fma(p[c].x, st.v[c].x, fma(p[c].y, st.v[c].y, d));
+    d = half_total(d);
+    const double2 tau = st.tau;
+    const double cd = -0.5 * (tau.x * tau.x + tau.y * tau.y) * d;
+    const double2 wk = dadd(dmul(tau, pk), dscale(vk, cd));
+    double xn = 0.0;
+#pragma unroll
+    for (int c = CS; c < C; ++c) {
+      const int j = lane + 32 * c;
+      w[c] = dadd(dmul(tau, p[c]), dscale(st.v[c], cd));
+      col[c] = sub_conj(sub_conj(dconj(col[c]), st.v[c], wk), w[c], vk);
+      if (j >= kk + 2) xn += col[c].x * col[c].x + col[c].y * col[c].y;
+    }
+    const double2 wk1 = dadd(dmul(tau, pk1), dscale(vk1, cd));
+    const double2 alpha = sub_conj(sub_conj(dconj(rk1), vk1, wk), wk1, vk);
+    xn = half_total(xn);
+    // 2. reflector kk
+    double beta;
+    double2 taun, scale;
+    if (xn == 0.0 && alpha.y == 0.0) {
+      taun = zero;
+      beta = alpha.x;
+      scale = zero;
+    } else {
+      const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn);
+      beta = alpha.x >= 0.0 ? -nrm : nrm;
+      const double ib = 1.0 / beta;
+      taun = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
+      const double2 den = make_double2(alpha.x - beta, alpha.y);  // scale = 1 / (alpha - beta)
+      const double id = 1.0 / (den.x * den.x + den.y * den.y);
+      scale = make_double2(den.x * id, -den.y * id);
+    }
+    double2 vn[C];
+#pragma unroll
+    for (int c = CS; c < C; ++c) {
+      const int j = lane + 32 * c;
+      double2 x = dmul(col[c], scale);  // 0 beyond the block
+      if (j < kk + 2) x = make_double2(j == kk + 1 ? 1.0 : 0.0, 0.0);
+      vn[c] = x;
+    }
+    if (wv == 0 && h == 0) {
       const int vo = tail_voff(L, kk) - kk - 1;
 #pragma unroll
-      for (int h = 0; h < (kTriTail + 63) / 64; ++h) {
-        const int j = lane + 64 * h;
-        if (j >= kTriTail) continue;
-        const double2 v = j == kk + 1 ? make_double2(1.0, 0.0)
-                                      : (j >= kk + 2 && j < L ? dmul(dconj(xrow[j]), scale) : zero);
-        vs[s][j] = v;
-        if (j > kk && j < L) vl[vo + j] = j == kk + 1 ? make_double2(beta, 0.0) : v;
+      for (int c = CS; c < C; ++c) {
+        const int j = lane + 32 * c;
+        q.vs[s ^ 1][j] = vn[c];
+        if (j > kk && j < L) vl[vo + j] = j == kk + 1 ? make_double2(beta, 0.0) : vn[c];
       }
       if (lane == 0) {
-        tau_s[s] = tau;
-        Dl[kk] = dk;
-        El[kk] = beta;
-        tl[kk] = tau;
+        q.Dl[kk] = rk - 2.0 * (vk.x * wk.x + vk.y * wk.y);
+        q.El[kk] = beta;
+        q.tl[kk] = taun;
+      }
+    }
+    // 3. the rows: the pending rank-2 update and p_i = sum_j A_ij v_j, all rows in one
+    //    block of code so that their loads and sums overlap
+    double t[R];
+#pragma unroll
+    for (int r = R0; r < R; ++r) {
+      const int i = h + kTailH * r;
+      const double2 vi = q.vs[s][i], wi = dadd(dmul(tau, q.ps[s][i]), dscale(vi, cd));
+      double2 acc = zero;
+#pragma unroll
+      for (int c = CS; c < C; ++c) {
+        const double2 e = sub_conj(sub_conj(st.A[r][c], vi, w[c]), wi, st.v[c]);
+        st.A[r][c] = e;
+        acc = add_mul(acc, e, vn[c]);
+      }
+      t[r] = pair_rows(acc.x, acc.y);  // even rows of 16 lanes: the real part, odd rows: the imaginary part
+    }
+#pragma unroll
+    for (int r = R0; r < R; ++r) t[r] = row_total(t[r]);
+#pragma unroll
+    for (int r = R0; r < R; ++r) {
+      const int i = h + kTailH * r;
+      if (i == kk + 1) {  // the next column's row
+#pragma unroll
+        for (int c = CS; c < C; ++c) q.rows[s ^ 1][lane + 32 * c] = st.A[r][c];
+      }
+    }
+    if ((lane & 15) == 0) {  // p, cleared for finished rows
+#pragma unroll
+      for (int r = R0; r < R; ++r) {
+        const int i = h + kTailH * r;
+        ((double*)&q.ps[s ^ 1][i])[lane >> 4] = i > kk && i < L ? t[r] : 0.0;
       }
     }
     __syncthreads();
-    // 2. p_i = sum_j A_ij v_j for the rows of the trailing block, p^H v
-    const double2 vi = vs[s][i];
-    double2 pi = zero;
-    const bool live = wave * kTailRowsW + kTailRowsW - 1 >= kk + 1;  // the wave holds trailing rows
-    if (live) {
-      double2 acc[4] = {zero, zero, zero, zero};  // four chains, added in order
 #pragma unroll
-      for (int h = 0; h < kTailC / kTailChunk; ++h) {
-        if (kTailChunk * h + kTailChunk - 1 < c1) continue;
-#pragma unroll
-        for (int u = 0; u < kTailChunk; ++u) {
-          const int c = kTailChunk * h + u;
-          acc[u & 3] = dadd(acc[u & 3], dmul(A[c], vs[s][q + kTailLanes * c]));
-        }
-      }
-      pi = sum_quad2(dadd(dadd(acc[0], acc[1]), dadd(acc[2], acc[3])));
-      if (i <= kk || i >= L) pi = zero;
-    }
-    if (q == 0) ps[s][i] = pi;
-    const double2 d = wave_sums(q == 0 ? dcmul(pi, vi) : zero);
-    // 3. the rank-2 update of the trailing block
-    if (live) rank2(s, tau_s[s], d, vi, pi, c1);
+    for (int c = CS; c < C; ++c) st.v[c] = vn[c];
+    st.tau = taun;
   }
-  if (wave == (L - 1) / kTailRowsW) {  // the last diagonal entry
-    if (i == L - 1) {
+}
+
+// C: column slots per lane (L <= 32 C); 4 C rows per half-wave.
+template <int C>
+__global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0) {
+  constexpr int R = 4 * C;
+  extern __shared__ double2 vl[];  // reflectors, packed (tail_voff)
+  __shared__ TailLds q;
+  const int n = a.n, L = n - k0;
+  const int b = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 31, h = tid >> 5;
+  const double2* Aw = a.Aw + (size_t)b * a.strideA;
+  const double2 zero = make_double2(0.0, 0.0);
+  TailState<C> st;
 #pragma unroll
-      for (int c = 0; c < kTailC; ++c) xrow[q + kTailLanes * c] = A[c];
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int i = h + kTailH * r, j = lane + 32 * c;
+      double2 x = zero;
+      if (i < L && j < L) x = Aw[(size_t)(k0 + i) * n + k0 + j];
+      st.A[r][c] = x;
     }
-    wave_sync();
-    if (lane == 0) Dl[L - 1] = xrow[L - 1].x;
+  // pending reflector k0-1 (v, p from the last column launch; none: zeros)
+  st.tau = zero;
+  if (k0 > 0) st.tau = a.tau[(size_t)b * n + k0 - 1];
+  if (tid < kTriTail) {
+    const double2* vprev = ((k0 & 1) ? a.vbuf[0] : a.vbuf[1]) + (size_t)b * n + k0;
+    const double2* pprev = ((k0 & 1) ? a.pbuf[0] : a.pbuf[1]) + (size_t)b * n + k0;
+    double2 x = zero, y = zero;
+    if (k0 > 0 && tid < L) {
+      x = vprev[tid];
+      y = pprev[tid];
+    }
+    q.vs[0][tid] = x;
+    q.ps[0][tid] = y;
+    q.vs[1][tid] = q.ps[1][tid] = zero;
+  }
+  if (h == 0) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) q.rows[0][lane + 32 * c] = st.A[0][c];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < C; ++c) st.v[c] = q.vs[0][lane + 32 * c];
+  tail_columns<C, 0>(st, q, vl, L, 0, min(L - 1, 31));
+  if constexpr (C > 1) tail_columns<C, 1>(st, q, vl, L, 31, min(L - 1, 63));
+  if constexpr (C > 2) tail_columns<C, 2>(st, q, vl, L, 63, min(L - 1, 95));
+  if (tid == 0) {  // the last diagonal entry: v of reflector L-2 is 1 there and 0 elsewhere
+    const int s = (L - 1) & 1;
+    const double2 pk = q.ps[s][L - 1], vk = q.vs[s][L - 1];
+    const double2 tau = st.tau;
+    const double cd = -0.5 * (tau.x * tau.x + tau.y * tau.y) * (pk.x * vk.x + pk.y * vk.y);
+    const double2 wk = dadd(dmul(tau, pk), dscale(vk, cd));
+    q.Dl[L - 1] = q.rows[s][L - 1].x - 2.0 * (vk.x * wk.x + vk.y * wk.y);
   }
   __syncthreads();
   double2* Vst = a.Vst + (size_t)b * a.strideA;
-  for (int kk = 0; kk < L - 1; ++kk) {
+  for (int kk = h; kk < L - 1; kk += kTailH) {
     const int vo = tail_voff(L, kk) - kk - 1;
-    for (int j = kk + 1 + tid; j < L; j += kTailNT) Vst[(size_t)(k0 + kk) * n + k0 + j] = vl[vo + j];
+    for (int j = kk + 1 + lane; j < L; j += 32) Vst[(size_t)(k0 + kk) * n + k0 + j] = vl[vo + j];
   }
-  for (int kk = tid; kk < L; kk += kTailNT) {
-    a.D[(size_t)b * n + k0 + kk] = Dl[kk];
-    if (kk < L - 1) {
-      a.E[(size_t)b * n + k0 + kk] = El[kk];
-      a.tau[(size_t)b * n + k0 + kk] = tl[kk];
+  if (tid < L) {
+    a.D[(size_t)b * n + k0 + tid] = q.Dl[tid];
+    if (tid < L - 1) {
+      a.E[(size_t)b * n + k0 + tid] = q.El[tid];
+      a.tau[(size_t)b * n + k0 + tid] = q.tl[tid];
     }
   }
+}
+
+template <int C>
+static hipError_t launch_tail(const TriArgs& a, int nbatch, int k0, hipStream_t s) {
+  static LdsLimit lim;
+  const hipError_t e = lim.ensure((const void*)k_tri_tail<C>, tail_lds(32 * C));
+  if (e != hipSuccess) return e;
+  k_tri_tail<C><<<dim3(1, nbatch), kTailNT, tail_lds(a.n - k0), s>>>(a, k0);
+  return hipGetLastError();
 }
 
 int tri_max_n() { return 3000; }
@@ -533,12 +598,10 @@ hipError_t launch_tridiag(const TriArgs& base, int nbatch, hipStream_t s, int ca
     else if (u <= 10) launch_col<10>(a, nbatch, rows, stream, s);
     else launch_col<12>(a, nbatch, rows, stream, s);
   }
-  static LdsLimit lim;
-  const hipError_t e = lim.ensure((const void*)k_tri_tail, tail_lds(kTriTail));
-  if (e != hipSuccess) return e;
   const int L = n - k0;
-  k_tri_tail<<<dim3(1, nbatch), kTailNT, tail_lds(L), s>>>(a, k0);
-  return hipGetLastError();
+  if (L <= 32) return launch_tail<1>(a, nbatch, k0, s);
+  if (L <= 64) return launch_tail<2>(a, nbatch, k0, s);
+  return launch_tail<3>(a, nbatch, k0, s);
 }
 
 }  // namespace slrx
