@@ -677,7 +677,7 @@ def bench_direct(args) -> int:
 
     def direct_roofline(pb):
         """IRLS-direct on the 128x128x16 data with its two classes timed: the Gram
-        matrix (lifting + zgemm, 8 s^2 rows flop on FP64 MFMA) and the CG (per operator
+        matrix (8 s^2 rows flop on FP64 MFMA) and the CG (per operator
         application lifting + cgemm, 8 s^2 rows flop on FP32 MFMA, + adjoint)."""
         T, P, Q = pb.b.shape
         s = pb.N1 * pb.N2 * pb.M

@@ -227,8 +227,11 @@ struct DirectArgs {
 };
 DirectArgs direct_args(int P, int Q, int T, int N1, int N2, int M, double lam);
 int direct_blocks(long V);  // blocks (and partials) of the adjoint pass for V samples
-// X = T(x), row-major rows x s (complex128 or complex64)
-hipError_t launch_dlift64(const DirectArgs& a, const float2* x, double2* X, hipStream_t s);
+// R = T(x)^H T(x), row-major, from the iterate; part: dgram_part_elems(a) entries;
+// bad: set to 1 on a non-finite entry (then written as 0)
+size_t dgram_part_elems(const DirectArgs& a);
+hipError_t launch_dgram(const DirectArgs& a, const float2* x, double2* part, double2* R, int* bad, hipStream_t s);
+// X = T(x), column j at j * rows (as are Y's columns in launch_dadj)
 hipError_t launch_dlift32(const DirectArgs& a, const float2* x, float2* X, hipStream_t s);
 // out = S o v + lam T^*(Y) (init: y - that, partials <out,out>, flag cleared); else partials <v,out>
 hipError_t launch_dadj(const DirectArgs& a, const float2* Y, const float2* v, const uint8_t* S, const float2* y,

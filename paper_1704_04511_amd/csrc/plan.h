@@ -89,12 +89,12 @@ struct slrx_plan {
   double2 *Yc64 = nullptr, *dco = nullptr;
 
   // IRLS-direct (SLRX_FLAG_DIRECT): one allocation, made at the first direct run,
-  // holding the lifted matrix of the iterate (complex128, for the Gram matrix), the
-  // lifted matrix of the CG direction and its product with H (complex64), and H
-  // (complex64); its own rocBLAS handle for the two plain GEMMs
+  // holding the Gram matrix's partial tiles (complex128), the lifted matrix of the CG
+  // direction and its product with H (complex64), and H (complex64); its own rocBLAS
+  // handle for the operator's plain GEMM
   void* direct_mem = nullptr;
   size_t direct_bytes = 0;
-  double2* X64 = nullptr;
+  double2* dpart = nullptr;
   float2 *Xv = nullptr, *Yd = nullptr, *Hf = nullptr;
   rocblas_handle dblas = nullptr;
 

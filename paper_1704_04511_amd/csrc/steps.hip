@@ -364,7 +364,7 @@ slrx_status slrx::direct_setup(slrx_plan* pl) {
   const DirectArgs da = direct_args(d.P, d.Q, d.T, d.N1, d.N2, d.M, 0.0);
   const size_t s = (size_t)pl->s();
   auto up = [](size_t n) { return (n + 255) & ~(size_t)255; };
-  const size_t b64 = up((size_t)da.rows * s * 16), b32 = up((size_t)da.rows * s * 8), bh = up(s * s * 8);
+  const size_t b64 = up(dgram_part_elems(da) * 16), b32 = up((size_t)da.rows * s * 8), bh = up(s * s * 8);
   const size_t need = b64 + 2 * b32 + bh;
   if (need > pl->direct_bytes) {
     if (pl->direct_mem) HIPCHK(hipFree(pl->direct_mem));
@@ -377,7 +377,7 @@ slrx_status slrx::direct_setup(slrx_plan* pl) {
     pl->direct_bytes = need;
   }
   char* m = (char*)pl->direct_mem;
-  pl->X64 = (double2*)m;
+  pl->dpart = (double2*)m;
   pl->Xv = (float2*)(m + b64);
   pl->Yd = (float2*)(m + b64 + b32);
   pl->Hf = (float2*)(m + b64 + 2 * b32);
@@ -390,22 +390,13 @@ slrx_status slrx::direct_setup(slrx_plan* pl) {
   return SLRX_OK;
 }
 
-// R = X^H X of the explicit linear lifting X of the iterate (complex128), row-major
-// into Aw for the eigen-decomposition chain: X is stored row-major (rows x s), i.e.
-// column-major s x rows, and the column-major product X_c X_c^H is R^T, whose
-// column-major layout is R's row-major one.
+// R = X^H X of the explicit linear lifting X of the iterate, row-major into Aw for the
+// eigen-decomposition chain.
 slrx_status slrx::step_direct_gram(slrx_plan* pl) {
   const slrx_dims& d = pl->d;
   KTimer kt(pl, SLRX_K_GRAM);
   const DirectArgs da = direct_args(d.P, d.Q, d.T, d.N1, d.N2, d.M, 0.0);
-  const int s = pl->s();
-  HIPCHK(launch_dlift64(da, pl->x, pl->X64, pl->stream));
-  const rocblas_double_complex one(1.0, 0.0), zero(0.0, 0.0);
-  const rocblas_status st = rocblas_zgemm(pl->dblas, rocblas_operation_none, rocblas_operation_conjugate_transpose, s,
-                                          s, (rocblas_int)da.rows, &one, (const rocblas_double_complex*)pl->X64, s,
-                                          (const rocblas_double_complex*)pl->X64, s, &zero,
-                                          (rocblas_double_complex*)pl->Aw, s);
-  if (st != rocblas_status_success) return fail(SLRX_EDEVICE, "rocblas_zgemm failed (status %d)", (int)st);
+  HIPCHK(launch_dgram(da, pl->x, pl->dpart, pl->Aw, (int*)(pl->info + kInfoNonfinite), pl->stream));
   return SLRX_OK;
 }
 
@@ -438,13 +429,13 @@ static slrx_status direct_apply(slrx_plan* pl, const float2* v, float2* out, boo
   const DirectArgs da = direct_args(d.P, d.Q, d.T, d.N1, d.N2, d.M, pl->prm.lambda);
   const int s = pl->s();
   HIPCHK(launch_dlift32(da, v, pl->Xv, pl->stream));
-  // row-major Y = Xv H: column-major Y^T = H^T Xv^T, and the row-major layouts of H
-  // and Xv are the column-major layouts of H^T and Xv^T
+  // Y = Xv H, column-major; the row-major H is the column-major H^T
   const rocblas_float_complex one(1.f, 0.f), zero(0.f, 0.f);
-  const rocblas_status st = rocblas_cgemm(pl->dblas, rocblas_operation_none, rocblas_operation_none, s,
-                                          (rocblas_int)da.rows, s, &one, (const rocblas_float_complex*)pl->Hf, s,
-                                          (const rocblas_float_complex*)pl->Xv, s, &zero,
-                                          (rocblas_float_complex*)pl->Yd, s);
+  const rocblas_int rows = (rocblas_int)da.rows;
+  const rocblas_status st = rocblas_cgemm(pl->dblas, rocblas_operation_none, rocblas_operation_transpose, rows, s, s,
+                                          &one, (const rocblas_float_complex*)pl->Xv, rows,
+                                          (const rocblas_float_complex*)pl->Hf, s, &zero,
+                                          (rocblas_float_complex*)pl->Yd, rows);
   if (st != rocblas_status_success) return fail(SLRX_EDEVICE, "rocblas_cgemm failed (status %d)", (int)st);
   HIPCHK(launch_dadj(da, pl->Yd, v, pl->S, pl->bm, out, init ? 1 : 0, part, pl->flag, pl->stream));
   return SLRX_OK;
