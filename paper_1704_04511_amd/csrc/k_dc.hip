@@ -2,12 +2,13 @@
 // reduction (FP64), middle stage of the Gram eigen-decomposition in the weight
 // update (Sec. III.B, Algorithm 1 step 1): divide and conquer.
 //
-// The index range is halved recursively down to single entries; every
-// coupling E[c-1] between the halves at a split c is torn off as a rank-one
-// term |E[c-1]| v v^T, v = (e_{c-1}, sign(E[c-1]) e_c), so each diagonal entry
-// first loses |E[i-1]| + |E[i]|.  The tree is then merged bottom-up, one launch
-// sequence per tree level with every node of the level in parallel.  A merge of
-// children with eigenpairs (D1, Q1), (D2, Q2) solves
+// The index range is halved recursively down to blocks of at most eight entries,
+// which are diagonalised directly; every coupling E[c-1] between the halves at a
+// split c is torn off as a rank-one term |E[c-1]| v v^T, v = (e_{c-1},
+// sign(E[c-1]) e_c), so the diagonal entries on both sides first lose |E[c-1]|.
+// The tree is then merged bottom-up: the nodes of at most kLeafN entries in one
+// launch (k_dc_leaf), above them one launch sequence per tree level with every
+// node of the level in parallel.  A merge of children with eigenpairs (D1, Q1), (D2, Q2) solves
 //   diag(D1, D2) + rho z z^T,  z = (last row of Q1, sign * first row of Q2) / sqrt(2),
 //   rho = 2 |E[c-1]|:
 //   1. deflate (one thread, in sorted order): entries with rho |z_i| <= tol keep
@@ -85,18 +86,6 @@ SLRX_DEV double wave_prod(double v) {
 SLRX_DEV double wave_max(double v) {
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
   return v;
-}
-
-// Tear every coupling off the diagonal; leaves (single entries) start with Q = 1.
-__global__ void k_dc_init(DcArgs a0) {
-  const DcArgs a = dc_at(a0, blockIdx.y);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.n) return;
-  double d = a.D[i];
-  if (i >= 1) d -= fabs(a.E[i - 1]);
-  if (i <= a.n - 2) d -= fabs(a.E[i]);
-  a.D[i] = d;
-  a.Q[(long)i * a.n + i] = 1.0;
 }
 
 // Sort, z, deflation of one merge (one workgroup per node, its size a multiple
@@ -438,15 +427,38 @@ __global__ __launch_bounds__(256) void k_dc_gather(DcArgs a0, int mmax) {
   }
 }
 
-// Terms of f = 1 + psi + phi at offset tau from the origin pole, over one
-// wave: psi sums the poles at or left of d_j, phi the poles right of it
+// Copy of v from the lane a DPP control selects (controls that give every lane a source).
+template <int CTRL>
+SLRX_DEV double dpp_f64(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+// Sum and product over aligned groups of G lanes (a wave or a quad); every lane of the
+// group gets it.
+template <int G>
+SLRX_DEV double group_sum(double v) {
+  static_assert(G == 64 || G == 4, "a wave or a quad");
+  if constexpr (G == 64) return wave_sum(v);
+  v += dpp_f64<0xB1>(v);  // quad_perm [1,0,3,2]
+  v += dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]
+  return v;
+}
+SLRX_DEV double quad_prod(double v) {
+  v *= dpp_f64<0xB1>(v);
+  v *= dpp_f64<0x4E>(v);
+  return v;
+}
+
+// Terms of f = 1 + psi + phi at offset tau from the origin pole, over a group of
+// G lanes: psi sums the poles at or left of d_j, phi the poles right of it
 // (values and derivatives), fa the magnitudes (rounding bound of f).
 struct SecTerms {
   double psi, dpsi, phi, dphi, fa;
 };
+template <int G>
 SLRX_DEV SecTerms secular(const double* dl, const double* z2, int k, int j, double dor, double rho, double tau) {
   double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int i = threadIdx.x & 63; i < k; i += 64) {
+  for (int i = threadIdx.x & (G - 1); i < k; i += G) {
     const double r = 1.0 / ((dl[i] - dor) - tau);
     const double w = z2[i] * r;
     if (i <= j) {
@@ -459,11 +471,11 @@ SLRX_DEV SecTerms secular(const double* dl, const double* z2, int k, int j, doub
     v[4] += fabs(w);
   }
   SecTerms t;
-  t.psi = rho * wave_sum(v[0]);
-  t.dpsi = rho * wave_sum(v[1]);
-  t.phi = rho * wave_sum(v[2]);
-  t.dphi = rho * wave_sum(v[3]);
-  t.fa = rho * wave_sum(v[4]);
+  t.psi = rho * group_sum<G>(v[0]);
+  t.dpsi = rho * group_sum<G>(v[1]);
+  t.phi = rho * group_sum<G>(v[2]);
+  t.dphi = rho * group_sum<G>(v[3]);
+  t.fa = rho * group_sum<G>(v[4]);
   return t;
 }
 
@@ -474,39 +486,22 @@ SLRX_DEV double bit_mid(double x0, double x1, double sign) {
   return sign * __longlong_as_double(a + (b - a) / 2);
 }
 
-// One wave per root.  The root's offset tau from the nearer pole stays in a
+// Root j of the secular equation of k poles dl with squared couplings z2, by a group of
+// G lanes.  The root's offset tau from the nearer pole stays in a
 // bracket [lo, hi] (f(lo) < 0 <= f(hi), f increasing).  Each step fits
 // f ~ c + S / (a - tau) + T / (b - tau) at the current tau (a, b the offsets of
 // the two poles around the root; S, T from the derivatives of psi and phi) and
 // takes the model's root; a step that leaves the bracket or does not halve the
 // previous step is replaced by bisection of the bit patterns, so the iteration
 // always ends.  It stops when |f| is within the rounding of its terms.
-__global__ __launch_bounds__(256) void k_dc_secular(DcArgs a0) {
-  const DcArgs a = dc_at(a0, blockIdx.z);
-  extern __shared__ double sec_lds[];
-  const int node = a.node0 + blockIdx.y;
-  const int4 nd = a.nodes[node];
-  const int s = nd.x, n = a.n;
-  const int k = a.ws_node[4 * node];
-  // the node's poles and squared couplings, read by every step of the four roots
-  double* dl = sec_lds;
-  double* z2 = sec_lds + k;
-  if (blockIdx.x * 4 >= k) return;
-  for (int i = threadIdx.x; i < k; i += 256) {
-    dl[i] = a.ws_d[s + i];
-    const double z = a.ws_d[n + s + i];
-    z2[i] = z * z;
-  }
-  __syncthreads();
-  const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= k) return;
-  const double rho = 2.0 * fabs(a.E[s + nd.z - 1]);
+template <int G>
+SLRX_DEV void secular_root(const double* dl, const double* z2, int k, int j, double rho, int& origin, double& offset) {
   const bool last = j == k - 1;
   int o;
   double sign, hiv;
   if (!last) {
     const double gap = dl[j + 1] - dl[j];
-    const SecTerms t = secular(dl, z2, k, j, dl[j], rho, 0.5 * gap);
+    const SecTerms t = secular<G>(dl, z2, k, j, dl[j], rho, 0.5 * gap);
     if (1.0 + t.psi + t.phi >= 0.0) {
       o = j;
       sign = 1.0;
@@ -517,10 +512,10 @@ __global__ __launch_bounds__(256) void k_dc_secular(DcArgs a0) {
     hiv = 0.5 * gap;
   } else {
     double zz = 0.0;
-    for (int i = threadIdx.x & 63; i < k; i += 64) zz += z2[i];
+    for (int i = threadIdx.x & (G - 1); i < k; i += G) zz += z2[i];
     o = j;
     sign = 1.0;
-    hiv = rho * wave_sum(zz);
+    hiv = rho * group_sum<G>(zz);
   }
   const double dor = dl[o];
   const double pa = dl[j] - dor;                     // left pole
@@ -529,7 +524,7 @@ __global__ __launch_bounds__(256) void k_dc_secular(DcArgs a0) {
   double x = sign * hiv;  // the midpoint (the far end for the last root)
   double prev_step = 1e300, fprev = 0.0;
   for (int it = 0; it < 200; ++it) {
-    const SecTerms t = secular(dl, z2, k, j, dor, rho, x);
+    const SecTerms t = secular<G>(dl, z2, k, j, dor, rho, x);
     const double f = 1.0 + t.psi + t.phi;
     if (fabs(f) <= 4.0 * __DBL_EPSILON__ * (1.0 + t.fa)) break;
     if (f < 0.0) lo = x;
@@ -593,8 +588,36 @@ __global__ __launch_bounds__(256) void k_dc_secular(DcArgs a0) {
     fprev = f;
     x = xn;
   }
+  origin = o;
+  offset = x;
+}
+
+// One wave per root.
+__global__ __launch_bounds__(256) void k_dc_secular(DcArgs a0) {
+  const DcArgs a = dc_at(a0, blockIdx.z);
+  extern __shared__ double sec_lds[];
+  const int node = a.node0 + blockIdx.y;
+  const int4 nd = a.nodes[node];
+  const int s = nd.x, n = a.n;
+  const int k = a.ws_node[4 * node];
+  // the node's poles and squared couplings, read by every step of the four roots
+  double* dl = sec_lds;
+  double* z2 = sec_lds + k;
+  if (blockIdx.x * 4 >= k) return;
+  for (int i = threadIdx.x; i < k; i += 256) {
+    dl[i] = a.ws_d[s + i];
+    const double z = a.ws_d[n + s + i];
+    z2[i] = z * z;
+  }
+  __syncthreads();
+  const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (j >= k) return;
+  const double rho = 2.0 * fabs(a.E[s + nd.z - 1]);
+  int o;
+  double x;
+  secular_root<64>(dl, z2, k, j, rho, o, x);
   if ((threadIdx.x & 63) == 0) {
-    a.D[s + j] = dor + x;
+    a.D[s + j] = dl[o] + x;
     a.ws_orig[s + j] = o;
     a.ws_d[4 * n + s + j] = x;
   }
@@ -732,6 +755,399 @@ __global__ __launch_bounds__(256) void k_dc_gemm(DcArgs a0) {
       }
 }
 
+// The lowest levels of the tree in one launch: a subtree of at most kLeafN entries per
+// workgroup, its matrices in LDS.  Blocks of at most kLeafBase entries are diagonalised
+// directly (implicit QR steps, eight lanes per block, a row of the vectors each); the
+// merges above them are the general ones with other units: a wave deflates a node (lane =
+// entry), a quad finds a root, recomputes a z entry or forms a vector, a wave multiplies
+// a 16 x 16 tile.  These levels are latency: as six launches each (4 to 10 us) the six
+// levels up to 51 entries took about 200 us of a decomposition at s = 405, all seven 245 us
+// at s = 75; here 90 us, bounded by the chain of divisions of the slowest root of a level
+// (10 to 17 us) and, below, of the QR steps (10 us); starting from single entries as the
+// larger levels do took 120 us.
+constexpr int kLeafN = 64, kLeafLd = kLeafN + 1, kLeafNT = 256, kLeafBase = 8;
+struct LeafLds {
+  double Q[2][kLeafN * kLeafLd];  // eigenvector state and the other buffer, row-major
+  double U[kLeafN * kLeafLd];     // merge eigenvectors, column c at c * kLeafLd
+  double D[kLeafN], E[kLeafN];    // eigenvalues of the nodes so far, couplings
+  double ds[kLeafN], zs[kLeafN];  // sorted poles and couplings of every node
+  double dl[kLeafN], zl[kLeafN];  // its kept ones, then zl: squared couplings
+  double zsign[kLeafN];           // the kept couplings (their signs)
+  double rc[kLeafN], rs[kLeafN], tau[kLeafN], zh[kLeafN];
+  int perm[kLeafN], order[kLeafN], flag[kLeafN], ki[kLeafN], rec[kLeafN], rp[kLeafN], rq[kLeafN], orig[kLeafN];
+  int node[kLeafN];               // node of every entry at this level
+  int k[kLeafN / kLeafBase], nrot[kLeafN / kLeafBase];
+};
+
+// LDS writes of a wave made visible to its other lanes.
+SLRX_DEV void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Node q of depth d below a node of m entries: start and size (halved as in dc_build_tree).
+SLRX_DEV void leaf_node(int m, int d, int q, int& start, int& size) {
+  start = 0;
+  size = m;
+  for (int b = d - 1; b >= 0; --b) {
+    const int n1 = size / 2;
+    if (q >> b & 1) {
+      start += n1;
+      size -= n1;
+    } else {
+      size = n1;
+    }
+  }
+}
+
+// Sort, z, deflation of one node by one wave (k_dc_deflate's steps).
+SLRX_DEV void leaf_deflate(LeafLds& L, const double* Q, int q, int s, int m) {
+  const int t = threadIdx.x & 63, n1 = m / 2;
+  const unsigned long long below = (1ull << t) - 1;
+  const double beta = L.E[s + n1 - 1];
+  const double rho = 2.0 * fabs(beta), sgn = beta >= 0.0 ? 1.0 : -1.0;
+  const double r2 = 0.70710678118654752440;
+  double d = 0.0, z = 0.0;
+  if (t < m) {
+    d = L.D[s + t];
+    z = t < n1 ? Q[(s + n1 - 1) * kLeafLd + s + t] * r2 : sgn * Q[(s + n1) * kLeafLd + s + t] * r2;
+    int r = 0;
+    for (int j = 0; j < m; ++j) {
+      const double dj = L.D[s + j];
+      r += dj < d || (dj == d && j < t);
+    }
+    L.perm[s + r] = t;
+    L.ds[s + r] = d;
+    L.zs[s + r] = z;
+    L.node[s + t] = q;
+  }
+  const double mx = wave_max(fmax(fabs(d), fabs(z)));
+  const double tol = 8.0 * __DBL_EPSILON__ * mx;
+  wave_lds_sync();
+  bool kept = false;
+  if (t < m) {
+    d = L.ds[s + t];
+    z = L.zs[s + t];
+    kept = rho * fabs(z) > tol;
+    L.flag[s + t] = kept;
+  }
+  const unsigned long long kb = __ballot(kept);
+  const int nk = __popcll(kb);
+  if (kept) {
+    const int i = __popcll(kb & below);
+    L.dl[s + i] = d;
+    L.zl[s + i] = z;
+    L.ki[s + i] = t;
+  }
+  wave_lds_sync();
+  const double inv = 1.0 / mx;
+  const double tol2 = 64.0 * __DBL_EPSILON__ * __DBL_EPSILON__;
+  bool cand = false;
+  if (t >= 1 && t < nk) {
+    const double zp = L.zl[s + t - 1], zt = L.zl[s + t];
+    const double Z2 = zp * zp, zt2 = zt * zt, rr = Z2 + zt2;
+    const double x = (L.dl[s + t] * inv) * Z2 - (L.dl[s + t - 1] * inv) * Z2;
+    cand = x * x * zt2 <= 2.0 * tol2 * Z2 * rr * rr || !(2.0 * tol2 * Z2 * rr * rr >= 1e-290);
+  }
+  const unsigned long long cb = __ballot(cand);
+  // the walk of k_dc_deflate, by every lane alike
+  int nrot = 0;
+  int i = cb ? __ffsll(cb) - 1 : -1;
+  while (i >= 0) {
+    const double zp = L.zl[s + i - 1];
+    double Z2 = zp * zp, N = (L.dl[s + i - 1] * inv) * Z2;
+    bool start = true;
+    for (;;) {
+      const double zt = L.zl[s + i], dt = L.dl[s + i] * inv;
+      const double zt2 = zt * zt;
+      const double rr = Z2 + zt2;
+      const double x = dt * Z2 - N;
+      const double rhs = tol2 * Z2 * rr * rr;
+      bool rot;
+      if (rhs >= 1e-290) {
+        rot = x * x * zt2 <= rhs;
+      } else {  // products near underflow: the test in its direct form
+        const double r = sqrt(rr);
+        rot = fabs((dt - N / Z2) * (zt / r) * (sqrt(Z2) / r)) <= 8.0 * __DBL_EPSILON__;
+      }
+      if (!rot) break;
+      if (t == 0) {
+        L.rec[s + nrot] = start ? ~(i - 1) : i - 1;
+        L.rc[s + nrot] = Z2;
+        L.rs[s + nrot] = N;
+      }
+      ++nrot;
+      Z2 = rr;
+      N = N + dt * zt2;
+      start = false;
+      if (++i >= nk) break;
+    }
+    if (i >= nk) break;
+    const unsigned long long rest = i + 1 < 64 ? cb & (~0ull << (i + 1)) : 0;
+    i = rest ? __ffsll(rest) - 1 : -1;
+  }
+  wave_lds_sync();
+  if (t < nrot) {
+    const int e = L.rec[s + t];
+    const bool start = e < 0;
+    const int ip = start ? ~e : e, it = ip + 1;
+    const bool end = t == nrot - 1 || L.rec[s + t + 1] < 0;  // the next rotation starts a new chain
+    const int p = L.ki[s + ip], u = L.ki[s + it];
+    const double zt = L.zl[s + it], dt = L.dl[s + it];
+    const double Z2 = L.rc[s + t];
+    const double zp = start ? L.zl[s + ip] : sqrt(Z2);
+    const double dp = start ? L.dl[s + ip] : (L.rs[s + t] / Z2) * mx;
+    const double r = hypot(zt, zp);
+    const double c = zt / r, sv = -zp / r;
+    L.rp[s + t] = p;
+    L.rq[s + t] = u;
+    L.rc[s + t] = c;
+    L.rs[s + t] = sv;
+    L.ds[s + p] = dp * c * c + dt * sv * sv;
+    L.zs[s + p] = 0.0;
+    if (end) {
+      L.ds[s + u] = dp * sv * sv + dt * c * c;
+      L.zs[s + u] = r;
+    }
+    L.flag[s + u] = 3 | (end ? 0 : 4) | (p << 3);
+    if (start) L.flag[s + p] = 5;
+  }
+  wave_lds_sync();
+  const int f = t < m ? L.flag[s + t] : 0;
+  const bool gone = t < m && (!(f & 1) || (f & 2)), stays = t < m && (f & 1) && !(f & 4);
+  const unsigned long long gb = __ballot(gone), sb = __ballot(stays);
+  const int k = __popcll(sb);
+  if (gone) L.order[s + m - 1 - __popcll(gb & below)] = (f & 2) ? f >> 3 : t;
+  if (stays) L.order[s + __popcll(sb & below)] = t;
+  wave_lds_sync();
+  if (t < m) {
+    const int o = L.order[s + t];
+    if (t < k) {
+      const double zk = L.zs[s + o];
+      L.dl[s + t] = L.ds[s + o];
+      L.zsign[s + t] = zk;
+      L.zl[s + t] = zk * zk;
+    } else {
+      L.D[s + t] = L.ds[s + o];  // deflated eigenvalue
+    }
+  }
+  if (t == 0) {
+    L.k[q] = k;
+    L.nrot[q] = nrot;
+  }
+}
+
+// Eigenpairs of the m <= kLeafBase entries from s on by implicit QR steps with
+// Wilkinson's shift (Golub and Van Loan, Matrix Computations, 8.3), by eight lanes: every
+// lane carries the same tridiagonal (d in L.D, its couplings in L.zs) and rotates its own
+// row of Q.  A coupling within rounding of its block counts as zero (the criterion of the
+// merges' deflation); the step count is bounded.
+SLRX_DEV void leaf_base(LeafLds& L, double* Q, int s, int m, int row) {
+  double* d = L.D + s;
+  double* e = L.zs + s;
+  double* z = Q + (s + row) * kLeafLd + s;
+  double anorm = 0.0;
+  for (int i = 0; i < m; ++i) {
+    e[i] = L.E[s + i];
+    anorm = fmax(anorm, fmax(fabs(d[i]), i < m - 1 ? fabs(L.E[s + i]) : 0.0));
+  }
+  int hi = m - 1;
+  for (int step = 0; hi > 0 && step < 40 * kLeafBase; ++step) {
+    auto small = [&](int k) {
+      return fabs(e[k]) <= __DBL_EPSILON__ * fmax(0.5 * anorm, fabs(d[k]) + fabs(d[k + 1]));
+    };
+    if (small(hi - 1)) {
+      --hi;
+      continue;
+    }
+    int lo = hi - 1;
+    while (lo > 0 && !small(lo - 1)) --lo;
+    // the eigenvalue of the trailing 2 x 2 block nearer to d[hi]
+    const double eh = e[hi - 1], del = 0.5 * (d[hi - 1] - d[hi]);
+    const double root = hypot(del, eh);
+    const double mu = d[hi] - eh * (eh / (del + copysign(root, del)));
+    double x = d[lo] - mu, y = e[lo];
+    for (int k = lo; k < hi; ++k) {
+      const double r = hypot(x, y);
+      const double c = r > 0.0 ? x / r : 1.0, t = r > 0.0 ? y / r : 0.0;
+      if (k > lo) e[k - 1] = r;
+      const double d0 = d[k], d1 = d[k + 1], ek = e[k];
+      const double g = 2.0 * c * t * ek;
+      d[k] = c * c * d0 + g + t * t * d1;
+      d[k + 1] = t * t * d0 - g + c * c * d1;
+      const double en = c * t * (d1 - d0) + (c - t) * (c + t) * ek;
+      e[k] = en;
+      if (k < hi - 1) {
+        x = en;
+        y = t * e[k + 1];
+        e[k + 1] = c * e[k + 1];
+      }
+      if (row < m) {
+        const double z0 = z[k], z1 = z[k + 1];
+        z[k] = c * z0 + t * z1;
+        z[k + 1] = c * z1 - t * z0;
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(kLeafNT) void k_dc_leaf(DcArgs a0, int depth) {
+  const DcArgs a = dc_at(a0, blockIdx.y);
+  extern __shared__ double lds[];
+  LeafLds& L = *(LeafLds*)lds;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kWaves = kLeafNT / 64;
+  int base, M;
+  leaf_node(a.n, depth, blockIdx.x, base, M);
+  int cur = 0, levels = 0;
+  while (((M - 1) >> levels) + 1 > kLeafBase) ++levels;
+  for (int e = tid; e < kLeafN * kLeafLd; e += kLeafNT) L.Q[0][e] = 0.0;
+  __syncthreads();
+  if (tid < M) {
+    // the couplings at the ends of this entry's block are torn off its diagonal
+    int s = 0, m = M;
+    for (int b = 0; b < levels; ++b) {
+      const int n1 = m / 2;
+      if (tid - s >= n1) {
+        s += n1;
+        m -= n1;
+      } else {
+        m = n1;
+      }
+    }
+    const int i = base + tid;
+    double d = a.D[i];
+    if (tid == s && i >= 1) d -= fabs(a.E[i - 1]);
+    if (tid == s + m - 1 && i <= a.n - 2) d -= fabs(a.E[i]);
+    L.D[tid] = d;
+    L.E[tid] = i <= a.n - 2 ? a.E[i] : 0.0;
+    L.Q[0][tid * kLeafLd + tid] = 1.0;
+  }
+  __syncthreads();
+  if (wave == 0) {  // at most 8 blocks (kLeafN / kLeafBase)
+    int s, m;
+    leaf_node(M, levels, lane >> 3, s, m);
+    if (lane >> 3 < 1 << levels) leaf_base(L, L.Q[0], s, m, lane & 7);
+  }
+  __syncthreads();
+  for (int dep = levels - 1; dep >= 0; --dep) {
+    const int nodes = 1 << dep;
+    double* Q = L.Q[cur];
+    double* Qn = L.Q[cur ^ 1];
+    for (int q = wave; q < nodes; q += kWaves) {
+      int s, m;
+      leaf_node(M, dep, q, s, m);
+      leaf_deflate(L, Q, q, s, m);
+    }
+    __syncthreads();
+    // sorted columns of diag(Q1, Q2), a wave per row
+    for (int r = wave; r < M; r += kWaves) {
+      int s, m;
+      leaf_node(M, dep, L.node[r], s, m);
+      const int n1 = m / 2;
+      if (lane < m) {
+        const int col = L.perm[s + lane];
+        Qn[r * kLeafLd + s + lane] = (r - s < n1) == (col < n1) ? Q[r * kLeafLd + s + col] : 0.0;
+      }
+    }
+    // this level's node of column (tid / 4) for the roots
+    const int g = tid >> 2, gl = tid & 3;
+    int gs = 0, gm = 0, gk = 0;
+    double rho = 0.0;
+    if (g < M) {
+      leaf_node(M, dep, L.node[g], gs, gm);
+      gk = L.k[L.node[g]];
+      rho = 2.0 * fabs(L.E[gs + gm / 2 - 1]);
+    }
+    const int j = g - gs;
+    const bool root = g < M && j < gk;
+    if (root) {
+      int o;
+      double x;
+      secular_root<4>(L.dl + gs, L.zl + gs, gk, j, rho, o, x);
+      if (gl == 0) {
+        L.D[g] = L.dl[gs + o] + x;
+        L.orig[g] = o;
+        L.tau[g] = x;
+      }
+    }
+    __syncthreads();
+    if (tid < M) {  // deflation rotations of row tid
+      const int q = L.node[tid];
+      int s, m;
+      leaf_node(M, dep, q, s, m);
+      double* row = Qn + tid * kLeafLd + s;
+      for (int e = 0; e < L.nrot[q]; ++e) {
+        const int p0 = L.rp[s + e], p1 = L.rq[s + e];
+        const double c = L.rc[s + e], sv = L.rs[s + e];
+        const double x = row[p0], y = row[p1];
+        row[p0] = c * x + sv * y;
+        row[p1] = c * y - sv * x;
+      }
+    }
+    if (root) {  // z_hat
+      const double di = L.dl[g];
+      double p = 1.0;
+      for (int i = gl; i < gk; i += 4) {
+        const double li_di = (L.dl[gs + L.orig[gs + i]] - di) + L.tau[gs + i];
+        p *= i == j ? li_di / rho : li_di / (L.dl[gs + i] - di);
+      }
+      p = quad_prod(p);
+      if (gl == 0) L.zh[g] = copysign(sqrt(fmax(p, 0.0)), L.zsign[g]);
+    }
+    __syncthreads();
+    for (int r = wave; r < M; r += kWaves) {  // final column order, back into Q
+      int s, m;
+      leaf_node(M, dep, L.node[r], s, m);
+      if (lane < m) Q[r * kLeafLd + s + lane] = Qn[r * kLeafLd + s + L.order[s + lane]];
+    }
+    if (root) {  // vectors of the merge
+      const double dor = L.dl[gs + L.orig[g]], tau = L.tau[g];
+      double* u = L.U + g * kLeafLd + gs;
+      double ss = 0.0;
+      for (int i = gl; i < gk; i += 4) {
+        const double v = L.zh[gs + i] / ((L.dl[gs + i] - dor) - tau);
+        u[i] = v;
+        ss += v * v;
+      }
+      const double sc = 1.0 / sqrt(group_sum<4>(ss));
+      for (int i = gl; i < gk; i += 4) u[i] *= sc;
+    }
+    __syncthreads();
+    // Q_node(:, 0:k) = Q(:, 0:k) U, the deflated columns copied: 16 x 16 tiles over the waves
+    int job = 0;
+    for (int q = 0; q < nodes; ++q) {
+      int s, m;
+      leaf_node(M, dep, q, s, m);
+      const int k = L.k[q], nt = (m + 15) / 16;
+      for (int t = 0; t < nt * nt; ++t, ++job) {
+        if (job % kWaves != wave) continue;
+        const int i0 = t / nt * 16, j0 = t % nt * 16;
+        const int l = lane & 15, h = lane >> 4;
+        v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+        for (int kq = 0; kq < k; kq += 4) {
+          const int kk = kq + h;
+          const double av = i0 + l < m && kk < k ? Q[(s + i0 + l) * kLeafLd + s + kk] : 0.0;
+          const double bv = j0 + l < k && kk < k ? L.U[(s + j0 + l) * kLeafLd + s + kk] : 0.0;
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = i0 + h + 4 * v, c = j0 + l;
+          if (r < m && c < m) Qn[(s + r) * kLeafLd + s + c] = c < k ? acc[v] : Q[(s + r) * kLeafLd + s + c];
+        }
+      }
+    }
+    cur ^= 1;
+    __syncthreads();
+  }
+  __syncthreads();
+  if (tid < M) a.D[base + tid] = L.D[tid];
+  for (int r = wave; r < M; r += kWaves)
+    if (lane < M) a.Q[(long)(base + r) * a.n + base + lane] = L.Q[cur][r * kLeafLd + lane];
+}
+
 // Ascending eigenvalues and their permutation (one workgroup): bitonic sort of
 // (value, index) pairs in LDS, padded to a power of two; ties keep index order.
 __global__ __launch_bounds__(1024) void k_dc_sort(DcArgs a0) {
@@ -825,10 +1241,11 @@ int dc_max_n() { return kDcMaxN; }
 hipError_t launch_tdeig(const TdArgs& t, hipStream_t st) {
   const int n = t.n;
   if (n < 1 || n > kDcMaxN) return hipErrorInvalidValue;
-  static LdsLimit lim_deflate, lim_gather, lim_sort;
+  static LdsLimit lim_deflate, lim_gather, lim_sort, lim_leaf;
   hipError_t e = lim_deflate.ensure((const void*)k_dc_deflate, dc_deflate_lds(kDcMaxN));
   if (e == hipSuccess) e = lim_gather.ensure((const void*)k_dc_gather, (size_t)4 * kDcMaxN * sizeof(double));
   if (e == hipSuccess) e = lim_sort.ensure((const void*)k_dc_sort, (size_t)4096 * (sizeof(double) + sizeof(int)));
+  if (e == hipSuccess) e = lim_leaf.ensure((const void*)k_dc_leaf, sizeof(LeafLds));
   if (e != hipSuccess) return e;
   DcArgs a{};
   a.n = n;
@@ -848,9 +1265,13 @@ hipError_t launch_tdeig(const TdArgs& t, hipStream_t st) {
   a.s_wsi = t.s_wsi;
   a.s_wsd = t.s_wsd;
   const int nb = t.nb;
-  k_dc_init<<<dim3((n + 255) / 256, nb), 256, 0, st>>>(a);
+  // subtrees of at most kLeafN entries (sizes of one depth differ by at most one), then
+  // the levels above them, one launch sequence each
+  int depth = 0;
+  while (((n - 1) >> depth) + 1 > kLeafN) ++depth;
+  k_dc_leaf<<<dim3(1 << depth, nb), kLeafNT, sizeof(LeafLds), st>>>(a, depth);
   const int nlev = (int)t.level_start.size() - 1;
-  for (int L = 0; L < nlev; ++L) {
+  for (int L = nlev - depth; L < nlev; ++L) {
     const int first = t.level_start[L], count = t.level_start[L + 1] - first;
     if (count <= 0) continue;
     int mmax = 0;
