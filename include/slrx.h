@@ -352,7 +352,9 @@ slrx_status slrx_release(slrx_server* srv, uint64_t ticket);
  * file, choices are appended to it and read back by later processes.
  * slrx_tri_workgroup_budget: the workgroups per column launch chosen for the
  * tridiagonalisation of nbatch problems of Gram size n (decompositions run
- * together in a batch), or 0 while that shape is still being tuned. */
+ * together in a batch), or 0 while that shape is still being tuned; for sizes whose
+ * columns are reduced in one launch with the matrix in registers (nothing to tune),
+ * the workgroups of that launch. */
 int32_t slrx_tri_workgroup_budget(int32_t n, int32_t nbatch);
 
 /* --- the normal operator without allocation ------------------------------
@@ -386,6 +388,12 @@ const char* slrx_status_str(slrx_status s);
  * allocation of the process.  Other environment variables: SLRX_LOG (print every
  * failure to stderr), SLRX_TUNE_CACHE (the tuner's cache file). */
 void slrx_fault_alloc(int32_t n);
+
+/* Test hook: the next n launches of the register-resident tridiagonalisation give up
+ * waiting at once, as they do after 2 s when the device keeps some of their workgroups
+ * from running (other processes on the GPU); the call that collects the result then
+ * repeats the run by column launches.  n <= 0 switches it off. */
+void slrx_fault_stall(int32_t n);
 
 /* CG strategy of lock-step batches and servers (process-wide): -1 (default)
  * picks, per step shape, by timing both on the first steps (online tuner, after

@@ -478,6 +478,7 @@ static slrx_status check_idle(slrx_plan* pl) {
 extern "C" slrx_status slrx_set_kspace(slrx_plan* pl, const void* b, slrx_mem mem) {
   PlanScope scope(pl);
   STCHK(check_idle(pl));
+  pl->inputs_kept = false;
   STCHK(copy_in(pl, pl->b, b, pl->vol() * sizeof(float2), mem));
   pl->has_b = true;
   pl->prepared = false;
@@ -487,6 +488,7 @@ extern "C" slrx_status slrx_set_kspace(slrx_plan* pl, const void* b, slrx_mem me
 extern "C" slrx_status slrx_set_coils(slrx_plan* pl, int32_t ncoils, const void* C, const void* b, slrx_mem mem) {
   PlanScope scope(pl);
   STCHK(check_idle(pl));
+  pl->inputs_kept = false;
   if (ncoils < 0 || ncoils > SLRX_MAX_COILS)
     return fail(SLRX_EINVAL, "ncoils=%d out of range [0,%d]", (int)ncoils, SLRX_MAX_COILS);
   if (mem != SLRX_MEM_HOST && mem != SLRX_MEM_DEVICE) return fail(SLRX_EINVAL, "bad memory kind %d", (int)mem);
@@ -538,6 +540,7 @@ extern "C" slrx_status slrx_set_coils(slrx_plan* pl, int32_t ncoils, const void*
 extern "C" slrx_status slrx_set_mask(slrx_plan* pl, const uint8_t* S, slrx_mem mem) {
   PlanScope scope(pl);
   STCHK(check_idle(pl));
+  pl->inputs_kept = false;
   STCHK(copy_in(pl, pl->S, S, pl->vol(), mem));
   pl->has_S = true;
   pl->prepared = false;
@@ -547,6 +550,7 @@ extern "C" slrx_status slrx_set_mask(slrx_plan* pl, const uint8_t* S, slrx_mem m
 extern "C" slrx_status slrx_set_init(slrx_plan* pl, const void* x0, slrx_mem mem) {
   PlanScope scope(pl);
   STCHK(check_idle(pl));
+  pl->inputs_kept = false;
   STCHK(copy_in(pl, pl->x0, x0, pl->vol() * sizeof(float2), mem));
   pl->has_init = true;
   pl->prepared = false;
@@ -556,6 +560,7 @@ extern "C" slrx_status slrx_set_init(slrx_plan* pl, const void* x0, slrx_mem mem
 extern "C" slrx_status slrx_clear_init(slrx_plan* pl) {
   PlanScope scope(pl);
   STCHK(check_idle(pl));
+  pl->inputs_kept = false;
   pl->has_init = false;
   pl->prepared = false;
   return SLRX_OK;
@@ -564,6 +569,7 @@ extern "C" slrx_status slrx_clear_init(slrx_plan* pl) {
 extern "C" slrx_status slrx_set_filter(slrx_plan* pl, int32_t N1, int32_t N2, int32_t M) {
   PlanScope scope(pl);
   STCHK(check_idle(pl));
+  pl->inputs_kept = false;
   slrx_dims d = pl->d;
   d.N1 = N1;
   d.N2 = N2;
@@ -581,6 +587,7 @@ extern "C" slrx_status slrx_set_filter(slrx_plan* pl, int32_t N1, int32_t N2, in
 extern "C" slrx_status slrx_set_params(slrx_plan* pl, const slrx_params* prm) {
   PlanScope scope(pl);
   STCHK(check_idle(pl));
+  pl->inputs_kept = false;
   STCHK(validate_params(prm));
   STCHK(validate_combo(pl->d, *prm));
   pl->prm = *prm;
@@ -640,6 +647,7 @@ slrx_status slrx::enqueue_run(slrx_plan* pl) {
   pl->ran = false;
   pl->run_irls = nirls;
   pl->run_timing = timing;
+  pl->inputs_kept = true;
   return SLRX_OK;
 }
 
@@ -656,6 +664,20 @@ slrx_status slrx::finish(slrx_plan* pl) {
   pl->ran = true;
   std::vector<rocblas_int> info(kInfoEntries);
   HIPCHK(hipMemcpy(info.data(), pl->info, kInfoEntries * sizeof(rocblas_int), hipMemcpyDeviceToHost));
+  if (info[kInfoStalled] != 0) {
+    // a resident tridiagonalisation gave up waiting for its workgroups: once more, by
+    // column launches, from the inputs the plan still holds
+    pl->ran = false;
+    if (pl->tri_columns || !pl->inputs_kept)
+      return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running%s",
+                  pl->tri_columns ? "" : ", and inputs were set before the result was collected");
+    HIPCHK(hipMemsetAsync(pl->flag + 8, 0, sizeof(int), pl->stream));
+    pl->tri_columns = true;
+    slrx_status again = enqueue_run(pl);
+    if (again == SLRX_OK) again = finish(pl);
+    pl->tri_columns = false;
+    return again;
+  }
   if (info[kInfoNonfinite] != 0) {
     pl->ran = false;
     return fail(SLRX_ENUMERIC, "non-finite Gram matrix (non-finite data, initial guess or iterate)");
@@ -893,11 +915,22 @@ extern "C" slrx_status slrx_step_weights(slrx_plan* pl, double eps, double* lam_
   if (pl && pl->voxel()) return step_weights_voxel(pl, eps, lam_out, H_out, E_out, mem);
   if (pl && pl->direct()) return fail(SLRX_EINVAL, "SLRX_FLAG_DIRECT plans run whole reconstructions only");
   STCHK(ensure_prepared(pl));
-  STCHK(step_gram(pl));
-  STCHK(step_eigh(pl, -1));
-  HIPCHK(hipMemcpyAsync(pl->scal, &eps, sizeof(double), hipMemcpyHostToDevice, pl->stream));
-  HIPCHK(hipStreamSynchronize(pl->stream));
-  STCHK(step_weights(pl, -1, false, 1.0, nullptr, nullptr, H_out != nullptr));
+  for (int attempt = 0;; ++attempt) {
+    HIPCHK(hipMemsetAsync(pl->info + kInfoStalled, 0, sizeof(rocblas_int), pl->stream));
+    STCHK(step_gram(pl));
+    STCHK(step_eigh(pl, -1));
+    HIPCHK(hipMemcpyAsync(pl->scal, &eps, sizeof(double), hipMemcpyHostToDevice, pl->stream));
+    HIPCHK(hipStreamSynchronize(pl->stream));
+    STCHK(step_weights(pl, -1, false, 1.0, nullptr, nullptr, H_out != nullptr));
+    int stalled = 0;
+    HIPCHK(hipMemcpyAsync(&stalled, pl->info + kInfoStalled, sizeof(int), hipMemcpyDeviceToHost, pl->stream));
+    HIPCHK(hipStreamSynchronize(pl->stream));
+    pl->tri_columns = false;
+    if (!stalled) break;
+    if (attempt > 0) return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running");
+    HIPCHK(hipMemsetAsync(pl->flag + 8, 0, sizeof(int), pl->stream));
+    pl->tri_columns = true;  // once more, by column launches
+  }
   const slrx_dims& d = pl->d;
   const size_t s = (size_t)d.N1 * d.N2 * d.M;
   const size_t W = (size_t)d.M * (d.M + 1) / 2;

@@ -71,7 +71,7 @@ static size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 // Layout of the buffers for nb problems of size n: every matrix-sized buffer
 // per problem, the vectors for all of them.
 struct GroupLayout {
-  size_t sA, sQ, sWi, sWd, sB, sv, sd, total;
+  size_t sA, sQ, sWi, sWd, sB, sv, sd, total;  // and 256 bytes for the give-up flag
 };
 static GroupLayout group_layout(int n, int nb) {
   GroupLayout L;
@@ -83,7 +83,7 @@ static GroupLayout group_layout(int n, int nb) {
   L.sB = al(bt_scratch_elems(n) * sizeof(double2));
   L.sv = al((size_t)nb * n * sizeof(double2));
   L.sd = al((size_t)nb * n * sizeof(double));
-  L.total = (size_t)nb * (3 * L.sA + L.sQ + L.sWi + L.sWd + L.sB) + 5 * L.sv + 2 * L.sd;
+  L.total = (size_t)nb * (3 * L.sA + L.sQ + L.sWi + L.sWd + L.sB) + 5 * L.sv + 2 * L.sd + 256;
   return L;
 }
 static size_t tree_bytes(int n) { return std::max<size_t>((size_t)4 * n, 4) * sizeof(int); }
@@ -185,6 +185,8 @@ static slrx_status group_reserve(BatchEig& be, int n, int nb, EigGroup*& out) {
     e.trip[1] = (double2*)take(sv);
     e.D = (double*)take(sd);
     e.E = (double*)take(sd);
+    e.stall = (int*)take(256);
+    HIPCHK(hipMemset(e.stall, 0, 256));
     e.sA = (long)(sA / sizeof(double2));
     e.sZ = e.sA;
     e.sQ = (long)(sQ / sizeof(double));
@@ -213,6 +215,7 @@ slrx_status slrx::engine_begin(slrx_plan* pl) {
   pl->ran = false;
   pl->run_irls = pl->prm.n_irls;
   pl->run_timing = false;
+  pl->inputs_kept = true;
   return SLRX_OK;
 }
 
@@ -396,6 +399,7 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
     bool settled = true;
     for (auto& kv : groups) {
       const int nb = (int)kv.second.size();
+      if (tri_resident(kv.first)) continue;  // no launch shape to tune
       const int c = tune_choice(TUNE_TRI, kv.first, nb, 0);
       settled = settled && c >= 0 && tune_choice(TUNE_TRI_ACCESS, kv.first, nb, c) >= 0;
     }
@@ -441,7 +445,8 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
       slrx_plan* pl = g[i];
       const int it = pl->it_next;
       HIPCHK(hipStreamWaitEvent(pl->stream, be.ev, 0));
-      STCHK(step_weights(pl, it, it == 0, pl->prm.gamma, e.Z + (size_t)i * e.sZ, e.D + (size_t)i * n));
+      STCHK(step_weights(pl, it, it == 0, pl->prm.gamma, e.Z + (size_t)i * e.sZ, e.D + (size_t)i * n, false,
+                         e.stall));
       HIPCHK(hipEventRecord(pl->ev_step, pl->stream));
       HIPCHK(hipStreamWaitEvent(be.stream, pl->ev_step, 0));
       if (grouped && cg_groupable(pl)) {

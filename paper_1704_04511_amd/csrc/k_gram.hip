@@ -187,6 +187,7 @@ __global__ void k_eps(WeightArgs a) {
   *a.eps = e;
   if (a.lam_max_out) *a.lam_max_out = lmax;
   if (a.eps_out) *a.eps_out = e;
+  if (a.stall && *a.stall) *a.stalled = 1;
 }
 
 // V = U diag(sqrt(alpha)), alpha_k = (max(lambda_k, 0) + eps)^(p/2 - 1), stored K-major.

@@ -2,10 +2,12 @@
 // tridiagonal form, R = Q T Q^H (FP64), first stage of the eigen-decomposition
 // in the weight update (Sec. III.B, Algorithm 1 step 1).
 //
-// Column k needs a global matrix-vector product with the trailing block, so
-// every column is one launch (the launch boundary is the grid-wide sync; a
-// software barrier between persistent workgroups costs as much or more on this
-// part).  A launch for column k:
+// Column k needs a global matrix-vector product with the trailing block, and so
+// a grid-wide exchange.  Sizes whose matrix fits the registers of 256 workgroups
+// (129 to 1280) are reduced in one launch (k_tri_res, below); other sizes, calls
+// on a stream that is being captured, and runs repeated after a resident launch
+// gave up use one launch per column, the launch boundary being the exchange.  A
+// launch for column k:
 //   * in every workgroup (redundantly, identical arithmetic): finishes the
 //     previous reflector's w = tau p - |tau|^2/2 (p^H v) v from the previous
 //     launch's p = A v, corrects row k with the pending rank-2 update
@@ -14,8 +16,8 @@
 //     of LAPACK's zlarfg);
 //   * on its rows i > k: applies the pending rank-2 update and accumulates
 //     p_i = sum_j A_ij v_j for the next launch.
-// The time of a launch is the serial chain of the reflector, not the traffic
-// of the trailing block, so the chain is kept short: thread t holds the
+// Where the trailing block is small the time of a launch is the serial chain of
+// the reflector, not the traffic of the block, so the chain is kept short: thread t holds the
 // entries j = k + t + 256 u of every vector in registers (the same entries of
 // every row it updates), and a launch makes exactly three block reductions
 // (p^H v, the norm of the column, the row products), each a fixed DPP tree in
@@ -29,10 +31,14 @@
 // stored as LAPACK's zhetrd (lower) stores them: v(k+2:n) in column k of the
 // column-major matrix Vst below the subdiagonal, tau(k), diagonal D, real
 // subdiagonal E.
+#include <atomic>
+#include <mutex>
 #include <type_traits>
+#include <vector>
 
 #include "common.h"
 #include "kernels.h"
+#include "../../include/slrx.h"
 
 namespace slrx {
 
@@ -83,19 +89,35 @@ SLRX_DEV double dpp_all(double v) {
   return __hiloint2double(hi, lo);
 }
 
-// Sum over the 64 lanes of a wave in a fixed tree (pairs, quads, half rows,
-// rows, then rows 0+1 and 2+3 and the two halves); every lane gets the total.
-// Call with all 64 lanes active.
-SLRX_DEV double wave_total(double v) {
+// The two values of lanes 16 apart within a half-wave, added: the even row of 16
+// lanes gets the sums of x over both rows, the odd row those of y
+// (v_permlane16_swap exchanges the odd row of its first operand with the even row
+// of the second).
+SLRX_DEV double pair_rows(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(y), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// The same for lanes 32 apart: lanes 0-31 get the sums of x over both halves of the wave,
+// lanes 32-63 those of y.
+SLRX_DEV double pair_halves(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(y), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// Sum over each row of 16 lanes (a fixed tree); every lane of the row gets it.
+SLRX_DEV double row_total(double v) {
   v += dpp_all<0xB1>(v);   // quad_perm [1,0,3,2]
   v += dpp_all<0x4E>(v);   // quad_perm [2,3,0,1]
   v += dpp_all<0x141>(v);  // row_half_mirror
   v += dpp_all<0x140>(v);  // row_mirror
-  v += dpp_mov<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-  v += dpp_mov<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-  return __hiloint2double(hi, lo);
+  return v;
+}
+// Sum over the 64 lanes of a wave in a fixed tree; every lane gets the total.
+// Call with all 64 lanes active.
+SLRX_DEV double wave_total(double v) {
+  v = pair_halves(v, v);
+  return row_total(pair_rows(v, v));
 }
 SLRX_DEV double2 wave_total2(double2 v) { return make_double2(wave_total(v.x), wave_total(v.y)); }
 // The four wave sums of an exchange slot, added in wave order.
@@ -311,23 +333,6 @@ constexpr int kTailH = kTailNT / 32;  // half-waves
 __host__ __device__ inline int tail_voff(int L, int kk) { return kk * (2 * L - kk - 1) / 2; }
 inline size_t tail_lds(int L) { return (size_t)tail_voff(L, L - 1) * sizeof(double2); }
 
-// The two values of lanes 16 apart within a half-wave, added: the even row of 16
-// lanes gets the sums of x over both rows, the odd row those of y
-// (v_permlane16_swap exchanges the odd row of its first operand with the even row
-// of the second).
-SLRX_DEV double pair_rows(double x, double y) {
-  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(y), false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(y), false, false);
-  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-// Sum over each row of 16 lanes (a fixed tree); every lane of the row gets it.
-SLRX_DEV double row_total(double v) {
-  v += dpp_all<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_all<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_all<0x141>(v);  // row_half_mirror
-  v += dpp_all<0x140>(v);  // row_mirror
-  return v;
-}
 // Sum over each half-wave of 32 lanes; every lane of it gets the total.
 SLRX_DEV double half_total(double v) { return row_total(pair_rows(v, v)); }
 
@@ -470,13 +475,21 @@ SLRX_DEV void tail_columns(TailState<C>& st, TailLds& q, double2* vl, int L, int
 
 // C: column slots per lane (L <= 32 C); 4 C rows per half-wave.
 template <int C>
-__global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0) {
+__global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0, const double2* vpend, const double2* ppend,
+                                                      const int* stall) {
   constexpr int R = 4 * C;
   extern __shared__ double2 vl[];  // reflectors, packed (tail_voff)
   __shared__ TailLds q;
   const int n = a.n, L = n - k0;
   const int b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 31, h = tid >> 5;
+  if (stall && *stall) {  // the resident launch gave up: a finite result that is not used
+    for (int i = tid; i < n; i += kTailNT) {
+      a.D[(size_t)b * n + i] = a.E[(size_t)b * n + i] = 0.0;
+      a.tau[(size_t)b * n + i] = make_double2(0.0, 0.0);
+    }
+    return;
+  }
   const double2* Aw = a.Aw + (size_t)b * a.strideA;
   const double2 zero = make_double2(0.0, 0.0);
   TailState<C> st;
@@ -493,8 +506,8 @@ __global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0) {
   st.tau = zero;
   if (k0 > 0) st.tau = a.tau[(size_t)b * n + k0 - 1];
   if (tid < kTriTail) {
-    const double2* vprev = ((k0 & 1) ? a.vbuf[0] : a.vbuf[1]) + (size_t)b * n + k0;
-    const double2* pprev = ((k0 & 1) ? a.pbuf[0] : a.pbuf[1]) + (size_t)b * n + k0;
+    const double2* vprev = vpend + (size_t)b * n + k0;
+    const double2* pprev = ppend + (size_t)b * n + k0;
     double2 x = zero, y = zero;
     if (k0 > 0 && tid < L) {
       x = vprev[tid];
@@ -537,13 +550,357 @@ __global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0) {
   }
 }
 
+// ------------------------------------------------------- resident reduction
+// The columns before the last ones in ONE launch, for n in (kTriResMin, 1280]: the
+// trailing block stays in registers (n = 1125: 20 MB over 225 workgroups), so a column
+// costs no pass over it and no launch, only an exchange: p = A v of every row and the
+// next column have to reach every workgroup.
+//   Workgroup g of G holds the rows g + G r, thread t of it their columns t + 256 u (the
+// dealt-out rows keep the workgroups balanced as the block shrinks).  Every workgroup
+// repeats the reflector, as in k_tri_col, from the vectors of the exchange.
+//   The exchange has one hop: a workgroup stores the entries of its rows, and everybody
+// polls the vector itself.  Each column has its own vectors (P: p, C: the next column,
+// write-once, column k at k n), filled with a bit pattern that no arithmetic produces (all
+// ones), so an entry that differs has arrived; entries are read and written as atomic words
+// of 8 bytes at device scope.  No counter, no second round trip for a flag: an exchange
+// through an agent-scope counter costs 6.2 us over 256 workgroups, this one 0.7 us (n = 140)
+// to 1.2 us (n = 1125).
+//   What bounds it: the chain of a column.  Measured in cycles per column at n = 405 (135
+// workgroups) and n = 1125 (225): exchange 1680 and 2430, d 360 and 420, norm 710 and 820,
+// reflector 760 and 880, rows 980 and 1490, publishing 330 and 330 (about 2 GHz).  Whole
+// reductions with the last columns: 961 us (n = 405) and 3440 us (n = 1125), where the
+// column launches take 1503 and 6970 us (4.4 to 11.6 us each, the longer ones bound by
+// reading and writing the trailing block).
+//   Every wait ends: a thread that has polled for `wait` ticks, or sees that another has,
+// gives up, raises `stall`, and its workgroup leaves the kernel at the next barrier.  The
+// last-columns kernel then writes zeros for the problem and the host, which finds the
+// flag, repeats the run by column launches.  This only happens where workgroups of the
+// launch are kept from running (the launches of this process that may run at a time are
+// limited to what fits the chip, res_admit).
+constexpr int kTriResMin = 128;   // largest n left to the column launches
+constexpr unsigned long long kResEmpty = ~0ull;
+
+// An element of a column's vector as two words.
+struct ResWords {
+  unsigned long long re, im;
+};
+SLRX_DEV ResWords res_load(const double2* p) {
+  const unsigned long long* w = (const unsigned long long*)p;
+  return ResWords{__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                  __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+}
+SLRX_DEV void res_store(double2* p, double2 v) {
+  unsigned long long* w = (unsigned long long*)p;
+  __hip_atomic_store(w, (unsigned long long)__double_as_longlong(v.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(w + 1, (unsigned long long)__double_as_longlong(v.y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// One of two values (by value: a select of their addresses would put them in memory).
+SLRX_DEV double2 pick(bool c, double2 a, double2 b) {
+  double x = b.x, y = b.y;
+  if (c) {
+    x = a.x;
+    y = a.y;
+  }
+  return make_double2(x, y);
+}
+SLRX_DEV bool res_missing(ResWords w) { return w.re == kResEmpty || w.im == kResEmpty; }
+SLRX_DEV double2 res_value(ResWords w) {
+  return make_double2(__longlong_as_double((long long)w.re), __longlong_as_double((long long)w.im));
+}
+
+__global__ __launch_bounds__(256) void k_tri_res_fill(TriResArgs x, long n2, int nb) {
+  const long stride = (long)gridDim.x * 256, i0 = (long)blockIdx.x * 256 + threadIdx.x;
+  const unsigned long long e = kResEmpty;
+  for (int b = 0; b < nb; ++b) {
+    ulonglong2* P = (ulonglong2*)(x.P + b * x.sP);
+    ulonglong2* C = (ulonglong2*)(x.C + b * x.sC);
+    for (long i = i0; i < n2; i += stride) P[i] = C[i] = make_ulonglong2(e, e);
+  }
+  if (i0 == 0) *x.stall = 0;
+}
+
+// Rows per workgroup by column slots U.  One problem (or few) is split finely: a column
+// costs its serial chain, and fewer rows shorten it until the exchange among more
+// workgroups costs as much (n = 405: 2, 3, 4, 6, 12 rows take 929, 949, 1005, 1086, 1349
+// us).  Batches take as many rows as fit 256 registers per thread, so that more problems run
+// at a time.
+__host__ __device__ constexpr int res_rows(int U, bool many) {
+  return many ? (U == 1 ? 8 : U == 2 ? 12 : U == 3 ? 8 : U == 4 ? 6 : 5) : (U == 1 ? 2 : U == 2 ? 3 : U);
+}
+template <int U, int R>
+struct ResState {
+  double2 A[R][U], v[U], tau;
+};
+template <int U, int R>
+struct ResLds {
+  double2 v[2][256 * U];         // v by column parity
+  double2 pown[R];               // p of this workgroup's rows
+  double2 xcol[R];               // the next column's entries in them
+  double xc[4][R + 1][2];        // row sums by wave (rows in pairs)
+  double xa[4], xb[4];           // wave sums of d and of the norm
+  double2 pk, vk, ck, alpha;     // entries k and k + 1
+  int dead;
+};
+
+// Columns kk0 .. kk1-1, kk / 256 == US.  false: the workgroup gave up.
+template <int U, int R, int US>
+SLRX_DEV bool res_columns(ResState<U, R>& st, ResLds<U, R>& q, const TriArgs& a, const TriResArgs& x, int g, int G, int b,
+                          int kk0, int kk1) {
+  constexpr int R0 = US * 256 / ((256 * U + R - 1) / R);  // rows before R0 are finished (G <= ceil(256 U / R))
+  const int n = a.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double2 zero = make_double2(0.0, 0.0);
+  for (int k = kk0; k < kk1; ++k) {
+    const int par = k & 1;
+    // 0. p of the pending reflector and column k, once every entry has arrived
+    double2 p[U], col[U];
+    if (k == 0) {
+#pragma unroll
+      for (int u = US; u < U; ++u) {
+        const int j = tid + 256 * u;
+        p[u] = col[u] = zero;
+        if (j < n) col[u] = dconj(a.Aw[(size_t)b * a.strideA + j]);
+      }
+    } else {
+      const double2* vp = x.P + b * x.sP + (size_t)(k - 1) * n;
+      const double2* vc = x.C + b * x.sC + (size_t)(k - 1) * n;
+      ResWords wp[U], wc[U];
+      bool miss = false;
+#pragma unroll
+      for (int u = US; u < U; ++u) {
+        const int j = tid + 256 * u;
+        const bool need = j >= k && j < n;
+        wp[u] = wc[u] = ResWords{need ? kResEmpty : 0, 0};
+      }
+      // The first look comes when the entries are due.  A look that finds them missing
+      // costs the whole vector once more, from every workgroup, and delays the stores it
+      // waits for: n = 1125 took 4780 us without a delay and 3440 us with it.
+      // Due: about 450 cycles after the own entries, and the time that the vectors of all
+      // workgroups take.
+      for (int i = 7 + ((n - k) * (int)(gridDim.x * gridDim.y) >> 15); i > 0; --i) __builtin_amdgcn_s_sleep(1);
+      unsigned long long t0 = 0;
+      for (int spin = 0;; ++spin) {
+        miss = false;
+#pragma unroll
+        for (int u = US; u < U; ++u) {
+          const int j = tid + 256 * u;
+          if (res_missing(wp[u])) wp[u] = res_load(vp + j);
+          if (res_missing(wc[u])) wc[u] = res_load(vc + j);
+        }
+#pragma unroll
+        for (int u = US; u < U; ++u) miss = miss || res_missing(wp[u]) || res_missing(wc[u]);
+        if (__ballot(miss) == 0) break;
+        if ((spin & 63) == 63) {  // give up after `wait` ticks, or if anybody has
+          const unsigned long long t = wall_clock64();
+          if (t0 == 0) t0 = t;
+          if (t - t0 > x.wait || __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+            if (lane == 0) {
+              __hip_atomic_store(x.stall, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              q.dead = 1;
+            }
+            break;
+          }
+        }
+      }
+#pragma unroll
+      for (int u = US; u < U; ++u) {
+        p[u] = res_value(wp[u]);
+        col[u] = res_value(wc[u]);
+      }
+    }
+    // 1. d = Re p^H v; the entries at k
+    double d = 0.0;
+#pragma unroll
+    for (int u = US; u < U; ++u) d = fma(p[u].x, st.v[u].x, fma(p[u].y, st.v[u].y, d));
+    d = wave_total(d);
+    if (lane == 0) q.xa[wave] = d;
+    if (tid == (k & 255)) {
+      q.pk = p[US];
+      q.vk = st.v[US];
+      q.ck = col[US];
+    }
+    __syncthreads();
+    if (q.dead) return false;
+    const double2 tau = st.tau, pk = q.pk, vk = q.vk;
+    const double cd = -0.5 * (tau.x * tau.x + tau.y * tau.y) * (((q.xa[0] + q.xa[1]) + q.xa[2]) + q.xa[3]);
+    const double2 wk = dadd(dmul(tau, pk), dscale(vk, cd));
+    const double dk = q.ck.x - 2.0 * (vk.x * wk.x + vk.y * wk.y);
+    // 2. w, column k with the pending update, its norm below k + 1
+    double2 w[U];
+    double xn = 0.0;
+#pragma unroll
+    for (int u = US; u < U; ++u) {
+      w[u] = dadd(dmul(tau, p[u]), dscale(st.v[u], cd));
+      col[u] = sub_conj(sub_conj(col[u], st.v[u], wk), w[u], vk);
+      if (tid + 256 * u >= k + 2) xn = fma(col[u].x, col[u].x, fma(col[u].y, col[u].y, xn));
+    }
+    xn = wave_total(xn);
+    if (lane == 0) q.xb[wave] = xn;
+    // entry k + 1: thread (k + 1) mod 256, whose slot is the next one at the end of a slot
+    const bool wrap = (k & 255) == 255;
+    constexpr int UN = US + 1 < U ? US + 1 : US;
+    if (tid == ((k + 1) & 255)) q.alpha = pick(wrap, col[UN], col[US]);
+    __syncthreads();
+    const double xn2 = ((q.xb[0] + q.xb[1]) + q.xb[2]) + q.xb[3];
+    const double2 alpha = q.alpha;
+    // 3. reflector k
+    double beta;
+    double2 taun, scale;
+    if (xn2 == 0.0 && alpha.y == 0.0) {
+      taun = zero;
+      beta = alpha.x;
+      scale = zero;
+    } else {
+      const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn2);
+      beta = alpha.x >= 0.0 ? -nrm : nrm;
+      const double ib = 1.0 / beta;
+      taun = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
+      const double2 den = make_double2(alpha.x - beta, alpha.y);  // scale = 1 / (alpha - beta)
+      const double id = 1.0 / (den.x * den.x + den.y * den.y);
+      scale = make_double2(den.x * id, -den.y * id);
+    }
+    double2 vn[U];
+#pragma unroll
+    for (int u = US; u < U; ++u) {
+      const int j = tid + 256 * u;
+      double2 y = dmul(col[u], scale);  // 0 beyond the matrix
+      if (j < k + 2) y = make_double2(j == k + 1 ? 1.0 : 0.0, 0.0);
+      vn[u] = y;
+      q.v[par][j] = y;
+    }
+    if (g == k % G) {  // its row k is finished
+      double2* Vst = a.Vst + (size_t)b * a.strideA;
+#pragma unroll
+      for (int u = US; u < U; ++u) {
+        const int j = tid + 256 * u;
+        if (j > k && j < n) Vst[(size_t)k * n + j] = j == k + 1 ? make_double2(beta, 0.0) : vn[u];
+      }
+      if (tid == 0) {
+        a.D[(size_t)b * n + k] = dk;
+        a.E[(size_t)b * n + k] = beta;
+        a.tau[(size_t)b * n + k] = taun;
+      }
+    }
+    // 4. the rows: pending update, p_i = sum_j A_ij v_j, the entries of column k + 1.
+    //    p and v of the pending reflector at the rows are in LDS (own p, v of all).
+    double t[R + 1];
+#pragma unroll
+    for (int r = R0; r < R; ++r) {
+      const int i = min(g + G * r, n - 1);
+      const double2 vi = q.v[par ^ 1][i], wi = dadd(dmul(tau, q.pown[r]), dscale(vi, cd));
+      double2 acc = zero;
+#pragma unroll
+      for (int u = US; u < U; ++u) {
+        const double2 e = sub_conj(sub_conj(st.A[r][u], vi, w[u]), wi, st.v[u]);
+        st.A[r][u] = e;
+        acc = add_mul(acc, e, vn[u]);
+      }
+      t[r] = pair_halves(acc.x, acc.y);
+    }
+    t[R] = 0.0;
+    if (tid == ((k + 1) & 255)) {
+#pragma unroll
+      for (int r = R0; r < R; ++r) q.xcol[r] = pick(wrap, st.A[r][UN], st.A[r][US]);
+    }
+    // rows of 16 lanes: re of row r, re of row r + 1, im of row r, im of row r + 1
+#pragma unroll
+    for (int r = R0; r < R; r += 2) t[r] = row_total(pair_rows(t[r], t[r + 1]));
+    if ((lane & 15) == 0) {
+#pragma unroll
+      for (int r = R0; r < R; r += 2) q.xc[wave][r + (lane >> 4 & 1)][lane >> 5] = t[r];
+    }
+    __syncthreads();
+    {
+      const int r = R0 + (tid & 63), i = g + G * r;
+      if (r < R) {
+        if (wave == 0) {
+          const double2 s = make_double2(((q.xc[0][r][0] + q.xc[1][r][0]) + q.xc[2][r][0]) + q.xc[3][r][0],
+                                         ((q.xc[0][r][1] + q.xc[1][r][1]) + q.xc[2][r][1]) + q.xc[3][r][1]);
+          q.pown[r] = s;
+          if (i > k && i < n) res_store(x.P + b * x.sP + (size_t)k * n + i, s);
+        } else if (wave == 1) {
+          if (i > k && i < n) res_store(x.C + b * x.sC + (size_t)k * n + i, q.xcol[r]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = US; u < U; ++u) st.v[u] = vn[u];
+    st.tau = taun;
+  }
+  return true;
+}
+
+// U: column slots per thread (n <= 256 U); workgroup (g, problem b) = (blockIdx.x, blockIdx.y);
+// columns 0 .. k0-1, k0 = n - kTriTail.
+template <int U, int R>
+__global__ __launch_bounds__(256) void k_tri_res(TriArgs a, TriResArgs x, int k0) {
+  __shared__ ResLds<U, R> q;
+  const int n = a.n, g = blockIdx.x, G = gridDim.x, b = blockIdx.y, tid = threadIdx.x;
+  double2* Aw = a.Aw + (size_t)b * a.strideA;
+  const double2 zero = make_double2(0.0, 0.0);
+  ResState<U, R> st;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = g + G * r, j = tid + 256 * u;
+      double2 e = zero;
+      if (i < n && j < n) e = Aw[(size_t)i * n + j];
+      st.A[r][u] = e;
+    }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    st.v[u] = zero;
+    q.v[1][tid + 256 * u] = zero;
+  }
+  st.tau = zero;
+  if (tid < R) q.pown[tid] = zero;
+  if (tid == 0) q.dead = x.wait == 0 && g == G - 1;  // wait 0: give up at once (tests)
+  __syncthreads();
+  if (q.dead) {
+    if (tid == 0) __hip_atomic_store(x.stall, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  if (!res_columns<U, R, 0>(st, q, a, x, g, G, b, 0, min(k0, 256))) return;
+  if constexpr (U > 1)
+    if (!res_columns<U, R, 1>(st, q, a, x, g, G, b, 256, min(k0, 512))) return;
+  if constexpr (U > 2)
+    if (!res_columns<U, R, 2>(st, q, a, x, g, G, b, 512, min(k0, 768))) return;
+  if constexpr (U > 3)
+    if (!res_columns<U, R, 3>(st, q, a, x, g, G, b, 768, min(k0, 1024))) return;
+  if constexpr (U > 4)
+    if (!res_columns<U, R, 4>(st, q, a, x, g, G, b, 1024, min(k0, 1280))) return;
+  // the trailing block and the pending reflector for the last-columns kernel
+  __syncthreads();
+  const size_t o = (size_t)b * n;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = g + G * r;
+    if (i < k0 || i >= n) continue;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = tid + 256 * u;
+      if (j >= k0 && j < n) Aw[(size_t)i * n + j] = st.A[r][u];
+    }
+    if (tid == 0) a.pbuf[0][o + i] = q.pown[r];
+  }
+  if (g == 0)
+    for (int j = k0 + tid; j < n; j += 256) a.vbuf[0][o + j] = q.v[(k0 - 1) & 1][j];
+}
+
 template <int C>
-static hipError_t launch_tail(const TriArgs& a, int nbatch, int k0, hipStream_t s) {
+static hipError_t launch_tail_c(const TriArgs& a, int nbatch, int k0, int par, const int* stall, hipStream_t s) {
   static LdsLimit lim;
   const hipError_t e = lim.ensure((const void*)k_tri_tail<C>, tail_lds(32 * C));
   if (e != hipSuccess) return e;
-  k_tri_tail<C><<<dim3(1, nbatch), kTailNT, tail_lds(a.n - k0), s>>>(a, k0);
+  k_tri_tail<C><<<dim3(1, nbatch), kTailNT, tail_lds(a.n - k0), s>>>(a, k0, a.vbuf[par], a.pbuf[par], stall);
   return hipGetLastError();
+}
+// Columns k0.. of every problem; v and p of the pending reflector in buffer `par`.
+static hipError_t launch_tail(const TriArgs& a, int nbatch, int k0, int par, const int* stall, hipStream_t s) {
+  const int L = a.n - k0;
+  if (L <= 32) return launch_tail_c<1>(a, nbatch, k0, par, stall, s);
+  if (L <= 64) return launch_tail_c<2>(a, nbatch, k0, par, stall, s);
+  return launch_tail_c<3>(a, nbatch, k0, par, stall, s);
 }
 
 int tri_max_n() { return 3000; }
@@ -559,6 +916,7 @@ static void launch_col(const TriArgs& a, int nbatch, int rows, bool stream, hipS
 // Workgroup budgets per column launch (all problems of a batch together) the
 // tuner chooses from: each workgroup recomputes the reflector, so many small
 // problems want more rows per workgroup than one large one.
+// (Timings at 1125 are from when that size used column launches.)
 // One problem also tries 256 with long columns split so that every row of a
 // workgroup is loaded at kernel entry (kTriRB rows each, up to 320 workgroups):
 // 8.03 against 8.13 ms per 1125 x 1125 decomposition when measured.  The row
@@ -598,10 +956,163 @@ hipError_t launch_tridiag(const TriArgs& base, int nbatch, hipStream_t s, int ca
     else if (u <= 10) launch_col<10>(a, nbatch, rows, stream, s);
     else launch_col<12>(a, nbatch, rows, stream, s);
   }
-  const int L = n - k0;
-  if (L <= 32) return launch_tail<1>(a, nbatch, k0, s);
-  if (L <= 64) return launch_tail<2>(a, nbatch, k0, s);
-  return launch_tail<3>(a, nbatch, k0, s);
+  return launch_tail(a, nbatch, k0, (k0 + 1) & 1, nullptr, s);
+}
+
+// Workgroups of a resident launch wait for each other, so all of them have to fit the
+// chip together with those of the other resident launches that may run.  256 threads of
+// at most 256 registers leave room for two workgroups per CU (512 on 256 CUs, spread
+// evenly over the XCDs by the dispatcher).  Per stream (its launches run one after
+// another) the last launch is kept; a new one waits, on the device, for the streams whose
+// launches would not fit beside it, the ones used longest ago first.  So of launches that
+// may run together the one admitted last has left room for all the others.  Ordinary
+// kernels only delay a resident launch.
+namespace {
+struct ResStream {
+  hipStream_t s;
+  hipEvent_t done;  // its last launch
+  int wgs;          // its largest launch that may not have run yet
+};
+struct ResDevice {
+  std::mutex mu;
+  std::vector<ResStream> streams;  // in order of their last launch; those that have run are dropped
+  std::vector<hipEvent_t> spare;
+};
+ResDevice g_res[32];
+std::atomic<int> g_res_stall{0};  // tests: resident launches that give up at once
+
+// Workgroups of resident launches that the current device holds at a time (0: unknown),
+// by the kernel with the most registers and LDS; at most two per CU are counted.
+int res_capacity() {
+  static std::atomic<int> known[32];  // capacity + 1
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  std::atomic<int>& c = known[dev & 31];
+  if (c.load() == 0) {
+    int cus = 0, per = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_tri_res<5, res_rows(5, true)>, 256, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return 0;
+    }
+    c.store(cus * (per < 2 ? per : 2) + 1);
+  }
+  return c.load() - 1;
+}
+
+// Room for wgs workgroups on stream s (d.mu held); the stream's entry is the last one then.
+hipError_t res_admit(ResDevice& d, int wgs, hipStream_t s) {
+  ResStream mine{s, nullptr, wgs};
+  std::vector<ResStream> keep;
+  for (const ResStream& t : d.streams) {
+    const bool ran = hipEventQuery(t.done) == hipSuccess;
+    (void)hipGetLastError();
+    if (t.s == s) {
+      mine.done = t.done;
+      if (!ran && t.wgs > mine.wgs) mine.wgs = t.wgs;
+    } else if (ran) {
+      d.spare.push_back(t.done);
+    } else {
+      keep.push_back(t);
+    }
+  }
+  hipError_t e = hipSuccess;
+  int sum = wgs;
+  for (size_t i = keep.size(); i-- > 0 && e == hipSuccess;) {
+    if (sum + keep[i].wgs <= res_capacity()) sum += keep[i].wgs;
+    else e = hipStreamWaitEvent(s, keep[i].done, 0);
+  }
+  if (!mine.done) {
+    if (d.spare.empty()) {
+      const hipError_t ec = hipEventCreateWithFlags(&mine.done, hipEventDisableTiming);
+      if (ec != hipSuccess) {
+        d.streams.swap(keep);
+        return ec;
+      }
+    } else {
+      mine.done = d.spare.back();
+      d.spare.pop_back();
+    }
+  }
+  keep.push_back(mine);
+  d.streams.swap(keep);
+  return e;
+}
+
+int res_groups(int n, bool many) {
+  const int R = res_rows((n + 255) / 256, many);
+  return (n + R - 1) / R;
+}
+// The split of a batch: fine while all problems then run at a time on a workgroup per CU,
+// else coarse, as many problems at a time as fit, in launches of about equal size.
+struct ResShape {
+  bool many;
+  int G, per;  // workgroups per problem, problems per launch
+};
+ResShape res_shape(int n, int nbatch) {
+  const bool many = nbatch * res_groups(n, false) > 256;
+  const int G = res_groups(n, many), most = res_capacity() / G;
+  const int launches = (nbatch + most - 1) / most;
+  return ResShape{many, G, (nbatch + launches - 1) / launches};
+}
+}  // namespace
+
+// Sizes with more columns than the last-columns kernel takes plus a few (each is worth an
+// exchange then), whose rows fit the registers of 256 workgroups.
+bool tri_resident(int n) { return n > kTriResMin && n <= 256 * 5 && res_capacity() >= 256; }
+int tri_resident_workgroups(int n, int nbatch) {
+  const ResShape r = res_shape(n, nbatch);
+  return r.G * r.per;
+}
+
+template <int U>
+static void res_launch(const TriArgs& a, const TriResArgs& x, const ResShape& r, int nb, int k0, hipStream_t s) {
+  const dim3 grid(r.G, nb);
+  if (r.many) k_tri_res<U, res_rows(U, true)><<<grid, 256, 0, s>>>(a, x, k0);
+  else k_tri_res<U, res_rows(U, false)><<<grid, 256, 0, s>>>(a, x, k0);
+}
+
+hipError_t launch_tridiag_resident(const TriArgs& base, const TriResArgs& xbase, int nbatch, hipStream_t s) {
+  const int n = base.n, U = (n + 255) / 256, k0 = n - kTriTail;
+  if (!tri_resident(n)) return hipErrorInvalidValue;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  ResDevice& d = g_res[dev & 31];
+  const ResShape r = res_shape(n, nbatch);
+  TriResArgs x = xbase;
+  x.wait = kTriResWait;
+  if (g_res_stall.load() > 0 && g_res_stall.fetch_sub(1) > 0) x.wait = 0;
+  k_tri_res_fill<<<512, 256, 0, s>>>(x, (long)n * n, nbatch);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  for (int b = 0; b < nbatch; b += r.per) {
+    const int nb = nbatch - b < r.per ? nbatch - b : r.per;
+    TriArgs a = base;
+    a.Aw += b * base.strideA;
+    a.Vst += b * base.strideA;
+    a.D += (long)b * n;
+    a.E += (long)b * n;
+    a.tau += (long)b * n;
+    a.vbuf[0] += (long)b * n;
+    a.pbuf[0] += (long)b * n;
+    TriResArgs y = x;
+    y.P += b * x.sP;
+    y.C += b * x.sC;
+    std::lock_guard<std::mutex> lk(d.mu);  // launches are made in the order of their admission
+    if ((e = res_admit(d, r.G * nb, s)) != hipSuccess) return e;
+    if (U == 1) res_launch<1>(a, y, r, nb, k0, s);
+    else if (U == 2) res_launch<2>(a, y, r, nb, k0, s);
+    else if (U == 3) res_launch<3>(a, y, r, nb, k0, s);
+    else if (U == 4) res_launch<4>(a, y, r, nb, k0, s);
+    else res_launch<5>(a, y, r, nb, k0, s);
+    e = hipGetLastError();
+    const hipError_t er = hipEventRecord(d.streams.back().done, s);
+    if (e != hipSuccess) return e;
+    if (er != hipSuccess) return er;
+  }
+  return launch_tail(base, nbatch, k0, 0, x.stall, s);
 }
 
 }  // namespace slrx
+
+extern "C" void slrx_fault_stall(int32_t n) { slrx::g_res_stall.store(n < 0 ? 0 : n); }

@@ -251,6 +251,8 @@ struct WeightArgs {
   double* eps_out;          // per-iteration record (may be null)
   int first;                // 1 on the first IRLS iteration
   double eps0_frac, gamma, p;
+  const int* stall;         // the eigensolver's give-up flag (may be null) ..
+  int* stalled;             // .. recorded here
 };
 hipError_t launch_eps(const WeightArgs& a, hipStream_t s);  // the eps update alone
 hipError_t launch_weights(const WeightArgs& a, hipStream_t s, bool eps = true);
@@ -275,6 +277,21 @@ struct TriArgs {
 // workgroup at those loaded at kernel entry); stream: nontemporal loads and
 // stores of the trailing-block rows.  Results depend on neither.
 hipError_t launch_tridiag(const TriArgs& a, int nbatch, hipStream_t s, int cand, bool stream);
+// The same in one launch with the matrix in registers (tri_resident(n)), then the last
+// columns; vbuf[0] and pbuf[0] hold the pending reflector between the two.  P, C: write-once
+// vectors of the exchange, n x n elements per problem each.  stall is set to 1 when a wait
+// was given up: every output of the launch is then finite but not a result.
+struct TriResArgs {
+  double2* P;
+  double2* C;
+  long sP, sC;              // elements between the problems of a batch
+  int* stall;
+  unsigned long long wait;  // longest wait of a thread in ticks of 10 ns (0: give up at once)
+};
+constexpr unsigned long long kTriResWait = 200000000ull;  // 2 s
+bool tri_resident(int n);
+int tri_resident_workgroups(int n, int nbatch);  // of one launch
+hipError_t launch_tridiag_resident(const TriArgs& a, const TriResArgs& x, int nbatch, hipStream_t s);
 int tri_budget_candidates(int nbatch);
 int tri_budget(int nbatch, int cand);
 int tri_max_n();

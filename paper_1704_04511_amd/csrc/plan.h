@@ -13,9 +13,11 @@ namespace slrx {
 constexpr int kMaxS = 3000;    // largest filter size s = N1 N2 M (own eigensolver chain)
 constexpr int kMaxCg = 10000;  // largest CG iteration count
 // info: eigensolver status per outer iteration, the single-step slot
-// (SLRX_MAX_IRLS), and a flag raised by the Gram pass on a non-finite entry
+// (SLRX_MAX_IRLS), a flag raised by the Gram pass on a non-finite entry, and one
+// raised when a resident tridiagonalisation gave up waiting
 constexpr int kInfoNonfinite = SLRX_MAX_IRLS + 1;
-constexpr int kInfoEntries = SLRX_MAX_IRLS + 2;
+constexpr int kInfoStalled = SLRX_MAX_IRLS + 2;
+constexpr int kInfoEntries = SLRX_MAX_IRLS + 3;
 
 enum Buf {
   B_B, B_BM, B_X0, B_IMG, B_X, B_R, B_P, B_Q, B_T, B_S, B_ET, B_ESTAGE,
@@ -124,6 +126,8 @@ struct slrx_plan {
 
   bool has_b = false, has_S = false, has_init = false;
   bool prepared = false, running = false, ran = false;
+  bool tri_columns = false;  // tridiagonalise by column launches (after a resident launch gave up)
+  bool inputs_kept = false;  // nothing was set since the run was started
   int run_irls = 0;
   bool run_timing = false;
 
@@ -167,6 +171,8 @@ struct EighBufs {
   const std::vector<int>* level_start = nullptr;
   const std::vector<int>* node_sizes = nullptr;
   long sA = 0, sZ = 0, sQ = 0, s_wsi = 0, s_wsd = 0, s_bts = 0;
+  int* stall = nullptr;        // give-up flag of the resident tridiagonalisation
+  bool tri_columns = false;    // column launches instead of it
 };
 EighBufs plan_eigh_bufs(slrx_plan* pl);
 hipError_t eigh_tri(const EighBufs& e, hipStream_t s);     // Gram in A (row-major) -> D, E, tau, V
@@ -174,7 +180,7 @@ hipError_t eigh_tdeig(const EighBufs& e, hipStream_t s);   // D, E -> eigenvalue
 hipError_t eigh_backtr(const EighBufs& e, hipStream_t s);  // Z <- Q Z (A used as workspace)
 slrx_status dc_prepare(slrx_plan* pl);
 slrx_status step_weights(slrx_plan* pl, int it, bool first, double gamma, const double2* U = nullptr,
-                         const double* lamv = nullptr, bool want_H = false);
+                         const double* lamv = nullptr, bool want_H = false, const int* stall = nullptr);
 // Weight update of the pixel-wise prior (SLRX_FLAG_HLR_VOXEL), in place of
 // step_gram, step_eigh and step_weights.
 slrx_status step_voxel(slrx_plan* pl, int it, bool first, double gamma);

@@ -158,6 +158,8 @@ EighBufs slrx::plan_eigh_bufs(slrx_plan* pl) {
   e.tree = pl->dc_tree;
   e.level_start = &pl->dc_level_start;
   e.node_sizes = &pl->dc_node_sizes;
+  e.stall = pl->flag + 8;
+  e.tri_columns = pl->tri_columns;
   return e;
 }
 
@@ -174,6 +176,23 @@ hipError_t slrx::eigh_tri(const EighBufs& e, hipStream_t st) {
   ta.vbuf[1] = e.triv[1];
   ta.pbuf[0] = e.trip[0];
   ta.pbuf[1] = e.trip[1];
+  // one launch with the matrix in registers where it fits (the eigenvector buffers hold
+  // its exchange); not while the stream is being captured, where it could not be ordered
+  // against the resident launches of other streams
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (!e.tri_columns && tri_resident(e.n)) {
+    const hipError_t ec = hipStreamIsCapturing(st, &cap);
+    if (ec != hipSuccess) return ec;
+    if (cap == hipStreamCaptureStatusNone) {
+      TriResArgs x{};
+      x.P = e.Z;
+      x.sP = e.sZ;
+      x.C = (double2*)e.Q;  // Q and Qs
+      x.sC = e.sQ / 2;
+      x.stall = e.stall;
+      return launch_tridiag_resident(ta, x, e.nb, st);
+    }
+  }
   // workgroups per launch: tuned per (n, problems) on the first decompositions;
   // then the row access policy for the chosen budget
   TuneTicket tk, tk_access;
@@ -258,7 +277,7 @@ slrx_status slrx::step_eigh(slrx_plan* pl, int it) {
 // (spec_supported), else from H itself (filter product on MFMA, then its
 // diagonal sums). want_H also forms H (in Hre / Him) on the spectral path.
 slrx_status slrx::step_weights(slrx_plan* pl, int it, bool first, double gamma, const double2* U,
-                               const double* lamv, bool want_H) {
+                               const double* lamv, bool want_H, const int* stall) {
   const slrx_dims& d = pl->d;
   const int s = d.N1 * d.N2 * d.M;
   WeightArgs wa{};
@@ -273,6 +292,8 @@ slrx_status slrx::step_weights(slrx_plan* pl, int it, bool first, double gamma, 
   wa.eps0_frac = pl->prm.eps0_frac;
   wa.gamma = gamma;
   wa.p = pl->prm.p;
+  wa.stall = stall ? stall : pl->flag + 8;
+  wa.stalled = pl->info + kInfoStalled;
   const int ng = spec_supported(d.N1, d.N2, d.M) ? spec_groups(d.N1, d.N2, d.M, (size_t)s * s) : 0;
   {
     KTimer kt(pl, SLRX_K_FILTER);
@@ -417,6 +438,8 @@ slrx_status slrx::step_direct_weights(slrx_plan* pl, int it, bool first, double 
   wa.eps0_frac = pl->prm.eps0_frac;
   wa.gamma = gamma;
   wa.p = pl->prm.p;
+  wa.stall = pl->flag + 8;
+  wa.stalled = pl->info + kInfoStalled;
   HIPCHK(launch_weights(wa, pl->stream));
   HIPCHK(launch_filter_product(s, pl->VT, pl->Hre, pl->Him, pl->stream));
   HIPCHK(launch_hf((long)s * s, pl->Hre, pl->Him, pl->Hf, pl->stream));

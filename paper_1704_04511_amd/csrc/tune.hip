@@ -194,6 +194,7 @@ int tune_choice(int kind, int a, int b, int c) {
 
 extern "C" int32_t slrx_tri_workgroup_budget(int32_t n, int32_t nbatch) {
   if (n < 1 || nbatch < 1) return 0;
+  if (slrx::tri_resident(n)) return slrx::tri_resident_workgroups(n, nbatch);
   const int c = slrx::tune_choice(slrx::TUNE_TRI, n, nbatch, 0);
   return c < 0 ? 0 : slrx::tri_budget(nbatch, c);
 }
