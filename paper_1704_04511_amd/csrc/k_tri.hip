@@ -625,7 +625,7 @@ __global__ __launch_bounds__(256) void k_tri_res_fill(TriResArgs x, long n2, int
 // us).  Batches take as many rows as fit 256 registers per thread, so that more problems run
 // at a time.
 __host__ __device__ constexpr int res_rows(int U, bool many) {
-  return many ? (U == 1 ? 8 : U == 2 ? 12 : U == 3 ? 8 : U == 4 ? 6 : 5) : (U == 1 ? 2 : U == 2 ? 3 : U);
+  return many ? (U == 1 ? 12 : U == 2 ? 14 : U == 3 ? 10 : U == 4 ? 7 : 5) : (U == 1 ? 2 : U == 2 ? 3 : U);
 }
 template <int U, int R>
 struct ResState {
@@ -675,8 +675,11 @@ SLRX_DEV bool res_columns(ResState<U, R>& st, ResLds<U, R>& q, const TriArgs& a,
       // costs the whole vector once more, from every workgroup, and delays the stores it
       // waits for: n = 1125 took 4780 us without a delay and 3440 us with it.
       // Due: about 450 cycles after the own entries, and the time that the vectors of all
-      // workgroups take.
-      for (int i = 7 + ((n - k) * (int)(gridDim.x * gridDim.y) >> 15); i > 0; --i) __builtin_amdgcn_s_sleep(1);
+      // workgroups take; where two workgroups share a CU the others' rows come first (15
+      // problems of n = 405: 2060 us with 7 units of 64 cycles, 1660 with 24, 1510 with 32,
+      // 1570 with 50; 6 of n = 605: 3640, 2590, 2260, 2410; 32 of n = 140: 195, 173, 179, 190).
+      const int wgs = (int)(gridDim.x * gridDim.y);
+      for (int i = (wgs > 256 ? 28 : 7) + ((n - k) * wgs >> 15); i > 0; --i) __builtin_amdgcn_s_sleep(1);
       unsigned long long t0 = 0;
       for (int spin = 0;; ++spin) {
         miss = false;
@@ -1005,7 +1008,8 @@ hipError_t res_admit(ResDevice& d, int wgs, hipStream_t s) {
   ResStream mine{s, nullptr, wgs};
   std::vector<ResStream> keep;
   for (const ResStream& t : d.streams) {
-    const bool ran = hipEventQuery(t.done) == hipSuccess;
+    // an event of a stream that is gone gives an error: its work has run
+    const bool ran = hipEventQuery(t.done) != hipErrorNotReady;
     (void)hipGetLastError();
     if (t.s == s) {
       mine.done = t.done;
