@@ -855,6 +855,7 @@ extern "C" slrx_status slrx_run_batch(slrx_plan* const* plans, int32_t n, void* 
   for (int step = 0; step < maxit && st == SLRX_OK; ++step) st = engine_step(v, *g_batch_eig);
   for (size_t i = 0; i < v.size() && st == SLRX_OK; ++i) st = engine_end(v[i]);
   if (st != SLRX_OK) {  // no result: every begun plan drains its stream and is idle again
+    engine_drain(*g_batch_eig);
     for (size_t i = 0; i < begun; ++i) {
       (void)hipStreamSynchronize(v[i]->stream);
       v[i]->running = false;

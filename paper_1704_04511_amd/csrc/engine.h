@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <map>
+#include <tuple>
 #include <vector>
 
 #include "../../include/slrx.h"
@@ -21,18 +22,29 @@ struct EigGroup {
   ~EigGroup();
 };
 
-// Table of a grouped CG launch (kernels.h CgSlice): the device copy, a pinned
-// staging copy, and the host copy it was made from (rewritten only when the
-// problems of the group change).
-struct CgTable {
-  std::vector<CgSlice> host;
-  CgSlice* dev = nullptr;
-  CgSlice* pinned = nullptr;
+// Table of a grouped launch (kernels.h CgSlice, WeightSlice): the device copy, a pinned
+// staging copy, and the host copy it was made from (rewritten only when the problems
+// of the group change).
+template <class T>
+struct DevTable {
+  std::vector<T> host;
+  T* dev = nullptr;
+  T* pinned = nullptr;
   size_t cap = 0;                // entries of dev and pinned
   hipEvent_t copied = nullptr;   // the last upload from pinned has run
   bool pending = false;
-  ~CgTable();
+  DevTable() = default;
+  DevTable(const DevTable&) = delete;
+  DevTable& operator=(const DevTable&) = delete;
+  ~DevTable() {
+    if (dev) (void)hipFree(dev);
+    if (pinned) (void)hipHostFree(pinned);
+    if (copied) (void)hipEventDestroy(copied);
+  }
+  // The table on the device, in order on stream s (whose launches alone read it).
+  slrx_status upload(const std::vector<T>& h, hipStream_t s);
 };
+typedef std::tuple<int, int, int, int> WeightKey;  // N1, N2, M, part of the group
 
 // Shared state of the batched eigen-decompositions and the grouped CG (own
 // streams and events).
@@ -40,11 +52,13 @@ struct BatchEig {
   hipStream_t stream = nullptr;
   hipEvent_t ev = nullptr;       // eigenpairs ready
   hipEvent_t ev_free = nullptr;  // every reader of the group buffers has run
+  hipEvent_t ev_w = nullptr;     // the grouped weight updates so far have run
   bool have_free = false;
   std::map<int, EigGroup> groups;
   hipStream_t cg_stream = nullptr;  // grouped CG passes
   hipEvent_t ev_cg = nullptr;       // a group's CG has run
-  std::map<std::pair<int, int>, CgTable> cg_tables;  // by (M, n_cg)
+  std::map<std::pair<int, int>, DevTable<CgSlice>> cg_tables;  // by (M, n_cg)
+  std::map<WeightKey, DevTable<WeightSlice>> weight_tables;
   size_t allocated() const;  // device bytes held by the groups and tables
   ~BatchEig();
 };
@@ -61,6 +75,8 @@ slrx_status engine_begin(slrx_plan* pl);
 // Enqueue one outer iteration for every given problem that has iterations
 // left (no host synchronisation).
 slrx_status engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be);
+// Wait for everything the engine has enqueued (after a failed step).
+void engine_drain(BatchEig& be);
 // Record the completion event of a problem whose iterations are done.
 slrx_status engine_end(slrx_plan* pl);
 

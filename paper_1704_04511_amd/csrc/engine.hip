@@ -6,8 +6,10 @@
 // back-transformation), each kernel covering all of them at once; the kernels
 // treat every problem independently with the same arithmetic as for a single
 // problem, so a result is bit-identical alone, in a batch and in the server.
-// The Gram matrix, weights, masks and CG of each problem run on the problem's
-// own stream, ordered against the shared eigen-decomposition by events.
+// Within such a group the problems of one filter also share the launches of the
+// images, Gram matrices, weights and masks (on the engine's stream); the others'
+// run on the problem's own stream, ordered against the shared
+// eigen-decomposition by events, as does the CG unless it is grouped too.
 // Problems may join between steps (each keeps its own iteration index and
 // epsilon schedule), which is what the server does.  Problems that use the
 // library eigensolver take the single-problem path.
@@ -17,6 +19,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <vector>
@@ -48,10 +51,41 @@ slrx::EigGroup::~EigGroup() {
   if (tree) (void)hipFree(tree);
 }
 
-slrx::CgTable::~CgTable() {
-  if (dev) (void)hipFree(dev);
-  if (pinned) (void)hipHostFree(pinned);
-  if (copied) (void)hipEventDestroy(copied);
+template <class T>
+slrx_status slrx::DevTable<T>::upload(const std::vector<T>& h, hipStream_t s) {
+  if (host.size() == h.size() && std::memcmp(host.data(), h.data(), h.size() * sizeof(T)) == 0) return SLRX_OK;
+  // the new table follows, on the stream, the launches that read the old one
+  if (h.size() > cap) {
+    HIPCHK(hipStreamSynchronize(s));
+    if (dev) HIPCHK(hipFree(dev));
+    if (pinned) HIPCHK(hipHostFree(pinned));
+    dev = nullptr;
+    pinned = nullptr;
+    cap = 0;
+    pending = false;
+    host.clear();
+    const size_t n = std::max<size_t>(h.size(), 32);
+    if (dev_malloc((void**)&dev, n * sizeof(T)) != hipSuccess) {
+      (void)hipGetLastError();
+      dev = nullptr;
+      return fail(SLRX_ENOMEM, "table of a grouped launch (%zu entries)", n);
+    }
+    HIPCHK(hipHostMalloc((void**)&pinned, n * sizeof(T), hipHostMallocDefault));
+    if (!copied) HIPCHK(hipEventCreateWithFlags(&copied, hipEventDisableTiming));
+    cap = n;
+  }
+  if (pending) HIPCHK(hipEventSynchronize(copied));  // the staging copy is free again
+  std::memcpy((void*)pinned, (const void*)h.data(), h.size() * sizeof(T));
+  HIPCHK(hipMemcpyAsync(dev, pinned, h.size() * sizeof(T), hipMemcpyHostToDevice, s));
+  HIPCHK(hipEventRecord(copied, s));
+  pending = true;
+  host = h;
+  return SLRX_OK;
+}
+
+void slrx::engine_drain(BatchEig& be) {
+  if (be.stream) (void)hipStreamSynchronize(be.stream);
+  if (be.cg_stream) (void)hipStreamSynchronize(be.cg_stream);
 }
 
 slrx::BatchEig::~BatchEig() {
@@ -59,7 +93,9 @@ slrx::BatchEig::~BatchEig() {
   if (cg_stream) (void)hipStreamSynchronize(cg_stream);
   groups.clear();
   cg_tables.clear();
+  weight_tables.clear();
   if (ev) (void)hipEventDestroy(ev);
+  if (ev_w) (void)hipEventDestroy(ev_w);
   if (ev_free) (void)hipEventDestroy(ev_free);
   if (ev_cg) (void)hipEventDestroy(ev_cg);
   if (stream) (void)hipStreamDestroy(stream);
@@ -97,6 +133,7 @@ size_t slrx::BatchEig::allocated() const {
     if (kv.second.tree) b += tree_bytes(kv.first);
   }
   for (const auto& kv : cg_tables) b += kv.second.cap * sizeof(CgSlice);
+  for (const auto& kv : weight_tables) b += kv.second.cap * sizeof(WeightSlice);
   return b;
 }
 
@@ -131,6 +168,7 @@ static slrx_status group_reserve(BatchEig& be, int n, int nb, EigGroup*& out) {
     HIPCHK(hipStreamCreateWithFlags(&be.stream, hipStreamNonBlocking));
     HIPCHK(hipEventCreateWithFlags(&be.ev, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&be.ev_free, hipEventDisableTiming));
+    HIPCHK(hipEventCreateWithFlags(&be.ev_w, hipEventDisableTiming));
   }
   EigGroup& G = be.groups[n];
   if (G.n != n) {  // first use of this size: the divide-and-conquer tree
@@ -211,6 +249,7 @@ slrx_status slrx::engine_begin(slrx_plan* pl) {
   HIPCHK(hipMemsetAsync(pl->info, 0, kInfoEntries * sizeof(rocblas_int), pl->stream));
   HIPCHK(hipEventRecord(pl->ev_run[0], pl->stream));
   pl->it_next = 0;
+  pl->on_cg = nullptr;
   pl->running = true;
   pl->ran = false;
   pl->run_irls = pl->prm.n_irls;
@@ -255,10 +294,12 @@ static slrx_status step_single(slrx_plan* pl, std::vector<slrx_plan*>* deferred 
   }
   if (deferred && cg_groupable(pl)) {  // deferred: the step runs its CG in grouped launches
     HIPCHK(hipEventRecord(pl->ev_step, pl->stream));
+    pl->ev_weights = true;
     deferred->push_back(pl);
     return SLRX_OK;
   }
   STCHK(run_cg(pl, pl->prm.n_cg, it, false));
+  pl->on_cg = nullptr;
   pl->it_next = it + 1;
   return SLRX_OK;
 }
@@ -278,6 +319,7 @@ static CgSlice cg_slice_of(const slrx_plan* pl) {
   c.twP = pl->twPf;
   c.partA = pl->partA; c.partB = pl->partB; c.rr_hist = pl->rr_hist;
   c.flag = pl->flag;
+  c.rr_out = pl->stats + 2 * SLRX_MAX_IRLS;
   cg_slice_grids(c);
   return c;
 }
@@ -290,7 +332,6 @@ static slrx_status run_cg_group(BatchEig& be, const std::vector<slrx_plan*>& g, 
     HIPCHK(hipStreamCreateWithFlags(&be.cg_stream, hipStreamNonBlocking));
     HIPCHK(hipEventCreateWithFlags(&be.ev_cg, hipEventDisableTiming));
   }
-  CgTable& tb = be.cg_tables[std::make_pair(M, n_cg)];
   std::vector<CgSlice> host(g.size());
   int rows = 0, cols = 0, upd = 0;
   size_t pen_lds = 0;
@@ -306,35 +347,14 @@ static slrx_status run_cg_group(BatchEig& be, const std::vector<slrx_plan*>& g, 
     upd += up8(c.upd_gx);
     pen_lds = std::max(pen_lds, group_pen_lds(c.P, c.Q, c.T));
   }
-  for (slrx_plan* pl : g) HIPCHK(hipStreamWaitEvent(be.cg_stream, pl->ev_step, 0));
-  const bool same = tb.host.size() == host.size() &&
-                    std::memcmp(tb.host.data(), host.data(), host.size() * sizeof(CgSlice)) == 0;
-  if (!same) {  // upload the new table (stream-ordered after the launches that read the old one)
-    if (host.size() > tb.cap) {
-      HIPCHK(hipStreamSynchronize(be.cg_stream));
-      if (tb.dev) HIPCHK(hipFree(tb.dev));
-      if (tb.pinned) HIPCHK(hipHostFree(tb.pinned));
-      tb.dev = nullptr;
-      tb.pinned = nullptr;
-      tb.cap = 0;
-      tb.pending = false;
-      const size_t cap = std::max<size_t>(host.size(), 32);
-      if (dev_malloc((void**)&tb.dev, cap * sizeof(CgSlice)) != hipSuccess) {
-        (void)hipGetLastError();
-        tb.dev = nullptr;
-        return fail(SLRX_ENOMEM, "grouped CG table (%zu entries)", cap);
-      }
-      HIPCHK(hipHostMalloc((void**)&tb.pinned, cap * sizeof(CgSlice), hipHostMallocDefault));
-      if (!tb.copied) HIPCHK(hipEventCreateWithFlags(&tb.copied, hipEventDisableTiming));
-      tb.cap = cap;
-    }
-    if (tb.pending) HIPCHK(hipEventSynchronize(tb.copied));  // the staging copy is free again
-    std::memcpy(tb.pinned, host.data(), host.size() * sizeof(CgSlice));
-    HIPCHK(hipMemcpyAsync(tb.dev, tb.pinned, host.size() * sizeof(CgSlice), hipMemcpyHostToDevice, be.cg_stream));
-    HIPCHK(hipEventRecord(tb.copied, be.cg_stream));
-    tb.pending = true;
-    tb.host = host;
+  bool weights = false;  // some plan's weights were updated in a grouped launch
+  for (slrx_plan* pl : g) {
+    if (pl->ev_weights) HIPCHK(hipStreamWaitEvent(be.cg_stream, pl->ev_step, 0));
+    else weights = true;
   }
+  if (weights) HIPCHK(hipStreamWaitEvent(be.cg_stream, be.ev_w, 0));
+  DevTable<CgSlice>& tb = be.cg_tables[std::make_pair(M, n_cg)];
+  STCHK(tb.upload(host, be.cg_stream));
   CgGroup G{};
   G.tab = tb.dev;
   G.ns = (int)host.size();
@@ -354,15 +374,72 @@ static slrx_status run_cg_group(BatchEig& be, const std::vector<slrx_plan*>& g, 
     HIPCHK(launch_group_fin(G, 0, s));
     HIPCHK(launch_group_update(G, k, s));
   }
-  HIPCHK(hipEventRecord(be.ev_cg, s));
-  for (size_t i = 0; i < g.size(); ++i) {
-    slrx_plan* pl = g[i];
-    const int it = pl->it_next;
-    HIPCHK(hipStreamWaitEvent(pl->stream, be.ev_cg, 0));
-    HIPCHK(launch_store_sum(n_cg == 0 ? pl->partA : pl->partB, n_cg == 0 ? host[i].nfin : host[i].nupd,
-                            pl->stats + 2 * SLRX_MAX_IRLS + it, pl->stream));
-    pl->it_next = it + 1;
+  for (int i0 = 0; i0 < G.ns; i0 += kGroupIts) {
+    const int n = std::min(kGroupIts, G.ns - i0);
+    GroupIts it{};
+    for (int i = 0; i < n; ++i) it.it[i] = (short)g[i0 + i]->it_next;
+    HIPCHK(launch_group_store(G, i0, n, n_cg == 0, it, s));
   }
+  HIPCHK(hipEventRecord(be.ev_cg, s));
+  for (slrx_plan* pl : g) {
+    HIPCHK(hipStreamWaitEvent(pl->stream, be.ev_cg, 0));
+    pl->on_cg = &be;
+    ++pl->it_next;
+  }
+  return SLRX_OK;
+}
+
+// A part of an eigen-decomposition group whose weight updates run as grouped launches on
+// the engine's stream: problems of one filter (at least two, at most kGroupIts).
+struct WeightPart {
+  std::vector<int> at;  // positions in the group
+  WeightGroup G{};
+};
+
+// The Gram matrices of the part's problems into the group's buffers.
+static slrx_status weight_part_gram(BatchEig& be, const EighBufs& e, const std::vector<slrx_plan*>& g, int part,
+                                    WeightPart& wp) {
+  bool cg = false;
+  std::vector<WeightSlice> host(wp.at.size());
+  WeightGroup& G = wp.G;
+  const slrx_dims& d0 = g[wp.at[0]]->d;
+  G.ns = (int)wp.at.size();
+  G.N1 = d0.N1; G.N2 = d0.N2; G.M = d0.M;
+  for (size_t k = 0; k < wp.at.size(); ++k) {
+    const int i = wp.at[k];
+    slrx_plan* pl = g[i];
+    // after the problem's last work: the grouped CG, or what its own stream holds
+    if (pl->on_cg == &be) {
+      cg = true;
+    } else {
+      HIPCHK(hipEventRecord(pl->ev_step, pl->stream));
+      HIPCHK(hipStreamWaitEvent(be.stream, pl->ev_step, 0));
+    }
+    const slrx_dims& d = pl->d;
+    WeightSlice& c = host[k];
+    std::memset((void*)&c, 0, sizeof c);
+    c.x = pl->x;
+    c.t = pl->t;
+    c.img = pl->img;
+    c.twP = pl->twPf;
+    c.twQ = pl->twQf;
+    c.img_scale = (float)(1.0 / std::sqrt((double)d.P * d.Q));
+    c.gram = gram_args(pl, e.A + (size_t)i * e.sA, true);
+    weight_args(pl, 0, false, pl->prm.gamma, e.Z + (size_t)i * e.sZ, e.D + (size_t)i * e.n, e.stall, c.w, c.spec,
+                c.mask);
+    G.ngroups = c.spec.ngroups;
+    G.maxP = std::max(G.maxP, d.P);
+    G.maxQ = std::max(G.maxQ, d.Q);
+    G.maxPQ = std::max(G.maxPQ, (long)d.P * d.Q);
+    G.row_blocks = std::max(G.row_blocks, image_row_blocks(d.P, d.T));
+    G.col_blocks = std::max(G.col_blocks, image_col_blocks(d.Q, d.T));
+  }
+  if (cg) HIPCHK(hipStreamWaitEvent(be.stream, be.ev_cg, 0));
+  DevTable<WeightSlice>& tb = be.weight_tables[WeightKey(d0.N1, d0.N2, d0.M, part)];
+  STCHK(tb.upload(host, be.stream));
+  G.tab = tb.dev;
+  HIPCHK(launch_group_images(G, be.stream));
+  HIPCHK(launch_group_gram(G, be.stream));
   return SLRX_OK;
 }
 
@@ -429,8 +506,29 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
     STCHK(group_reserve(be, n, nb, G));
     EighBufs e = G->bufs;
     e.nb = nb;
-    // Gram matrices (row-major) into the group buffer once the previous step's readers are done
+    // problems of one filter share launches of the weight update's kernels too (two or
+    // more: one launch for all of them is never slower than their own, run at once)
+    std::map<std::tuple<int, int, int>, std::vector<int>> filters;
+    std::vector<int> alone;
     for (int i = 0; i < nb; ++i) {
+      const slrx_dims& d = g[i]->d;
+      if (spec_supported(d.N1, d.N2, d.M) && spec_groups(d.N1, d.N2, d.M, (size_t)n * n) > 0)
+        filters[std::make_tuple(d.N1, d.N2, d.M)].push_back(i);
+      else
+        alone.push_back(i);
+    }
+    std::vector<WeightPart> parts;
+    for (auto& f : filters) {
+      const size_t m = f.second.size();
+      if (m < 2) alone.push_back(f.second[0]);
+      for (size_t k = 0; m >= 2 && k < m; k += kGroupIts) {
+        parts.emplace_back();
+        parts.back().at.assign(f.second.begin() + k, f.second.begin() + std::min(m, k + kGroupIts));
+      }
+    }
+    // Gram matrices (row-major) into the group buffer once the previous step's readers are done
+    for (size_t k = 0; k < parts.size(); ++k) STCHK(weight_part_gram(be, e, g, (int)k, parts[k]));
+    for (int i : alone) {
       slrx_plan* pl = g[i];
       if (be.have_free) HIPCHK(hipStreamWaitEvent(pl->stream, be.ev_free, 0));
       STCHK(step_gram(pl, false, e.A + (size_t)i * e.sA));
@@ -441,7 +539,25 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
     HIPCHK(eigh_tdeig(e, be.stream));
     HIPCHK(eigh_backtr(e, be.stream));
     HIPCHK(hipEventRecord(be.ev, be.stream));
-    for (int i = 0; i < nb; ++i) {
+    for (const WeightPart& wp : parts) {
+      GroupIts its{};
+      for (size_t k = 0; k < wp.at.size(); ++k) its.it[k] = (short)g[wp.at[k]]->it_next;
+      HIPCHK(launch_group_weights(wp.G, its, be.stream));
+      HIPCHK(hipEventRecord(be.ev_w, be.stream));
+      for (int i : wp.at) {
+        slrx_plan* pl = g[i];
+        pl->ev_weights = false;
+        if (grouped && cg_groupable(pl)) {
+          deferred.push_back(pl);
+        } else {
+          HIPCHK(hipStreamWaitEvent(pl->stream, be.ev_w, 0));
+          STCHK(run_cg(pl, pl->prm.n_cg, pl->it_next, false));
+          pl->on_cg = nullptr;
+          ++pl->it_next;
+        }
+      }
+    }
+    for (int i : alone) {
       slrx_plan* pl = g[i];
       const int it = pl->it_next;
       HIPCHK(hipStreamWaitEvent(pl->stream, be.ev, 0));
@@ -449,10 +565,12 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
                          e.stall));
       HIPCHK(hipEventRecord(pl->ev_step, pl->stream));
       HIPCHK(hipStreamWaitEvent(be.stream, pl->ev_step, 0));
+      pl->ev_weights = true;
       if (grouped && cg_groupable(pl)) {
         deferred.push_back(pl);
       } else {
         STCHK(run_cg(pl, pl->prm.n_cg, it, false));
+        pl->on_cg = nullptr;
         pl->it_next = it + 1;
       }
     }

@@ -25,15 +25,16 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------ Gram pass 1
 // Block per image row r1: lagged products for every tap pair (FP64), then the
 // pruned DFT along r2 at lags delta2 = -(N2-1)..(N2-1).
+// (Every kernel of the weight update is a body that takes its block index, run by a
+// launch of one problem or, in batches, of a table of problems.)
 template <int M>
-__global__ __launch_bounds__(256) void k_gram_rows(GramArgs a) {
+SLRX_DEV void gram_rows_body(const GramArgs& a, int bx, double2* sm) {  // sm: cw[W][Q], tw[Q]
   constexpr int W = M * (M + 1) / 2;
-  extern __shared__ double2 sm[];  // cw[W][Q], tw[Q]
   const int P = a.P, Q = a.Q, T = a.T, N2 = a.N2;
   const int L2 = 2 * N2 - 1;
   double2* cw = sm;
   double2* tw = sm + (size_t)W * Q;
-  const int r1 = blockIdx.x;
+  const int r1 = bx;
   const long fs = (long)P * Q;
   for (int i = threadIdx.x; i < Q; i += 256) tw[i] = a.twQ[i];
   for (int r2 = threadIdx.x; r2 < Q; r2 += 256) {
@@ -82,11 +83,17 @@ __global__ __launch_bounds__(256) void k_gram_rows(GramArgs a) {
   }
 }
 
+template <int M>
+__global__ __launch_bounds__(256) void k_gram_rows(GramArgs a) {
+  extern __shared__ double2 sm[];
+  gram_rows_body<M>(a, blockIdx.x, sm);
+}
+
 // Pass 2: pruned DFT along r1 at lags delta1 = -(N1-1)..(N1-1).
-__global__ __launch_bounds__(256) void k_gram_cols(GramArgs a, int W) {
+SLRX_DEV void gram_cols_body(const GramArgs& a, int W, int bx) {
   // four lanes per output, each over every fourth r1, combined in a fixed order
   const int L1 = 2 * a.N1 - 1, L2 = 2 * a.N2 - 1;
-  const int gt = blockIdx.x * 256 + threadIdx.x;
+  const int gt = bx * 256 + threadIdx.x;
   const int o = gt >> 2, q = gt & 3;
   const bool valid = o < W * L1 * L2;
   const int oo = valid ? o : 0;
@@ -114,11 +121,13 @@ __global__ __launch_bounds__(256) void k_gram_cols(GramArgs a, int W) {
   if (valid && q == 0) a.g[o] = make_double2(sx, sy);
 }
 
+__global__ __launch_bounds__(256) void k_gram_cols(GramArgs a, int W) { gram_cols_body(a, W, blockIdx.x); }
+
 // Pass 3: window extraction into R (column-major, full Hermitian matrix).
-__global__ __launch_bounds__(256) void k_gram_assemble(GramArgs a) {
+SLRX_DEV void gram_assemble_body(const GramArgs& a, int bx) {
   const int N1 = a.N1, N2 = a.N2, M = a.M;
   const int NN = N1 * N2, s = NN * M;
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  const long idx = (long)bx * 256 + threadIdx.x;
   if (idx >= (long)s * s) return;
   // element (i, j): column-major R[i + j s], or row-major R[i s + j]
   const int i = a.rowmajor ? (int)(idx / s) : (int)(idx % s);
@@ -143,6 +152,8 @@ __global__ __launch_bounds__(256) void k_gram_assemble(GramArgs a) {
   }
   a.R[idx] = v;
 }
+
+__global__ __launch_bounds__(256) void k_gram_assemble(GramArgs a) { gram_assemble_body(a, blockIdx.x); }
 
 template <int M>
 static hipError_t gram_m(const GramArgs& a, hipStream_t s) {
@@ -180,14 +191,16 @@ hipError_t launch_gram(const GramArgs& a, hipStream_t s) {
 
 // ---------------------------------------------------------------- weights
 // eps^(0) = eps0_frac * lambda_max on the first iteration, else eps <- eps / gamma.
-__global__ void k_eps(WeightArgs a) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+SLRX_DEV void eps_body(const WeightArgs& a) {
   const double lmax = a.lamv[a.s - 1];
   const double e = a.first ? a.eps0_frac * lmax : (*a.eps) / a.gamma;
   *a.eps = e;
   if (a.lam_max_out) *a.lam_max_out = lmax;
   if (a.eps_out) *a.eps_out = e;
   if (a.stall && *a.stall) *a.stalled = 1;
+}
+__global__ void k_eps(WeightArgs a) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) eps_body(a);
 }
 
 // V = U diag(sqrt(alpha)), alpha_k = (max(lambda_k, 0) + eps)^(p/2 - 1), stored K-major.
@@ -357,12 +370,11 @@ constexpr int kSpecPf = kSpecMaxS / 256;  // prefetched eigenvector entries per 
 constexpr int kSpecMaxL1 = 32; // 256 threads = 32 rows f1 x 8 columns f2
 
 template <int M>
-__global__ __launch_bounds__(256) void k_spec_accum(SpecArgs a) {
+SLRX_DEV void spec_accum_body(const SpecArgs& a, int bx, int by, double2* spl) {
   constexpr int W = M * (M + 1) / 2;
-  extern __shared__ double2 spl[];
   const int N1 = a.N1, N2 = a.N2, s = a.s;
   const int L1 = 2 * N1 - 1, L2 = 2 * N2 - 1, F = L1 * L2;
-  const int c0 = blockIdx.y * kSpecF2, nf2 = min(kSpecF2, L2 - c0);
+  const int c0 = by * kSpecF2, nf2 = min(kSpecF2, L2 - c0);
   double2* v = spl;                    // eigenvector k, s entries
   double2* Y = v + s;                  // [M N1][nf2]
   double2* t1 = Y + M * N1 * kSpecF2;  // e^{-2 pi i j / L1}
@@ -383,7 +395,7 @@ __global__ __launch_bounds__(256) void k_spec_accum(SpecArgs a) {
   double2 acc[W];
 #pragma unroll
   for (int w = 0; w < W; ++w) acc[w] = make_double2(0.0, 0.0);
-  const int k0 = blockIdx.x * a.kper, k1 = min(s, k0 + a.kper);
+  const int k0 = bx * a.kper, k1 = min(s, k0 + a.kper);
   const double e = *a.eps, ex = a.p * 0.5 - 1.0;
   // eigenvector k + 1 is loaded into registers while k is transformed
   double2 nxt[kSpecPf];
@@ -462,17 +474,23 @@ __global__ __launch_bounds__(256) void k_spec_accum(SpecArgs a) {
   if (act) {
     const int f = f1 * L2 + c0 + fl;
 #pragma unroll
-    for (int w = 0; w < W; ++w) a.part[((long)blockIdx.x * W + w) * F + f] = acc[w];
+    for (int w = 0; w < W; ++w) a.part[((long)bx * W + w) * F + f] = acc[w];
   }
+}
+
+template <int M>
+__global__ __launch_bounds__(256) void k_spec_accum(SpecArgs a) {
+  extern __shared__ double2 spl[];
+  spec_accum_body<M>(a, blockIdx.x, blockIdx.y, spl);
 }
 
 // Slice q of the groups: C[q][w][f] = sum over groups g = q, q + kSpecSlices, ..
 // of part[g][w][f], in group order (the slices are added in order by the
 // inverse transform).
-__global__ __launch_bounds__(256) void k_spec_reduce(SpecArgs a, int W) {
+SLRX_DEV void spec_reduce_body(const SpecArgs& a, int W, int bx) {
   const int F = (2 * a.N1 - 1) * (2 * a.N2 - 1);
   const long WF = (long)W * F;
-  const long o = (long)blockIdx.x * 256 + threadIdx.x;
+  const long o = (long)bx * 256 + threadIdx.x;
   if (o >= kSpecSlices * WF) return;
   const int q = (int)(o / WF);
   const long wf = o % WF;
@@ -485,12 +503,13 @@ __global__ __launch_bounds__(256) void k_spec_reduce(SpecArgs a, int W) {
   a.C[o] = make_double2(sx, sy);
 }
 
+__global__ __launch_bounds__(256) void k_spec_reduce(SpecArgs a, int W) { spec_reduce_body(a, W, blockIdx.x); }
+
 // wsum[w][j1][j2] = (1 / F) sum_f C[w][f] e^{+2 pi i (Delta1 f1 / L1 + Delta2 f2 / L2)},
 // Delta = j - (N - 1): one workgroup per pair, the two 1-D transforms in turn.
-__global__ __launch_bounds__(1024) void k_spec_inverse(SpecArgs a, double2* wsum, int W) {
-  extern __shared__ double2 spl[];
+SLRX_DEV void spec_inverse_body(const SpecArgs& a, double2* wsum, int W, int bx, double2* spl) {
   const int N1 = a.N1, N2 = a.N2, L1 = 2 * N1 - 1, L2 = 2 * N2 - 1, F = L1 * L2;
-  const int w = blockIdx.x, tid = threadIdx.x;
+  const int w = bx, tid = threadIdx.x;
   double2* Cs = spl;       // C[w][f1][f2]
   double2* Ts = Cs + F;    // [f1][j2]
   double2* t1 = Ts + F;    // e^{+2 pi i j / L1}
@@ -550,6 +569,11 @@ __global__ __launch_bounds__(1024) void k_spec_inverse(SpecArgs a, double2* wsum
   }
 }
 
+__global__ __launch_bounds__(1024) void k_spec_inverse(SpecArgs a, double2* wsum, int W) {
+  extern __shared__ double2 spl[];
+  spec_inverse_body(a, wsum, W, blockIdx.x, spl);
+}
+
 bool spec_supported(int N1, int N2, int M) {
   const int s = N1 * N2 * M, L1 = 2 * N1 - 1, L2 = 2 * N2 - 1;
   if (M > kSpecMaxM || L1 > kSpecMaxL1 || s > kSpecMaxS) return false;
@@ -570,11 +594,13 @@ int spec_groups(int N1, int N2, int M, size_t cap) {
   return (s + kper - 1) / kper;
 }
 
+int spec_per_group(int s, int ngroups) { return (s + ngroups - 1) / ngroups; }
+
 hipError_t launch_spec_masks(const SpecArgs& a0, double2* wsum, hipStream_t st) {
   SpecArgs a = a0;
   const int M = a.M, W = M * (M + 1) / 2;
   const int L1 = 2 * a.N1 - 1, L2 = 2 * a.N2 - 1, F = L1 * L2;
-  a.kper = (a.s + a.ngroups - 1) / a.ngroups;
+  a.kper = spec_per_group(a.s, a.ngroups);
   const dim3 grid(a.ngroups, (L2 + kSpecF2 - 1) / kSpecF2);
   const size_t lds = ((size_t)a.s + (size_t)M * a.N1 * kSpecF2 + L1 + L2) * sizeof(double2);
   switch (M) {
@@ -630,9 +656,9 @@ __global__ __launch_bounds__(256) void k_diagsum(MaskArgs a, int W, int s) {
 }
 
 // s1[w][j1][r2] = sum_{j2} w[w][j1][j2] e^{+2 pi i Delta2 r2 / Q}
-__global__ __launch_bounds__(256) void k_mask_rows(MaskArgs a, int W) {
+SLRX_DEV void mask_rows_body(const MaskArgs& a, int W, int bx) {
   const int L1 = 2 * a.N1 - 1, L2 = 2 * a.N2 - 1, Q = a.Q;
-  const long o = (long)blockIdx.x * 256 + threadIdx.x;
+  const long o = (long)bx * 256 + threadIdx.x;
   if (o >= (long)W * L1 * Q) return;
   const int r2 = (int)(o % Q);
   const long wj = o / Q;  // w * L1 + j1
@@ -650,11 +676,13 @@ __global__ __launch_bounds__(256) void k_mask_rows(MaskArgs a, int W) {
   a.s1[o] = make_double2(sx, sy);
 }
 
+__global__ __launch_bounds__(256) void k_mask_rows(MaskArgs a, int W) { mask_rows_body(a, W, blockIdx.x); }
+
 // E_w(r1, r2) = sum_{j1} s1[w][j1][r2] e^{+2 pi i Delta1 r1 / P}, rounded to FP32 and
 // stored as transposed planes Et[w][r2][r1] (the layout of the column penalty pass).
-__global__ __launch_bounds__(256) void k_mask_cols(MaskArgs a, int W) {
+SLRX_DEV void mask_cols_body(const MaskArgs& a, int W, int bx) {
   const int L1 = 2 * a.N1 - 1, P = a.P, Q = a.Q;
-  const long o = (long)blockIdx.x * 256 + threadIdx.x;
+  const long o = (long)bx * 256 + threadIdx.x;
   if (o >= (long)W * P * Q) return;
   const int r1 = (int)(o % P);
   const int r2 = (int)((o / P) % Q);
@@ -673,6 +701,8 @@ __global__ __launch_bounds__(256) void k_mask_cols(MaskArgs a, int W) {
   a.Et[o] = make_float2((float)sx, (float)sy);
 }
 
+__global__ __launch_bounds__(256) void k_mask_cols(MaskArgs a, int W) { mask_cols_body(a, W, blockIdx.x); }
+
 hipError_t launch_masks(const MaskArgs& a, hipStream_t s) {
   const int W = a.M * (a.M + 1) / 2;
   const int sN = a.N1 * a.N2 * a.M;
@@ -688,6 +718,107 @@ hipError_t launch_masks(const MaskArgs& a, hipStream_t s) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const long n3 = (long)W * a.P * a.Q;
   k_mask_cols<<<(unsigned)((n3 + 255) / 256), 256, 0, s>>>(a, W);
+  return hipGetLastError();
+}
+
+// ------------------------------------------- grouped weight updates (batches)
+// The weight update of several problems with the same filter in one launch per kernel:
+// problem blockIdx.y (z for the accumulation) of the table, its own blocks, and the
+// arithmetic of its own launches.  A batch of small slices is otherwise bound by the
+// launches themselves: 32 slices of 64 x 64 x 8 with 5 x 5 x 3 made 352 of them a step.
+template <int M>
+__global__ __launch_bounds__(256) void k_group_gram_rows(const WeightSlice* tab) {
+  extern __shared__ double2 sm[];
+  const GramArgs a = tab[blockIdx.y].gram;
+  if ((int)blockIdx.x < a.P) gram_rows_body<M>(a, blockIdx.x, sm);
+}
+__global__ __launch_bounds__(256) void k_group_gram_cols(const WeightSlice* tab, int W) {
+  const GramArgs a = tab[blockIdx.y].gram;
+  gram_cols_body(a, W, blockIdx.x);
+}
+__global__ __launch_bounds__(256) void k_group_gram_assemble(const WeightSlice* tab) {
+  const GramArgs a = tab[blockIdx.y].gram;
+  gram_assemble_body(a, blockIdx.x);
+}
+// it.it[i]: outer iteration of problem i
+__global__ void k_group_eps(const WeightSlice* tab, int ns, GroupIts it) {
+  const int i = threadIdx.x;
+  if (i >= ns) return;
+  WeightArgs a = tab[i].w;
+  a.first = it.it[i] == 0 ? 1 : 0;
+  a.lam_max_out += it.it[i];
+  a.eps_out += it.it[i];
+  eps_body(a);
+}
+template <int M>
+__global__ __launch_bounds__(256) void k_group_spec_accum(const WeightSlice* tab) {
+  extern __shared__ double2 spl[];
+  const SpecArgs a = tab[blockIdx.z].spec;
+  spec_accum_body<M>(a, blockIdx.x, blockIdx.y, spl);
+}
+__global__ __launch_bounds__(256) void k_group_spec_reduce(const WeightSlice* tab, int W) {
+  const SpecArgs a = tab[blockIdx.y].spec;
+  spec_reduce_body(a, W, blockIdx.x);
+}
+__global__ __launch_bounds__(1024) void k_group_spec_inverse(const WeightSlice* tab, int W) {
+  extern __shared__ double2 spl[];
+  const SpecArgs a = tab[blockIdx.y].spec;
+  spec_inverse_body(a, tab[blockIdx.y].mask.wsum, W, blockIdx.x, spl);
+}
+__global__ __launch_bounds__(256) void k_group_mask_rows(const WeightSlice* tab, int W) {
+  const MaskArgs a = tab[blockIdx.y].mask;
+  mask_rows_body(a, W, blockIdx.x);
+}
+__global__ __launch_bounds__(256) void k_group_mask_cols(const WeightSlice* tab, int W) {
+  const MaskArgs a = tab[blockIdx.y].mask;
+  mask_cols_body(a, W, blockIdx.x);
+}
+
+template <int M>
+static hipError_t group_gram_m(const WeightGroup& g, hipStream_t s) {
+  constexpr int W = M * (M + 1) / 2;
+  static LdsLimit lim;
+  const hipError_t e = lim.ensure((const void*)k_group_gram_rows<M>, ((size_t)W * 256 + 256) * sizeof(double2));
+  if (e != hipSuccess) return e;
+  k_group_gram_rows<M><<<dim3(g.maxP, g.ns), 256, ((size_t)W * g.maxQ + g.maxQ) * sizeof(double2), s>>>(g.tab);
+  return hipGetLastError();
+}
+
+hipError_t launch_group_gram(const WeightGroup& g, hipStream_t s) {
+  hipError_t e;
+  switch (g.M) {
+    case 1: e = group_gram_m<1>(g, s); break;
+    case 2: e = group_gram_m<2>(g, s); break;
+    case 3: e = group_gram_m<3>(g, s); break;
+    case 4: e = group_gram_m<4>(g, s); break;
+    case 5: e = group_gram_m<5>(g, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  if (e != hipSuccess) return e;
+  const int W = g.M * (g.M + 1) / 2, F = (2 * g.N1 - 1) * (2 * g.N2 - 1);
+  k_group_gram_cols<<<dim3((4 * W * F + 255) / 256, g.ns), 256, 0, s>>>(g.tab, W);
+  const long sN = (long)g.N1 * g.N2 * g.M;
+  k_group_gram_assemble<<<dim3((unsigned)((sN * sN + 255) / 256), g.ns), 256, 0, s>>>(g.tab);
+  return hipGetLastError();
+}
+
+hipError_t launch_group_weights(const WeightGroup& g, const GroupIts& it, hipStream_t s) {
+  const int M = g.M, W = M * (M + 1) / 2, L1 = 2 * g.N1 - 1, L2 = 2 * g.N2 - 1, F = L1 * L2;
+  k_group_eps<<<1, kGroupIts, 0, s>>>(g.tab, g.ns, it);
+  const dim3 grid(g.ngroups, (L2 + kSpecF2 - 1) / kSpecF2, g.ns);
+  const size_t lds = ((size_t)g.N1 * g.N2 * M + (size_t)M * g.N1 * kSpecF2 + L1 + L2) * sizeof(double2);
+  switch (M) {
+    case 1: k_group_spec_accum<1><<<grid, 256, lds, s>>>(g.tab); break;
+    case 2: k_group_spec_accum<2><<<grid, 256, lds, s>>>(g.tab); break;
+    case 3: k_group_spec_accum<3><<<grid, 256, lds, s>>>(g.tab); break;
+    case 4: k_group_spec_accum<4><<<grid, 256, lds, s>>>(g.tab); break;
+    case 5: k_group_spec_accum<5><<<grid, 256, lds, s>>>(g.tab); break;
+    default: return hipErrorInvalidValue;
+  }
+  k_group_spec_reduce<<<dim3((unsigned)(((long)kSpecSlices * W * F + 255) / 256), g.ns), 256, 0, s>>>(g.tab, W);
+  k_group_spec_inverse<<<dim3(W, g.ns), 1024, (2 * (size_t)F + L1 + L2) * sizeof(double2), s>>>(g.tab, W);
+  k_group_mask_rows<<<dim3((unsigned)(((long)W * L1 * g.maxQ + 255) / 256), g.ns), 256, 0, s>>>(g.tab, W);
+  k_group_mask_cols<<<dim3((unsigned)(((long)W * g.maxPQ + 255) / 256), g.ns), 256, 0, s>>>(g.tab, W);
   return hipGetLastError();
 }
 

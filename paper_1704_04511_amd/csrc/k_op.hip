@@ -337,16 +337,16 @@ __global__ __launch_bounds__(kPenNT) void k_cols_pen(PenArgs a) {
 }
 
 // Plain column DFT of up to 16 columns of one frame: transposed in, row-major out.
+constexpr int kPlainCols = 16;
+__host__ __device__ inline int plain_cols(int Q) { return Q < kPlainCols ? Q : kPlainCols; }
 template <int N, int SIGN>
-__global__ __launch_bounds__(kNT) void k_cols_plain(ColArgs a) {
-  constexpr int CB = 16;
+SLRX_DEV void cols_plain_body(const ColArgs& a, const Blk& b, float2* lds, float2* twt) {
+  constexpr int CB = kPlainCols;
   constexpr int BS = fft_stride(N);
-  __shared__ float2 lds[CB * BS];
-  __shared__ float2 twt[fft_tw_size<N>()];
   const int P = a.P, Q = a.Q;
-  const int cb = Q < CB ? Q : CB;
-  const int t = blockIdx.y;
-  const int c0 = blockIdx.x * cb;
+  const int cb = plain_cols(Q);
+  const int t = b.by;
+  const int c0 = b.bx * cb;
   const long fo = (long)t * P * Q;
   fft_twiddles<N, kNT>(twt, a.tw);
   for (int e = threadIdx.x; e < cb * N; e += kNT)  // [cc][r]
@@ -359,6 +359,13 @@ __global__ __launch_bounds__(kNT) void k_cols_plain(ColArgs a) {
     const int cc = e % cb, r = e / cb;
     a.dst[fo + (long)r * Q + c0 + cc] = cscale(lds[cc * BS + fft_pidx(r)], sc);
   }
+}
+
+template <int N, int SIGN>
+__global__ __launch_bounds__(kNT) void k_cols_plain(ColArgs a) {
+  __shared__ float2 lds[kPlainCols * fft_stride(N)];
+  __shared__ float2 twt[fft_tw_size<N>()];
+  cols_plain_body<N, SIGN>(a, launch_blk(), lds, twt);
 }
 
 // ----------------------------------------------- pass 3: rows + combine + dot
@@ -678,6 +685,61 @@ __global__ __launch_bounds__(kNT) void k_group_update(const CgSlice* tab, int ns
   update_body(a, Blk{lb, 0, c.upd_gx, 1}, red);
 }
 
+// Images of every problem of a weight group (rows, then columns).
+__global__ __launch_bounds__(kNT) void k_group_img_rows(const WeightSlice* tab) {
+  __shared__ float2 lds[kRowB * fft_stride(256)];
+  __shared__ float2 twt[kTwMax];
+  __shared__ double red[kNT / 64];
+  const WeightSlice& c = tab[blockIdx.y];
+  RowArgs a{};
+  a.P = c.gram.P; a.Q = c.gram.Q; a.T = c.gram.T;
+  const int gx = a.P / row_block(a.P), lb = (int)blockIdx.x;
+  if (lb >= gx * a.T) return;
+  a.mode = ROW_PLAIN;
+  a.sign = +1;
+  a.src = c.x;
+  a.dst = c.t;
+  a.scale = 1.0f;
+  a.tw = c.twQ;
+  const Blk b{lb % gx, lb / gx, gx, a.T};
+  SLRX_SWITCH_N(a.Q, rows_t_body<N_, +1>(a, b, lds, twt, red))
+}
+__global__ __launch_bounds__(kNT) void k_group_img_cols(const WeightSlice* tab) {
+  __shared__ float2 lds[kPlainCols * fft_stride(256)];
+  __shared__ float2 twt[kTwMax];
+  const WeightSlice& c = tab[blockIdx.y];
+  ColArgs a{};
+  a.P = c.gram.P; a.Q = c.gram.Q; a.T = c.gram.T;
+  const int gx = a.Q / plain_cols(a.Q), lb = (int)blockIdx.x;
+  if (lb >= gx * a.T) return;
+  a.sign = +1;
+  a.src = c.t;
+  a.dst = c.img;
+  a.scale = c.img_scale;
+  a.tw = c.twP;
+  const Blk b{lb % gx, lb / gx, gx, a.T};
+  SLRX_SWITCH_N(a.P, cols_plain_body<N_, +1>(a, b, lds, twt))
+}
+int image_row_blocks(int P, int T) { return P / row_block(P) * T; }
+int image_col_blocks(int Q, int T) { return Q / plain_cols(Q) * T; }
+hipError_t launch_group_images(const WeightGroup& g, hipStream_t s) {
+  k_group_img_rows<<<dim3((g.row_blocks + 7) / 8 * 8, g.ns), kNT, 0, s>>>(g.tab);
+  k_group_img_cols<<<dim3((g.col_blocks + 7) / 8 * 8, g.ns), kNT, 0, s>>>(g.tab);
+  return hipGetLastError();
+}
+
+// The last residual norms of problems i0 .. i0 + n - 1 of a CG group.
+__global__ __launch_bounds__(kNT) void k_group_store(const CgSlice* tab, int fin, GroupIts it) {
+  __shared__ double red[kNT / 64];
+  const CgSlice& c = tab[blockIdx.x];
+  const double v = fin ? reduce_partials<kNT>(c.partA, c.nfin, red) : reduce_partials<kNT>(c.partB, c.nupd, red);
+  if (threadIdx.x == 0) c.rr_out[it.it[blockIdx.x]] = v;
+}
+hipError_t launch_group_store(const CgGroup& g, int i0, int n, int fin, const GroupIts& it, hipStream_t s) {
+  k_group_store<<<n, kNT, 0, s>>>(g.tab + i0, fin, it);
+  return hipGetLastError();
+}
+
 // The problem's own grids and partial counts (what its single launches use).
 void cg_slice_grids(CgSlice& c) {
   c.rows_gx = c.P / row_block(c.P);
@@ -747,8 +809,7 @@ hipError_t launch_rows(const RowArgs& a, hipStream_t s) { SLRX_DISPATCH_N(a.Q, r
 
 template <int N>
 static hipError_t cols_plain_n(const ColArgs& a, hipStream_t s) {
-  const int cb = a.Q < 16 ? a.Q : 16;
-  dim3 grid(a.Q / cb, a.T);
+  dim3 grid(a.Q / plain_cols(a.Q), a.T);
   if (a.sign < 0) k_cols_plain<N, -1><<<grid, kNT, 0, s>>>(a);
   else k_cols_plain<N, +1><<<grid, kNT, 0, s>>>(a);
   return hipGetLastError();

@@ -112,6 +112,7 @@ struct CgSlice {
   const float2 *twQ, *twP;              // complex64 twiddles of the row and column lengths
   double *partA, *partB, *rr_hist;
   int* flag;
+  double* rr_out;                       // record of the last residual norm by outer iteration
   int nfin, nupd;                       // partial counts of the finishing and update passes
   int rows_gx, rows_gy, cols_gx, upd_gx;  // the problem's own grids
   int rows0, cols0, upd0;               // its first block in the grouped grids (multiples of 8)
@@ -129,6 +130,13 @@ hipError_t launch_group_rows(const CgGroup& g, int mode, int k, hipStream_t s);
 hipError_t launch_group_pen(const CgGroup& g, hipStream_t s);
 hipError_t launch_group_fin(const CgGroup& g, int init, hipStream_t s);
 hipError_t launch_group_update(const CgGroup& g, int k, hipStream_t s);
+// Outer iteration of each problem of a grouped launch (at most kGroupIts of them).
+constexpr int kGroupIts = 64;
+struct GroupIts {
+  short it[kGroupIts];
+};
+// The last residual norms of problems i0 .. i0 + n - 1 (fin: of the finishing pass's partials).
+hipError_t launch_group_store(const CgGroup& g, int i0, int n, int fin, const GroupIts& it, hipStream_t s);
 
 // Multichannel data term (k_coil.hip): complex64 forward half, complex128
 // adjoint half after the sampling mask.
@@ -366,6 +374,33 @@ struct SpecArgs {
 };
 bool spec_supported(int N1, int N2, int M);
 int spec_groups(int N1, int N2, int M, size_t cap);
+int spec_per_group(int s, int ngroups);  // eigenvectors per group
 hipError_t launch_spec_masks(const SpecArgs& a, double2* wsum, hipStream_t st);
+
+// Grouped weight updates (batches): images, Gram matrices, and, after the eigenpairs,
+// eps, lag sums and masks of problems that share the filter (spec_supported), one launch
+// per kernel for all of them; every problem's blocks do what they do in its own launches.
+struct WeightSlice {
+  const float2* x;                // k-space iterate
+  float2 *t, *img;                // transposed scratch, images
+  const float2 *twP, *twQ;        // complex64 twiddles
+  float img_scale;                // 1 / sqrt(P Q)
+  GramArgs gram;
+  WeightArgs w;                   // its records point at outer iteration 0
+  SpecArgs spec;
+  MaskArgs mask;
+};
+struct WeightGroup {
+  const WeightSlice* tab;         // device copy of the table, ns <= kGroupIts entries
+  int ns;
+  int N1, N2, M, ngroups;
+  int maxP, maxQ, row_blocks, col_blocks;  // largest over the problems
+  long maxPQ;
+};
+int image_row_blocks(int P, int T);
+int image_col_blocks(int Q, int T);
+hipError_t launch_group_images(const WeightGroup& g, hipStream_t s);
+hipError_t launch_group_gram(const WeightGroup& g, hipStream_t s);
+hipError_t launch_group_weights(const WeightGroup& g, const GroupIts& it, hipStream_t s);
 
 }  // namespace slrx

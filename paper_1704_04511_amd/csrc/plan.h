@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/slrx.h"
+#include "kernels.h"
 
 namespace slrx {
 
@@ -117,6 +118,8 @@ struct slrx_plan {
   hipEvent_t ev_step = nullptr;  // ordering against a shared batched eigen-decomposition
   hipEvent_t ev_begin = nullptr; // start of a lock-step engine step (timing of the CG strategy)
   int it_next = 0;               // next outer iteration (lock-step engine)
+  bool ev_weights = false;       // ev_step marks this step's weights (else the engine's own event does)
+  const void* on_cg = nullptr;   // the engine whose grouped CG ran this plan's last work, or null
   hipEvent_t ev_iter[2] = {nullptr, nullptr};  // end of the last two engine steps (server pacing)
   std::vector<hipEvent_t> ev_phase;
   // per-kernel-class launch timing (SLRX_FLAG_KTIME): event pairs, reused across runs
@@ -181,6 +184,9 @@ hipError_t eigh_backtr(const EighBufs& e, hipStream_t s);  // Z <- Q Z (A used a
 slrx_status dc_prepare(slrx_plan* pl);
 slrx_status step_weights(slrx_plan* pl, int it, bool first, double gamma, const double2* U = nullptr,
                          const double* lamv = nullptr, bool want_H = false, const int* stall = nullptr);
+GramArgs gram_args(slrx_plan* pl, double2* R, bool rowmajor);
+void weight_args(slrx_plan* pl, int it, bool first, double gamma, const double2* U, const double* lamv,
+                 const int* stall, WeightArgs& wa, SpecArgs& sa, MaskArgs& ma);
 // Weight update of the pixel-wise prior (SLRX_FLAG_HLR_VOXEL), in place of
 // step_gram, step_eigh and step_weights.
 slrx_status step_voxel(slrx_plan* pl, int it, bool first, double gamma);

@@ -284,6 +284,7 @@ static void scheduler_main(slrx_server* s) {
           st = fail(SLRX_EDEVICE, "hipEventRecord failed");
       }
       if (st != SLRX_OK) {  // device-side state of the step is unknown: fail every active request
+        engine_drain(s->eig);
         for (Req* r : active) {
           (void)hipStreamSynchronize(r->plan->stream);
           r->plan->running = false;

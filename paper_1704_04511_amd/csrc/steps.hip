@@ -97,23 +97,27 @@ slrx_status slrx::images(slrx_plan* pl) { return fft2(pl, pl->x, pl->img, +1, nu
 // tridiagonalisation, column-major into Rm for rocSOLVER zheevd (or when
 // colmajor is forced, for the single-step entry point).
 slrx_status slrx::step_gram(slrx_plan* pl, bool colmajor, double2* R_out) {
-  const slrx_dims& d = pl->d;
   KTimer kt(pl, SLRX_K_GRAM);
   STCHK(images(pl));
+  const bool lib = pl->lib_eigh() || colmajor;
+  HIPCHK(launch_gram(gram_args(pl, R_out ? R_out : (lib ? pl->Rm : pl->Aw), !lib), pl->stream));
+  return SLRX_OK;
+}
+
+GramArgs slrx::gram_args(slrx_plan* pl, double2* R, bool rowmajor) {
+  const slrx_dims& d = pl->d;
   GramArgs ga{};
   ga.P = d.P; ga.Q = d.Q; ga.T = d.T; ga.N1 = d.N1; ga.N2 = d.N2; ga.M = d.M;
   ga.rho = pl->img;
   ga.c1 = pl->c1;
   ga.g = pl->g;
-  const bool lib = pl->lib_eigh() || colmajor;
-  ga.R = R_out ? R_out : (lib ? pl->Rm : pl->Aw);
-  ga.rowmajor = lib ? 0 : 1;
+  ga.R = R;
+  ga.rowmajor = rowmajor ? 1 : 0;
   ga.twP = pl->twPd;
   ga.twQ = pl->twQd;
   ga.circ = (pl->prm.flags & SLRX_FLAG_GIRAF) ? 1 : 0;
   ga.bad = (int*)(pl->info + kInfoNonfinite);
-  HIPCHK(launch_gram(ga, pl->stream));
-  return SLRX_OK;
+  return ga;
 }
 
 // Eigen-decomposition of the Gram matrix: Householder tridiagonalisation,
@@ -278,9 +282,36 @@ slrx_status slrx::step_eigh(slrx_plan* pl, int it) {
 // diagonal sums). want_H also forms H (in Hre / Him) on the spectral path.
 slrx_status slrx::step_weights(slrx_plan* pl, int it, bool first, double gamma, const double2* U,
                                const double* lamv, bool want_H, const int* stall) {
+  const int s = pl->s();
+  WeightArgs wa;
+  SpecArgs sa;
+  MaskArgs ma;
+  weight_args(pl, it, first, gamma, U, lamv, stall, wa, sa, ma);
+  {
+    KTimer kt(pl, SLRX_K_FILTER);
+    if (sa.ngroups > 0) {
+      HIPCHK(launch_eps(wa, pl->stream));
+      HIPCHK(launch_spec_masks(sa, pl->wsum, pl->stream));
+      if (want_H) {
+        HIPCHK(launch_weights(wa, pl->stream, false));
+        HIPCHK(launch_filter_product(s, pl->VT, pl->Hre, pl->Him, pl->stream));
+      }
+    } else {
+      HIPCHK(launch_weights(wa, pl->stream));
+      HIPCHK(launch_filter_product(s, pl->VT, pl->Hre, pl->Him, pl->stream));
+    }
+  }
+  KTimer kt(pl, SLRX_K_MASKS);
+  HIPCHK(launch_masks(ma, pl->stream));
+  return SLRX_OK;
+}
+
+// Arguments of the weight update (sa.ngroups = 0: by way of H).
+void slrx::weight_args(slrx_plan* pl, int it, bool first, double gamma, const double2* U, const double* lamv,
+                       const int* stall, WeightArgs& wa, SpecArgs& sa, MaskArgs& ma) {
   const slrx_dims& d = pl->d;
   const int s = d.N1 * d.N2 * d.M;
-  WeightArgs wa{};
+  wa = WeightArgs{};
   wa.s = s;
   wa.lamv = lamv ? lamv : pl->lam;
   wa.U = U ? U : (pl->lib_eigh() ? pl->Rm : pl->UZ);
@@ -295,30 +326,19 @@ slrx_status slrx::step_weights(slrx_plan* pl, int it, bool first, double gamma, 
   wa.stall = stall ? stall : pl->flag + 8;
   wa.stalled = pl->info + kInfoStalled;
   const int ng = spec_supported(d.N1, d.N2, d.M) ? spec_groups(d.N1, d.N2, d.M, (size_t)s * s) : 0;
-  {
-    KTimer kt(pl, SLRX_K_FILTER);
-    if (ng > 0) {
-      HIPCHK(launch_eps(wa, pl->stream));
-      SpecArgs sa{};
-      sa.N1 = d.N1; sa.N2 = d.N2; sa.M = d.M; sa.s = s;
-      sa.ngroups = ng;
-      sa.lamv = wa.lamv;
-      sa.U = wa.U;
-      sa.eps = pl->scal;
-      sa.p = pl->prm.p;
-      sa.part = (double2*)pl->VT;  // s^2 double2, unused by this path until H is formed
-      sa.C = sa.part + (size_t)ng * (d.M * (d.M + 1) / 2) * (2 * d.N1 - 1) * (2 * d.N2 - 1);
-      HIPCHK(launch_spec_masks(sa, pl->wsum, pl->stream));
-      if (want_H) {
-        HIPCHK(launch_weights(wa, pl->stream, false));
-        HIPCHK(launch_filter_product(s, pl->VT, pl->Hre, pl->Him, pl->stream));
-      }
-    } else {
-      HIPCHK(launch_weights(wa, pl->stream));
-      HIPCHK(launch_filter_product(s, pl->VT, pl->Hre, pl->Him, pl->stream));
-    }
+  sa = SpecArgs{};
+  sa.ngroups = ng;
+  if (ng > 0) {
+    sa.N1 = d.N1; sa.N2 = d.N2; sa.M = d.M; sa.s = s;
+    sa.kper = spec_per_group(s, ng);
+    sa.lamv = wa.lamv;
+    sa.U = wa.U;
+    sa.eps = pl->scal;
+    sa.p = pl->prm.p;
+    sa.part = (double2*)pl->VT;  // s^2 double2, unused by this path until H is formed
+    sa.C = sa.part + (size_t)ng * (d.M * (d.M + 1) / 2) * (2 * d.N1 - 1) * (2 * d.N2 - 1);
   }
-  MaskArgs ma{};
+  ma = MaskArgs{};
   ma.P = d.P; ma.Q = d.Q; ma.N1 = d.N1; ma.N2 = d.N2; ma.M = d.M;
   ma.Hre = ng > 0 ? nullptr : pl->Hre;  // null: wsum is already the lag sums
   ma.Him = pl->Him;
@@ -327,9 +347,6 @@ slrx_status slrx::step_weights(slrx_plan* pl, int it, bool first, double gamma, 
   ma.Et = pl->Et;
   ma.twP = pl->twPd;
   ma.twQ = pl->twQd;
-  KTimer kt(pl, SLRX_K_MASKS);
-  HIPCHK(launch_masks(ma, pl->stream));
-  return SLRX_OK;
 }
 
 // Weight update of the pixel-wise prior (HLR-Voxel, SLRX_FLAG_HLR_VOXEL): per

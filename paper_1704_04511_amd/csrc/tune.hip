@@ -92,11 +92,14 @@ void save_choice(const Key& k, const Entry& en) {
 void collect(Entry& en) {
   for (size_t i = 0; i < en.pending.size();) {
     Pending& p = en.pending[i];
-    if (p.ended && hipEventQuery(p.e1) == hipSuccess) {
+    const hipError_t q = p.ended ? hipEventQuery(p.e1) : hipErrorNotReady;
+    if (q != hipErrorNotReady) {
       float ms = 0.f;
-      if (hipEventElapsedTime(&ms, p.e0, p.e1) == hipSuccess) {
+      if (q == hipSuccess && hipEventElapsedTime(&ms, p.e0, p.e1) == hipSuccess) {
         if (ms < en.best[p.cand]) en.best[p.cand] = ms;
         ++en.samples[p.cand];
+      } else {  // no time (an event of a stream that is gone): the candidate is tried again
+        (void)hipGetLastError();
       }
       --en.inflight[p.cand];
       g_pool.push_back(p.e0);
