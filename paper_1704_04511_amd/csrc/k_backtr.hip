@@ -225,8 +225,12 @@ __global__ void k_bt_explicit(int n, double2* V0, long sV) {
 // q(q+1)/2 + l, l <= q); G's strict upper triangle likewise (l < i at
 // i(i-1)/2 + l) and is overwritten level by level with X = G_AB T_B.  Indices
 // beyond the block's reflectors get tau = 0 and G = 0, so their rows and
-// columns of T are zero.
-__global__ __launch_bounds__(256) void k_bt_tmat(BtArgs a0) {
+// columns of T are zero.  A serial chain of 2 x 6 levels in one workgroup per block, bound
+// by LDS latency: a thread per entry of the widest level, and all of a thread's split sums
+// of G in flight together (51 us with 256 threads and one load at a time, 19 us so).
+constexpr int kTmatThreads = 1024;
+
+__global__ __launch_bounds__(kTmatThreads) void k_bt_tmat(BtArgs a0) {
   const BtArgs a = bt_at(a0, blockIdx.y);
   const double2* tau = a.tau;
   __shared__ double2 T[kBtNb * (kBtNb + 1) / 2];
@@ -235,66 +239,47 @@ __global__ __launch_bounds__(256) void k_bt_tmat(BtArgs a0) {
   const int k0 = kBtNb * g, nr = min(kBtNb, a.n - 1 - k0);
   auto tix = [](int l, int q) { return q * (q + 1) / 2 + l; };
   auto gix = [](int l, int i) { return i * (i - 1) / 2 + l; };
-  for (int e = tid; e < kBtNb * (kBtNb - 1) / 2; e += 256) {
-    int i = 1;
-    while ((i + 1) * i / 2 <= e) ++i;  // e = i(i-1)/2 + l, l < i
-    const int l = e - i * (i - 1) / 2;
-    double2 gsum = make_double2(0.0, 0.0);
-    if (i < nr)
-      for (int p = 0; p < a.nsplit; ++p) {
-        const double2 gv = a.Gp[((long)p * a.ng + g) * kBtNb * kBtNb + l + (long)i * kBtNb];
-        gsum.x += gv.x;
-        gsum.y += gv.y;
-      }
-    G[e] = gsum;
+  double2 gs[kBtNb * kBtNb / kTmatThreads];  // entry (l, i), l = e % 64, i = e / 64
+#pragma unroll
+  for (int u = 0; u < kBtNb * kBtNb / kTmatThreads; ++u) gs[u] = make_double2(0.0, 0.0);
+#pragma unroll 4
+  for (int p = 0; p < a.nsplit; ++p)
+#pragma unroll
+    for (int u = 0; u < kBtNb * kBtNb / kTmatThreads; ++u) {
+      const int e = tid + kTmatThreads * u, l = e % kBtNb, i = e / kBtNb;
+      if (l < i && i < nr) gs[u] = dadd(gs[u], a.Gp[((long)p * a.ng + g) * kBtNb * kBtNb + e]);
+    }
+#pragma unroll
+  for (int u = 0; u < kBtNb * kBtNb / kTmatThreads; ++u) {
+    const int e = tid + kTmatThreads * u, l = e % kBtNb, i = e / kBtNb;
+    if (l < i) G[gix(l, i)] = gs[u];
   }
-  for (int e = tid; e < kBtNb * (kBtNb + 1) / 2; e += 256) T[e] = make_double2(0.0, 0.0);
+  for (int e = tid; e < kBtNb * (kBtNb + 1) / 2; e += kTmatThreads) T[e] = make_double2(0.0, 0.0);
   __syncthreads();
   if (tid < nr) T[tix(tid, tid)] = tau[k0 + tid];
   __syncthreads();
   for (int bs = 1; bs < kBtNb; bs *= 2) {
-    const int per_pair = bs * bs, total = (kBtNb / (2 * bs)) * per_pair;  // = 32 bs <= 1024
-    double2 x[4];
-    // X(p, c) = sum_{q in B, q <= c} G(p, q) T(q, c), p in A, c in B
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + 256 * u;
-      x[u] = make_double2(0.0, 0.0);
-      if (e < total) {
-        const int pr = e / per_pair, r = e % per_pair;
-        const int a0 = 2 * bs * pr, b0 = a0 + bs;
-        const int p = a0 + r / bs, c = b0 + r % bs;
-        for (int q = b0; q <= c; ++q) x[u] = dadd(x[u], dmul(G[gix(p, q)], T[tix(q, c)]));
-      }
-    }
+    const int per_pair = bs * bs, total = (kBtNb / (2 * bs)) * per_pair;  // = 32 bs <= kTmatThreads
+    const int pr = tid / per_pair, rr = tid % per_pair;
+    const int a0 = 2 * bs * pr, b0 = a0 + bs;
+    const int r = a0 + rr / bs, c = b0 + rr % bs;
+    // X(r, c) = sum_{q in B, q <= c} G(r, q) T(q, c), r in A, c in B
+    double2 x = make_double2(0.0, 0.0);
+    if (tid < total)
+      for (int q = b0; q <= c; ++q) x = dadd(x, dmul(G[gix(r, q)], T[tix(q, c)]));
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + 256 * u;
-      if (e < total) {
-        const int pr = e / per_pair, r = e % per_pair;
-        const int a0 = 2 * bs * pr, b0 = a0 + bs;
-        G[gix(a0 + r / bs, b0 + r % bs)] = x[u];
-      }
-    }
+    if (tid < total) G[gix(r, c)] = x;
     __syncthreads();
     // T(r, c) = -sum_{p in A, p >= r} T(r, p) X(p, c), r in A, c in B
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + 256 * u;
-      if (e < total) {
-        const int pr = e / per_pair, rr = e % per_pair;
-        const int a0 = 2 * bs * pr, b0 = a0 + bs;
-        const int r = a0 + rr / bs, c = b0 + rr % bs;
-        double2 acc = make_double2(0.0, 0.0);
-        for (int p = r; p < b0; ++p) acc = dadd(acc, dmul(T[tix(r, p)], G[gix(p, c)]));
-        T[tix(r, c)] = make_double2(-acc.x, -acc.y);
-      }
+    if (tid < total) {
+      double2 acc = make_double2(0.0, 0.0);
+      for (int p = r; p < b0; ++p) acc = dadd(acc, dmul(T[tix(r, p)], G[gix(p, c)]));
+      T[tix(r, c)] = make_double2(-acc.x, -acc.y);
     }
     __syncthreads();
   }
   double2* out = a.Tb + (long)g * kBtNb * kBtNb;
-  for (int e = tid; e < kBtNb * kBtNb; e += 256) {
+  for (int e = tid; e < kBtNb * kBtNb; e += kTmatThreads) {
     const int r = e % kBtNb, c = e / kBtNb;
     out[e] = r <= c ? T[tix(r, c)] : make_double2(0.0, 0.0);
   }
@@ -331,7 +316,7 @@ hipError_t launch_backtransform(const BackTrArgs& b, hipStream_t s) {
   const int mt = (n - 1 + kTM - 1) / kTM;  // row tiles of the largest block (m = n - 1)
   a.nsplit = kBtSplitG;
   k_bt_gemm<BT_GRAM><<<dim3(kBtNb / kTN, 1, nb * ng * kBtSplitG), 256, 0, s>>>(a, ng * kBtSplitG);
-  k_bt_tmat<<<dim3(ng, nb), 256, 0, s>>>(a);
+  k_bt_tmat<<<dim3(ng, nb), kTmatThreads, 0, s>>>(a);
   a.nsplit = 1;
   k_bt_gemm<BT_YMAT><<<dim3(kBtNb / kTN, mt, nb * ng), 256, 0, s>>>(a, ng);
   const int nt = (n + kTN - 1) / kTN;

@@ -14,6 +14,7 @@
 //   = sum_Delta w_{m',m}[Delta] e^{+2 pi i Delta.r},
 //   w_{m',m}[Delta] = sum_{a'-a = Delta} H[(m',a'),(m,a)].
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -366,26 +367,39 @@ hipError_t launch_filter_product(int s, const double* VT, double* Hre, double* H
 // part[g][w][f], added in a fixed order by k_spec_reduce; k_spec_inverse
 // transforms back to the lags.
 constexpr int kSpecF2 = 8;     // columns f2 per workgroup
-constexpr int kSpecPf = kSpecMaxS / 256;  // prefetched eigenvector entries per thread
+constexpr int kSpecSmall = 512; // largest s of four subgroups per workgroup (otherwise two)
 constexpr int kSpecMaxL1 = 32; // 256 threads = 32 rows f1 x 8 columns f2
 
-template <int M>
+// LDS of a subgroup (double2), at least its 256 entries of the final sum.
+__host__ __device__ constexpr int spec_sub_elems(int N1, int s, int M) {
+  return s + M * N1 * kSpecF2 > 256 ? s + M * N1 * kSpecF2 : 256;
+}
+
+template <int M, int S>
 SLRX_DEV void spec_accum_body(const SpecArgs& a, int bx, int by, double2* spl) {
   constexpr int W = M * (M + 1) / 2;
   const int N1 = a.N1, N2 = a.N2, s = a.s;
   const int L1 = 2 * N1 - 1, L2 = 2 * N2 - 1, F = L1 * L2;
   const int c0 = by * kSpecF2, nf2 = min(kSpecF2, L2 - c0);
-  double2* v = spl;                    // eigenvector k, s entries
-  double2* Y = v + s;                  // [M N1][nf2]
-  double2* t1 = Y + M * N1 * kSpecF2;  // e^{-2 pi i j / L1}
-  double2* t2 = t1 + L1;               // e^{-2 pi i j / L2}
-  const int tid = threadIdx.x;
-  for (int j = tid; j < L1; j += 256) {
+  constexpr int PF = S == 4 ? kSpecSmall / 256 : kSpecMaxS / 256;  // entries per thread
+  const int sub = threadIdx.x / 256, tid = threadIdx.x % 256;
+  double2* t1 = spl;                        // e^{-2 pi i j / L1}
+  double2* t2 = t1 + L1;                    // e^{-2 pi i j / L2}
+  double2* v = t2 + L2 + (long)sub * spec_sub_elems(N1, s, M);  // eigenvector k, s entries
+  double2* Y = v + s;                       // [M N1][nf2]
+  double* al = (double*)(t2 + L2 + S * spec_sub_elems(N1, s, M));  // alpha of the group
+  const int k0 = bx * a.kper, k1 = min(s, k0 + a.kper);
+  const double e = *a.eps, ex = a.p * 0.5 - 1.0;
+  for (int k = k0 + threadIdx.x; k < k1; k += 256 * S) {
+    const double lk = a.lamv[k];
+    al[k - k0] = pow((lk > 0.0 ? lk : 0.0) + e, ex);
+  }
+  for (int j = threadIdx.x; j < L1; j += 256 * S) {
     double sn, cs;
     sincospi(-2.0 * j / L1, &sn, &cs);
     t1[j] = make_double2(cs, sn);
   }
-  for (int j = tid; j < L2; j += 256) {
+  for (int j = threadIdx.x; j < L2; j += 256 * S) {
     double sn, cs;
     sincospi(-2.0 * j / L2, &sn, &cs);
     t2[j] = make_double2(cs, sn);
@@ -395,27 +409,26 @@ SLRX_DEV void spec_accum_body(const SpecArgs& a, int bx, int by, double2* spl) {
   double2 acc[W];
 #pragma unroll
   for (int w = 0; w < W; ++w) acc[w] = make_double2(0.0, 0.0);
-  const int k0 = bx * a.kper, k1 = min(s, k0 + a.kper);
-  const double e = *a.eps, ex = a.p * 0.5 - 1.0;
-  // eigenvector k + 1 is loaded into registers while k is transformed
-  double2 nxt[kSpecPf];
+  // the subgroup's next eigenvector is loaded into registers while k is transformed
+  double2 nxt[PF];
 #pragma unroll
-  for (int r = 0; r < kSpecPf; ++r) {
+  for (int r = 0; r < PF; ++r) {
     const int i = tid + 256 * r;
-    nxt[r] = (k0 < k1 && i < s) ? a.U[(long)k0 * s + i] : make_double2(0.0, 0.0);
+    nxt[r] = (k0 + sub < k1 && i < s) ? a.U[(long)(k0 + sub) * s + i] : make_double2(0.0, 0.0);
   }
-  for (int k = k0; k < k1; ++k) {
+  for (int kb = k0; kb < k1; kb += S) {
+    const int k = kb + sub;  // beyond k1: nothing is added
     __syncthreads();  // the previous eigenvector's v and Y are no longer read
 #pragma unroll
-    for (int r = 0; r < kSpecPf; ++r) {
+    for (int r = 0; r < PF; ++r) {
       const int i = tid + 256 * r;
       if (i < s) v[i] = nxt[r];
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kSpecPf; ++r) {
+    for (int r = 0; r < PF; ++r) {
       const int i = tid + 256 * r;
-      if (k + 1 < k1 && i < s) nxt[r] = a.U[(long)(k + 1) * s + i];
+      if (k + S < k1 && i < s) nxt[r] = a.U[(long)(k + S) * s + i];
     }
     // stage 1: Y[m N1 + a1][c] = sum_{a2} v(m, a1, a2) e^{-2 pi i a2 (c0 + c) / L2},
     // a thread per (a1, c) and all M taps (one twiddle per M products)
@@ -441,9 +454,8 @@ SLRX_DEV void spec_accum_body(const SpecArgs& a, int bx, int by, double2* spl) {
       for (int m = 0; m < M; ++m) Y[(m * N1 + a1) * kSpecF2 + c] = make_double2(sx[m], sy[m]);
     }
     __syncthreads();
-    if (act) {
-      const double lk = a.lamv[k];
-      const double al = pow((lk > 0.0 ? lk : 0.0) + e, ex);
+    if (act && k < k1) {
+      const double ak = al[k - k0];
       double2 X[M];
 #pragma unroll
       for (int m = 0; m < M; ++m) X[m] = make_double2(0.0, 0.0);
@@ -466,22 +478,36 @@ SLRX_DEV void spec_accum_body(const SpecArgs& a, int bx, int by, double2* spl) {
         for (int mp = m; mp < M; ++mp, ++w) {  // alpha X_{m'} conj(X_m)
           const double re = X[mp].x * X[m].x + X[mp].y * X[m].y;
           const double im = X[mp].y * X[m].x - X[mp].x * X[m].y;
-          acc[w].x += al * re;
-          acc[w].y += al * im;
+          acc[w].x += ak * re;
+          acc[w].y += ak * im;
         }
     }
   }
-  if (act) {
+  // the subgroups' sums are added in their order, a pair product at a time
+  double2* red = t2 + L2;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    __syncthreads();
+    if (sub > 0) red[(sub - 1) * 256 + tid] = acc[w];
+    __syncthreads();
+    if (sub == 0)
+#pragma unroll
+      for (int q = 1; q < S; ++q) {
+        acc[w].x += red[(q - 1) * 256 + tid].x;
+        acc[w].y += red[(q - 1) * 256 + tid].y;
+      }
+  }
+  if (act && sub == 0) {
     const int f = f1 * L2 + c0 + fl;
 #pragma unroll
     for (int w = 0; w < W; ++w) a.part[((long)bx * W + w) * F + f] = acc[w];
   }
 }
 
-template <int M>
-__global__ __launch_bounds__(256) void k_spec_accum(SpecArgs a) {
+template <int M, int S>
+__global__ __launch_bounds__(256 * S) void k_spec_accum(SpecArgs a) {
   extern __shared__ double2 spl[];
-  spec_accum_body<M>(a, blockIdx.x, blockIdx.y, spl);
+  spec_accum_body<M, S>(a, blockIdx.x, blockIdx.y, spl);
 }
 
 // Slice q of the groups: C[q][w][f] = sum over groups g = q, q + kSpecSlices, ..
@@ -515,11 +541,13 @@ SLRX_DEV void spec_inverse_body(const SpecArgs& a, double2* wsum, int W, int bx,
   double2* t1 = Ts + F;    // e^{+2 pi i j / L1}
   double2* t2 = t1 + L1;   // e^{+2 pi i j / L2}
   const long WF = (long)W * F;
+  const double2* C = a.ngroups > kSpecSlices ? a.C : a.part;  // few groups: their own sums
   for (int f = tid; f < F; f += 1024) {
     double sx = 0.0, sy = 0.0;
 #pragma unroll
     for (int q = 0; q < kSpecSlices; ++q) {
-      const double2 v = a.C[q * WF + (long)w * F + f];
+      if (q >= a.ngroups) break;
+      const double2 v = C[q * WF + (long)w * F + f];
       sx += v.x;
       sy += v.y;
     }
@@ -583,18 +611,48 @@ bool spec_supported(int N1, int N2, int M) {
   return acc <= 65536 && inv <= 65536;
 }
 
-// Groups of eigenvectors that fit the partial sums (and C) into cap double2.
+// Groups of eigenvectors that fit the partial sums (and C) into cap double2, at most
+// one workgroup per CU over the blocks of columns: above kSpecSmall entries a workgroup
+// takes the registers of a whole CU, and a second round would double the time.
 int spec_groups(int N1, int N2, int M, size_t cap) {
   const int s = N1 * N2 * M, W = M * (M + 1) / 2;
   const size_t per = (size_t)W * (2 * N1 - 1) * (2 * N2 - 1);
   const long gmax = (long)(cap / per) - kSpecSlices;  // room for the slice sums C
   if (gmax < 1) return 0;
-  const int g = (int)std::min<long>(std::min<long>(gmax, 128), s);
+  const int blocks = (2 * N2 - 1 + kSpecF2 - 1) / kSpecF2;
+  const int g = (int)std::min<long>(std::min<long>(gmax, std::max(1, 256 / blocks)), s);
   const int kper = (s + g - 1) / g;
   return (s + kper - 1) / kper;
 }
 
 int spec_per_group(int s, int ngroups) { return (s + ngroups - 1) / ngroups; }
+
+// Four subgroups up to kSpecSmall entries, where their eigenvectors fit 128 registers
+// a thread, otherwise two.
+template <class F>
+static hipError_t spec_subgroups(int s, F&& launch) {
+  if (s <= kSpecSmall) return launch(std::integral_constant<int, 4>{});
+  return launch(std::integral_constant<int, 2>{});
+}
+
+// LDS of the accumulation: two subgroups of 64 KB at most, the twiddles and alpha.
+constexpr size_t kSpecLdsMax = 160 * 1024;
+static size_t spec_lds(int N1, int N2, int M, int kper, int S) {
+  const size_t tw = (size_t)(2 * N1 - 1) + (2 * N2 - 1);
+  return (tw + (size_t)S * spec_sub_elems(N1, N1 * N2 * M, M)) * sizeof(double2) + (size_t)kper * sizeof(double);
+}
+
+template <int M>
+static hipError_t accum_m(const SpecArgs& a, dim3 grid, hipStream_t st) {
+  return spec_subgroups(a.s, [&](auto sub) {
+    constexpr int S = decltype(sub)::value;
+    static LdsLimit lim;
+    const hipError_t e = lim.ensure((const void*)k_spec_accum<M, S>, kSpecLdsMax);
+    if (e != hipSuccess) return e;
+    k_spec_accum<M, S><<<grid, 256 * S, spec_lds(a.N1, a.N2, M, a.kper, S), st>>>(a);
+    return hipGetLastError();
+  });
+}
 
 hipError_t launch_spec_masks(const SpecArgs& a0, double2* wsum, hipStream_t st) {
   SpecArgs a = a0;
@@ -602,19 +660,20 @@ hipError_t launch_spec_masks(const SpecArgs& a0, double2* wsum, hipStream_t st) 
   const int L1 = 2 * a.N1 - 1, L2 = 2 * a.N2 - 1, F = L1 * L2;
   a.kper = spec_per_group(a.s, a.ngroups);
   const dim3 grid(a.ngroups, (L2 + kSpecF2 - 1) / kSpecF2);
-  const size_t lds = ((size_t)a.s + (size_t)M * a.N1 * kSpecF2 + L1 + L2) * sizeof(double2);
+  hipError_t e;
   switch (M) {
-    case 1: k_spec_accum<1><<<grid, 256, lds, st>>>(a); break;
-    case 2: k_spec_accum<2><<<grid, 256, lds, st>>>(a); break;
-    case 3: k_spec_accum<3><<<grid, 256, lds, st>>>(a); break;
-    case 4: k_spec_accum<4><<<grid, 256, lds, st>>>(a); break;
-    case 5: k_spec_accum<5><<<grid, 256, lds, st>>>(a); break;
+    case 1: e = accum_m<1>(a, grid, st); break;
+    case 2: e = accum_m<2>(a, grid, st); break;
+    case 3: e = accum_m<3>(a, grid, st); break;
+    case 4: e = accum_m<4>(a, grid, st); break;
+    case 5: e = accum_m<5>(a, grid, st); break;
     default: return hipErrorInvalidValue;
   }
-  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_spec_reduce<<<(unsigned)(((long)kSpecSlices * W * F + 255) / 256), 256, 0, st>>>(a, W);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (a.ngroups > kSpecSlices) {
+    k_spec_reduce<<<(unsigned)(((long)kSpecSlices * W * F + 255) / 256), 256, 0, st>>>(a, W);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   k_spec_inverse<<<W, 1024, (2 * (size_t)F + L1 + L2) * sizeof(double2), st>>>(a, wsum, W);
   return hipGetLastError();
 }
@@ -750,11 +809,11 @@ __global__ void k_group_eps(const WeightSlice* tab, int ns, GroupIts it) {
   a.eps_out += it.it[i];
   eps_body(a);
 }
-template <int M>
-__global__ __launch_bounds__(256) void k_group_spec_accum(const WeightSlice* tab) {
+template <int M, int S>
+__global__ __launch_bounds__(256 * S) void k_group_spec_accum(const WeightSlice* tab) {
   extern __shared__ double2 spl[];
   const SpecArgs a = tab[blockIdx.z].spec;
-  spec_accum_body<M>(a, blockIdx.x, blockIdx.y, spl);
+  spec_accum_body<M, S>(a, blockIdx.x, blockIdx.y, spl);
 }
 __global__ __launch_bounds__(256) void k_group_spec_reduce(const WeightSlice* tab, int W) {
   const SpecArgs a = tab[blockIdx.y].spec;
@@ -802,20 +861,35 @@ hipError_t launch_group_gram(const WeightGroup& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int M>
+static hipError_t group_accum_m(const WeightGroup& g, dim3 grid, hipStream_t st) {
+  const int n = g.N1 * g.N2 * M, kper = spec_per_group(n, g.ngroups);
+  return spec_subgroups(n, [&](auto sub) {
+    constexpr int S = decltype(sub)::value;
+    static LdsLimit lim;
+    const hipError_t e = lim.ensure((const void*)k_group_spec_accum<M, S>, kSpecLdsMax);
+    if (e != hipSuccess) return e;
+    k_group_spec_accum<M, S><<<grid, 256 * S, spec_lds(g.N1, g.N2, M, kper, S), st>>>(g.tab);
+    return hipGetLastError();
+  });
+}
+
 hipError_t launch_group_weights(const WeightGroup& g, const GroupIts& it, hipStream_t s) {
   const int M = g.M, W = M * (M + 1) / 2, L1 = 2 * g.N1 - 1, L2 = 2 * g.N2 - 1, F = L1 * L2;
   k_group_eps<<<1, kGroupIts, 0, s>>>(g.tab, g.ns, it);
   const dim3 grid(g.ngroups, (L2 + kSpecF2 - 1) / kSpecF2, g.ns);
-  const size_t lds = ((size_t)g.N1 * g.N2 * M + (size_t)M * g.N1 * kSpecF2 + L1 + L2) * sizeof(double2);
+  hipError_t e;
   switch (M) {
-    case 1: k_group_spec_accum<1><<<grid, 256, lds, s>>>(g.tab); break;
-    case 2: k_group_spec_accum<2><<<grid, 256, lds, s>>>(g.tab); break;
-    case 3: k_group_spec_accum<3><<<grid, 256, lds, s>>>(g.tab); break;
-    case 4: k_group_spec_accum<4><<<grid, 256, lds, s>>>(g.tab); break;
-    case 5: k_group_spec_accum<5><<<grid, 256, lds, s>>>(g.tab); break;
+    case 1: e = group_accum_m<1>(g, grid, s); break;
+    case 2: e = group_accum_m<2>(g, grid, s); break;
+    case 3: e = group_accum_m<3>(g, grid, s); break;
+    case 4: e = group_accum_m<4>(g, grid, s); break;
+    case 5: e = group_accum_m<5>(g, grid, s); break;
     default: return hipErrorInvalidValue;
   }
-  k_group_spec_reduce<<<dim3((unsigned)(((long)kSpecSlices * W * F + 255) / 256), g.ns), 256, 0, s>>>(g.tab, W);
+  if (e != hipSuccess) return e;
+  if (g.ngroups > kSpecSlices)
+    k_group_spec_reduce<<<dim3((unsigned)(((long)kSpecSlices * W * F + 255) / 256), g.ns), 256, 0, s>>>(g.tab, W);
   k_group_spec_inverse<<<dim3(W, g.ns), 1024, (2 * (size_t)F + L1 + L2) * sizeof(double2), s>>>(g.tab, W);
   k_group_mask_rows<<<dim3((unsigned)(((long)W * L1 * g.maxQ + 255) / 256), g.ns), 256, 0, s>>>(g.tab, W);
   k_group_mask_cols<<<dim3((unsigned)(((long)W * g.maxPQ + 255) / 256), g.ns), 256, 0, s>>>(g.tab, W);
