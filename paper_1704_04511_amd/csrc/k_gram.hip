@@ -364,8 +364,14 @@ hipError_t launch_filter_product(int s, const double* VT, double* Hre, double* H
 // f2); per eigenvector the N2-point DFTs of its rows for those columns (stage
 // 1, in LDS), then one thread per frequency (f1, f2) finishes its M spectra
 // and accumulates the W pair products.  Partial sums per group go to
-// part[g][w][f], added in a fixed order by k_spec_reduce; k_spec_inverse
-// transforms back to the lags.
+// part[g][w][f], added in a fixed order by k_spec_reduce (by the inverse transform
+// itself if there are at most kSpecSlices groups); k_spec_inverse transforms back to
+// the lags.
+// The chain over a group's eigenvectors bounds it (about 11000 cycles each at s = 405,
+// stage 1 with 72 of 256 threads at work), and part's room bounds the number of groups,
+// so S subgroups of 256 threads take every S-th eigenvector of a group and are added at
+// the end: 72 -> 38 us at s = 75, 53 -> 44 at 405 and 124 -> 105 at 1125, with alpha taken
+// once per eigenvector instead of once per thread.
 constexpr int kSpecF2 = 8;     // columns f2 per workgroup
 constexpr int kSpecSmall = 512; // largest s of four subgroups per workgroup (otherwise two)
 constexpr int kSpecMaxL1 = 32; // 256 threads = 32 rows f1 x 8 columns f2
