@@ -29,7 +29,15 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 
 
-def algorithmic_bytes(kind: str, T: int, P: int, Q: int, M: int, N1: int, N2: int, nc: int = 0) -> float:
+def rows_volumes(n_cg: int) -> float:
+    """Volumes that a row pass moves, averaged over a CG of n_cg iterations: the initial
+    residual reads x and writes t, the first iteration reads r and writes p and t, every
+    later one reads r, q, x, p and writes r, x, p, t."""
+    return (2 + 3 + 8 * (n_cg - 1)) / (n_cg + 1) if n_cg > 0 else 2
+
+
+def algorithmic_bytes(kind: str, T: int, P: int, Q: int, M: int, N1: int, N2: int, nc: int = 0,
+                      n_cg: int = 10) -> float:
     """Bytes one launch of a kernel class must move (complex64 = 8 B per element).
 
     Units: V = T P Q volume elements; mask S 1 B per element; masks E
@@ -39,14 +47,14 @@ def algorithmic_bytes(kind: str, T: int, P: int, Q: int, M: int, N1: int, N2: in
     W = M * (M + 1) // 2
     s = N1 * N2 * M
     c = 8
-    if kind == "rows":     # read r, p_old; write p and the row-transformed volume t
-        return 4 * V * c
+    if kind == "rows":
+        return rows_volumes(n_cg) * V * c
     if kind == "cols":     # read t (coils: the image rho) and the masks E; write t
         return 2 * V * c + W * P * Q * c
-    if kind == "fin":      # read t, p, S (1 B); write q (coils: no S; the complex128 group
+    if kind == "fin":      # read t, p, r, S (1 B); write q (coils: no S; the complex128 group
         if nc:             # sums of the coil combination instead)
-            return 3 * V * c + min(nc, 4) * V * 16
-        return 3 * V * c + V
+            return 4 * V * c + min(nc, 4) * V * 16
+        return 4 * V * c + V
     if kind == "coil":     # columns: read t and the maps, write rho and nc volumes (complex64);
         g = min(nc, 4)     # rows: read the nc volumes and S, write them in complex128;
         return ((2 + nc) * V * c + nc * P * Q * c     # combine: read the complex128 volumes and
@@ -81,7 +89,8 @@ def spectral_groups(N1: int, N2: int, M: int) -> int:
     gmax = (s * s) // (W * L1 * L2) - 8
     if gmax < 1:
         return 0
-    g = min(gmax, 128, s)
+    blocks = -(-L2 // 8)
+    g = min(gmax, max(1, 256 // blocks), s)
     kper = -(-s // g)
     return -(-s // kper)
 
@@ -137,17 +146,18 @@ def backtr_flop(n: int, nb: int = 64) -> float:
 
 
 def tri_launches(n: int) -> int:
-    """Launches of one tridiagonalisation (the library's launch schedule): one per
-    column up to the last 96, which share one launch."""
-    return max(n - 96, 0) + 1
+    """Launches of one tridiagonalisation (the library's launch schedule): the resident
+    kernel (after the fill of its exchange buffers) for 129 to 1280 unknowns, otherwise one
+    per column, and one for the last 96 columns."""
+    return 3 if 128 < n <= 1280 else max(n - 96, 0) + 1
 
 
-def roofline(kind, avg_ms, T, P, Q, M, N1, N2, nc=0):
+def roofline(kind, avg_ms, T, P, Q, M, N1, N2, nc=0, n_cg=10):
     """Roofline entry of one kernel class.  The filter product and the
     back-transformation are FP64 MFMA contractions (the spectral lag sums that
     replace the filter product where the shape allows are FP64 vector work); the
     tridiagonalisation is FP64 vector arithmetic, (16/3) s^3 flops per
-    decomposition, reported per launch; every other class is bound by HBM."""
+    decomposition; every other class is bound by HBM."""
     s = N1 * N2 * M
     if kind == "filter" and spectral_groups(N1, N2, M):  # FP64 vector arithmetic
         flop = spectral_flop(N1, N2, M)
@@ -161,16 +171,14 @@ def roofline(kind, avg_ms, T, P, Q, M, N1, N2, nc=0):
         return {"bound": "mfma", "kernel": kind, "achieved": round(ach, 2), "peak": FP64_MFMA_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(ach / FP64_MFMA_PEAK_TFLOPS, 4), "traffic": None,
                 "flop_per_launch": flop, "avg_launch_ms": round(avg_ms, 5)}
-    if kind == "tri":  # FP64 vector work, per launch
-        launches = tri_launches(s)
-        flop = tri_flop(s) / launches
-        ms = avg_ms / launches
-        ach = flop / (ms * 1e-3) / 1e12
+    if kind == "tri":  # FP64 vector work, per decomposition
+        flop = tri_flop(s)
+        ach = flop / (avg_ms * 1e-3) / 1e12
         return {"bound": "alu", "kernel": kind, "achieved": round(ach, 3), "peak": FP64_VALU_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(ach / FP64_VALU_PEAK_TFLOPS, 4), "traffic": None,
-                "flop_per_launch": flop, "launches_per_decomposition": launches,
-                "avg_launch_ms": round(ms, 6)}
-    nbytes = algorithmic_bytes(kind, T, P, Q, M, N1, N2, nc)
+                "flop_per_decomposition": flop, "launches_per_decomposition": tri_launches(s),
+                "avg_decomposition_ms": round(avg_ms, 6)}
+    nbytes = algorithmic_bytes(kind, T, P, Q, M, N1, N2, nc, n_cg)
     ach = nbytes / (avg_ms * 1e-3) / 1e9
     return {"bound": "hbm", "kernel": kind, "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None, "bytes_per_launch": nbytes,
@@ -535,7 +543,7 @@ def bench_mc(args) -> int:
     kms, kcnt = st["kernel_ms"], st["kernel_count"]
     own = [k for k in ("rows", "coil", "cols", "fin", "update", "gram", "tri", "backtr", "filter", "masks")
            if kcnt[k] > 0]
-    roofs = {k: roofline(k, kms[k] / kcnt[k], T, P, Q, pb.M, pb.N1, pb.N2, nc) for k in own}
+    roofs = {k: roofline(k, kms[k] / kcnt[k], T, P, Q, pb.M, pb.N1, pb.N2, nc, pb.n_cg) for k in own}
     dom = max(own, key=lambda k: kms[k])
     out = {
         "metric": "IRLS iters/s (128x128x12, 12 coils, filter 9x9x5)",
@@ -602,7 +610,7 @@ def bench_hlr(args) -> int:
     st = plan.stats()
     kms, kcnt = st["kernel_ms"], st["kernel_count"]
     own = [k for k in ("rows", "cols", "fin", "update", "voxel") if kcnt[k] > 0]
-    roofs = {k: roofline(k, kms[k] / kcnt[k], T, P, Q, pb.M, pb.N1, pb.N2) for k in own}
+    roofs = {k: roofline(k, kms[k] / kcnt[k], T, P, Q, pb.M, pb.N1, pb.N2, n_cg=pb.n_cg) for k in own}
     dom = max(own, key=lambda k: kms[k])
     out = {
         "metric": "IRLS iters/s (256x256x20, HLR-Voxel 1x1x5 per pixel)",
@@ -774,7 +782,7 @@ PROFILE_CLASSES = {
     "fin": (("k_rows_fin",), "k_rows_fin"),
     "update": (("k_update",), "k_update"),
     "gram": (("k_gram_",), "k_gram_assemble"),
-    "tri": (("k_tri_",), "k_tri_col"),
+    "tri": (("k_tri_",), None),
     "tdeig": (("k_dc_",), None),
     "backtr": (("k_bt_",), None),
     "filter": (("k_spec_", "k_eps", "k_weights", "k_filter_product"), None),
@@ -831,8 +839,8 @@ def grouped_rooflines(root: str, sub: str) -> list:
     V = sum(sp["T"] * sp["P"] * sp["Q"] for sp in specs)
     PQ = sum(sp["P"] * sp["Q"] for sp in specs)
     W = 15  # M = 5 for every slice of the draw
-    nbytes = {"k_group_rows": 32 * V, "k_group_pen<5>": 16 * V + 8 * W * PQ, "k_group_fin": 25 * V,
-              "k_group_update": 48 * V}
+    nbytes = {"k_group_rows": rows_volumes(10) * 8 * V, "k_group_pen<5>": 16 * V + 8 * W * PQ,
+              "k_group_fin": 33 * V, "k_group_update": 48 * V}
     rows = _csv_rows(root, sub, "group_dispatches.csv")
     gcols = [c for c in ("Grid_Size_X", "Grid_Size_Y", "Grid_Size_Z") if c in rows[0]] or ["Grid_Size"]
     by = {}
@@ -848,8 +856,7 @@ def grouped_rooflines(root: str, sub: str) -> list:
     out = ["", f"# grouped CG launches of the whole draw (sum of T*P*Q = {V} elements, {V * 8 / 1e6:.0f} MB per "
                "complex FP32 vector: the working set is beyond the 256 MB MALL) against the 8 TB/s HBM peak: "
                "algorithmic bytes per launch / average duration of the launches with the largest grid "
-               "(rows: the p-update launches' 32 B per element; the one initial-residual launch per outer "
-               "iteration moves 16 and is averaged in)",
+               "(rows: the average over the 11 launches of an outer iteration, 2 to 8 volumes each)",
            f"{'kernel':<16} {'launches':>9} {'MB_per_launch':>14} {'avg_us':>9} {'GB_per_s':>10} {'frac_of_8TB':>12}"]
     for key, d in by.items():
         gmax = max(g for g, _ in d)
@@ -1085,9 +1092,10 @@ def main() -> int:
     own = [k for k in ("rows", "cols", "fin", "update", "gram", "tri", "tdeig", "backtr", "filter", "masks")
            if kcnt[k] > 0]
     dom = max(own, key=lambda k: kms[k])
-    roofs = {k: roofline(k, kms[k] / kcnt[k], T, P, Q, pb.M, pb.N1, pb.N2) for k in own if k != "tdeig"}
+    roofs = {k: roofline(k, kms[k] / kcnt[k], T, P, Q, pb.M, pb.N1, pb.N2, n_cg=pb.n_cg) for k in own if k != "tdeig"}
     if st["kernel_count"].get(dom, 0) > 0 and dom in roofs:  # the dominant kernel from the timed region itself
-        roofs[dom] = roofline(dom, st["kernel_ms"][dom] / st["kernel_count"][dom], T, P, Q, pb.M, pb.N1, pb.N2)
+        roofs[dom] = roofline(dom, st["kernel_ms"][dom] / st["kernel_count"][dom], T, P, Q, pb.M, pb.N1, pb.N2,
+                              n_cg=pb.n_cg)
     for k in roofs:
         roofs[k]["traffic"] = measured_traffic(k)
     # the CG iteration against HBM on the method's own bytes: phase time of the CG

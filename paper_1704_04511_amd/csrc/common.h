@@ -61,6 +61,24 @@ SLRX_DEV double reduce_partials(const double* part, int n, double* red) {
   return block_sum<NT>(v, red);
 }
 
+// K block sums at once, in block_sum's order; red: K NT / 64 entries.
+template <int NT, int K>
+SLRX_DEV void block_sums(double (&v)[K], double* red) {
+  constexpr int NW = NT / 64;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    for (int off = 32; off > 0; off >>= 1) v[i] += __shfl_down(v[i], off, 64);
+    if ((threadIdx.x & 63) == 0) red[i * NW + (threadIdx.x >> 6)] = v[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    v[i] = 0.0;
+    for (int w = 0; w < NW; ++w) v[i] += red[i * NW + w];
+  }
+  __syncthreads();
+}
+
 // Raises a kernel's dynamic-LDS limit once per device: the first launches on a
 // device set it (concurrent first launches may both set it, which is harmless);
 // the flag bits are atomic, so host threads can launch concurrently.

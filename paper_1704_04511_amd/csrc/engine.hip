@@ -367,13 +367,13 @@ static slrx_status run_cg_group(BatchEig& be, const std::vector<slrx_plan*>& g, 
   // initial residual r = bm - A x, then n_cg iterations
   HIPCHK(launch_group_rows(G, ROW_PLAIN, 0, s));
   HIPCHK(launch_group_pen(G, s));
-  HIPCHK(launch_group_fin(G, 1, s));
+  HIPCHK(launch_group_fin(G, 1, 0, s));
   for (int k = 0; k < n_cg; ++k) {
-    HIPCHK(launch_group_rows(G, ROW_PUPDATE, k, s));
+    HIPCHK(launch_group_rows(G, k == 0 ? ROW_START : ROW_STEP, k, s));
     HIPCHK(launch_group_pen(G, s));
-    HIPCHK(launch_group_fin(G, 0, s));
-    HIPCHK(launch_group_update(G, k, s));
+    HIPCHK(launch_group_fin(G, 0, k, s));
   }
+  if (n_cg > 0) HIPCHK(launch_group_update(G, n_cg - 1, s));
   for (int i0 = 0; i0 < G.ns; i0 += kGroupIts) {
     const int n = std::min(kGroupIts, G.ns - i0);
     GroupIts it{};

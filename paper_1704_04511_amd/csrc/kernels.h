@@ -13,24 +13,31 @@ int max_frames();  // largest T handled by the column penalty pass
 int max_taps();    // largest M
 
 // ---------------------------------------------------------------- FFT passes
-enum RowMode { ROW_PLAIN = 0, ROW_MASKED = 1, ROW_PUPDATE = 2 };
+enum RowMode { ROW_PLAIN = 0, ROW_MASKED = 1, ROW_START = 2, ROW_STEP = 3 };
+constexpr int kFinPart = 1024;  // most blocks of a finishing pass; distance of its kinds of partials
 
 // Row DFT (length Q) of a row-major volume; output transposed per frame
-// ([t][col][row]).  ROW_PUPDATE also forms p = r + beta p (beta from partials).
+// ([t][col][row]).  ROW_START begins a CG: p = r, rr_hist[0] from the partials of the
+// initial residual.  ROW_STEP ends iteration k - 1 and begins k: alpha and beta from the
+// finishing pass's partials, x += alpha p, r -= alpha q, p = r + beta p, partials of <r, r>.
 struct RowArgs {
   int P, Q, T;
   int mode;              // RowMode
   int sign;              // -1 forward, +1 inverse (unnormalised)
-  const float2* src;     // input (r for ROW_PUPDATE)
-  float2* pvec;          // ROW_PUPDATE: p (read p_old, write p)
+  const float2* src;     // input (ROW_START: r)
+  float2* pvec;          // ROW_START, ROW_STEP: p
   const uint8_t* S;      // ROW_MASKED: mask
   float2* dst;           // transposed output
   float scale;
   const float2* tw;      // e^{-2 pi i t / Q}, t < Q
-  int k;                 // ROW_PUPDATE: CG iteration index
-  const double* part;    // ROW_PUPDATE: partials holding rr_k
+  int k;                 // ROW_STEP: CG iteration index
+  const double* part;    // ROW_START: partials of rr_0; ROW_STEP: of <p,q>, <r,q>, <q,q>, kFinPart apart
   int npart;
-  double* rr_hist;       // rr_hist[k] written by block 0; rr_hist[k-1] read
+  double* rr_hist;       // ROW_START: [0] written by block 0; ROW_STEP: [k - 1] read
+  float2 *x, *r;         // ROW_STEP
+  const float2* q;       // ROW_STEP
+  double* part_rr;       // ROW_STEP: per-block partials of rr_k
+  int* flag;             // ROW_STEP: CG stop flag
 };
 hipError_t launch_rows(const RowArgs& a, hipStream_t s);
 
@@ -72,6 +79,10 @@ struct FinArgs {
   const float2* y;       // right-hand side S o b (init)
   float2* out;
   double* part;          // per-block partials
+  const float2* r;       // CG residual or null: partials of <r,out> and <out,out> too, kFinPart apart
+  const double* part_rr; // or null: block 0 sums these npart_rr partials of rr_k into *rr
+  int npart_rr;
+  double* rr;
   int* flag;             // CG stop flag (cleared by block 0 when init)
   const float2* tw;      // e^{-2 pi i t / Q}
   // multichannel data term (coil = 1): no S o v; the complex128 forward row DFT
@@ -128,7 +139,7 @@ size_t group_pen_lds(int P, int Q, int T);
 // mode: ROW_PLAIN (initial residual, x) or ROW_PUPDATE (iteration k)
 hipError_t launch_group_rows(const CgGroup& g, int mode, int k, hipStream_t s);
 hipError_t launch_group_pen(const CgGroup& g, hipStream_t s);
-hipError_t launch_group_fin(const CgGroup& g, int init, hipStream_t s);
+hipError_t launch_group_fin(const CgGroup& g, int init, int k, hipStream_t s);
 hipError_t launch_group_update(const CgGroup& g, int k, hipStream_t s);
 // Outer iteration of each problem of a grouped launch (at most kGroupIts of them).
 constexpr int kGroupIts = 64;

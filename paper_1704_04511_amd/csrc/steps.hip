@@ -607,12 +607,11 @@ static slrx_status cg_body(slrx_plan* pl, int n_cg) {
   const slrx_dims& d = pl->d;
   const long V = (long)pl->vol();
   const int nfin = fin_blocks(d.P, d.T);
-  const int nupd = update_blocks(V);
   STCHK(apply_op(pl, pl->x, pl->r, true, pl->partA));
   for (int k = 0; k < n_cg; ++k) {
     RowArgs ra{};
     ra.P = d.P; ra.Q = d.Q; ra.T = d.T;
-    ra.mode = ROW_PUPDATE;
+    ra.mode = k == 0 ? ROW_START : ROW_STEP;
     ra.sign = +1;
     ra.src = pl->r;
     ra.pvec = pl->p;
@@ -620,9 +619,14 @@ static slrx_status cg_body(slrx_plan* pl, int n_cg) {
     ra.scale = 1.0f;
     ra.tw = pl->twQf;
     ra.k = k;
-    ra.part = k == 0 ? pl->partA : pl->partB;
-    ra.npart = k == 0 ? nfin : nupd;
+    ra.part = pl->partA;
+    ra.npart = nfin;
     ra.rr_hist = pl->rr_hist;
+    ra.x = pl->x;
+    ra.r = pl->r;
+    ra.q = pl->q;
+    ra.part_rr = pl->partB;
+    ra.flag = pl->flag;
     {
       KTimer kt(pl, SLRX_K_ROWS);
       HIPCHK(launch_rows(ra, pl->stream));
@@ -644,6 +648,12 @@ static slrx_status cg_body(slrx_plan* pl, int n_cg) {
     fa.y = pl->bm;
     fa.out = pl->q;
     fa.part = pl->partA;
+    fa.r = pl->r;
+    if (k > 0) {
+      fa.part_rr = pl->partB;
+      fa.npart_rr = nfin;
+      fa.rr = pl->rr_hist + k;
+    }
     fa.flag = pl->flag;
     fa.tw = pl->twQf;
     fin_coil(pl, fa);
@@ -651,6 +661,8 @@ static slrx_status cg_body(slrx_plan* pl, int n_cg) {
       KTimer kt(pl, SLRX_K_FIN);
       HIPCHK(launch_fin(fa, pl->stream));
     }
+  }
+  if (n_cg > 0) {  // the last iteration's x, r and <r, r>
     UpdArgs ua{};
     ua.n = V;
     ua.x = pl->x;
@@ -660,7 +672,7 @@ static slrx_status cg_body(slrx_plan* pl, int n_cg) {
     ua.partA = pl->partA;
     ua.nA = nfin;
     ua.rr_hist = pl->rr_hist;
-    ua.k = k;
+    ua.k = n_cg - 1;
     ua.partB = pl->partB;
     ua.flag = pl->flag;
     {
