@@ -9,10 +9,11 @@
 // T(0:i, i) = -tau_i T(0:i, 0:i) V(:, 0:i)^H v_i).  With Y = V T the block acts
 // on Z as Z <- Z - Y (V^H Z), and Q Z applies the blocks from the last to the
 // first.  Every product is a complex FP64 matrix product on the f64 16x16x4
-// MFMA: output tiles of 64 x 16 (one 16 x 16 tile per wave), K staged through
-// LDS in chunks of 16; long reductions are split over workgroups into partial
-// results that the consumer sums in a fixed order (results are reproducible
-// bit for bit).
+// MFMA.  k_bt_apply applies every block to eight columns of Z held in LDS; the
+// products within the blocks, and sizes whose columns do not fit, take output tiles of
+// 64 x 16 (one 16 x 16 tile per wave), K staged through LDS in chunks of 16; long
+// reductions are split over workgroups into partial results that the consumer sums
+// in a fixed order (results are reproducible bit for bit).
 #include "common.h"
 #include "kernels.h"
 
@@ -285,6 +286,130 @@ __global__ __launch_bounds__(kTmatThreads) void k_bt_tmat(BtArgs a0) {
   }
 }
 
+// Every block applied to eight columns of Z by one workgroup: Z(:, c0 .. c0+7) stays in
+// LDS as rows [re of 8 | im of 8], the 16 columns of a real operand, so a complex product is
+// two MFMAs, [Vr^T Z | Vi^T Z], whose halves are combined across lanes.  The columns of Z
+// are independent, so one launch does what took three per block of 64 reflectors (54 at
+// n = 1125), each with too little work for the chip.
+// Per block: W = V^H Z, a wave per 16 reflectors and half of the rows; then Z -= Y W, a wave
+// per 16 rows in turn.  Bound by the FP64 matrix cores of the ceil(n / 8) CUs at work (280 us
+// of its 468 at n = 1125), the panels' loads running ahead of them: the whole
+// back-transformation takes 717 -> 542 us at n = 1125, 183 -> 132 at 405, 63 -> 49 at 75.
+constexpr int kApNT = 512;
+constexpr int kApCols = 8;
+static size_t bt_apply_lds(int n) { return ((size_t)(n + 1) * 16 + 2 * kBtNb * 16) * sizeof(double); }
+constexpr size_t kApLds = 160 * 1024;
+
+// The value of lane ^ 8 (within rows of 16 lanes).
+SLRX_DEV double swap8(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x128, 0xf, 0xf, false);  // row_ror:8
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x128, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+__global__ __launch_bounds__(kApNT) void k_bt_apply(BtArgs a0) {
+  extern __shared__ double zl[];  // [n + 1][16], row n zero, then W [2][kBtNb][16]
+  const BtArgs a = bt_at(a0, blockIdx.y);
+  const int n = a.n, c0 = kApCols * blockIdx.x, nc = min(kApCols, n - c0);
+  double* W = zl + (size_t)(n + 1) * 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = lane & 15, q = lane >> 4;  // column (or row) and k of the MFMA operands
+  const double2 zero = make_double2(0.0, 0.0);
+  const v4d vzero = v4d{0.0, 0.0, 0.0, 0.0};
+  for (int e = tid; e < kApCols * (n + 8); e += kApNT) {  // 8 rows of 8 columns per wave
+    const int c = e / 8 % kApCols, r = e / 64 * 8 + e % 8;
+    const double2 v = c < nc && r < n ? a.Z[(long)(c0 + c) * n + r] : zero;
+    if (r <= n) {
+      zl[r * 16 + c] = v.x;
+      zl[r * 16 + kApCols + c] = v.y;
+    }
+  }
+  __syncthreads();
+  for (int g = a.ng - 1; g >= 0; --g) {
+    const int k0 = kBtNb * g, r0 = k0 + 1, m = n - r0, nr = min(kBtNb, n - 1 - k0);
+    // Loads are clamped instead of masked (no branch between a load and its use): rows from
+    // m on meet the zero row of Z or results that are not stored, columns from nr on zero rows of W.
+    {  // W = V^H Z: reflectors 16 tile + j, rows kb .. ke-1 of the block
+      const int tile = wave & 3, half = wave >> 2;
+      const int mh = (m + 95) / 96 * 48, kb = half * mh, ke = min(m, kb + mh);
+      const double2* vc = a.Vx + (long)(k0 + min(16 * tile + j, nr - 1)) * n + r0;
+      auto fetch = [&](double2 (&x)[4], int kc) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = vc[min(kc + 4 * u + q, m - 1)];
+      };
+      v4d P1 = vzero, P2 = vzero;
+      auto product = [&](const double2 (&x)[4], int kc) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double b = zl[min(r0 + kc + 4 * u + q, n) * 16 + j];
+          P1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u].x, b, P1, 0, 0, 0);
+          P2 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u].y, b, P2, 0, 0, 0);
+        }
+      };
+      double2 x0[4], x1[4], x2[4];
+      fetch(x0, kb);
+      fetch(x1, kb + 16);
+      for (int kc = kb; kc < ke; kc += 48) {
+        fetch(x2, kc + 32);
+        product(x0, kc);
+        fetch(x0, kc + 48);
+        product(x1, kc + 16);
+        fetch(x1, kc + 64);
+        product(x2, kc + 32);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {  // Re: Vr Zr + Vi Zi, Im: Vr Zi - Vi Zr
+        const double o = swap8(P2[v]);
+        W[(half * kBtNb + 16 * tile + q + 4 * v) * 16 + j] = j < kApCols ? P1[v] + o : P1[v] - o;
+      }
+    }
+    // Z -= Y W: rows i0 .. i0+15, columns 4 u + q of Y, u in halves H
+    constexpr int kH = kBtNb / 8, kStep = 16 * (kApNT / 64);
+    auto fetch = [&](double2 (&y)[kH], int i0, int h) {
+      const double2* yr = a.Yx + (long)k0 * n + r0 + min(i0 + j, m - 1);
+#pragma unroll
+      for (int u = 0; u < kH; ++u) y[u] = yr[min(4 * (kH * h + u) + q, nr - 1) * n];
+    };
+    double2 y0[kH], y1[kH];
+    fetch(y0, 16 * wave, 0);
+    __syncthreads();
+    double w[kBtNb / 4];
+#pragma unroll
+    for (int u = 0; u < kBtNb / 4; ++u)
+      w[u] = W[(4 * u + q) * 16 + j] + W[(kBtNb + 4 * u + q) * 16 + j];
+    if (nr < kBtNb) {
+#pragma unroll
+      for (int u = 0; u < kBtNb / 4; ++u)
+        if (4 * u + q >= nr) w[u] = 0.0;
+    }
+    for (int i0 = 16 * wave; i0 < m; i0 += kStep) {
+      v4d P1 = vzero, P2 = vzero;
+      auto product = [&](const double2 (&y)[kH], int h) {
+#pragma unroll
+        for (int u = 0; u < kH; ++u) {
+          P1 = __builtin_amdgcn_mfma_f64_16x16x4f64(y[u].x, w[kH * h + u], P1, 0, 0, 0);
+          P2 = __builtin_amdgcn_mfma_f64_16x16x4f64(y[u].y, w[kH * h + u], P2, 0, 0, 0);
+        }
+      };
+      fetch(y1, i0, 1);
+      product(y0, 0);
+      fetch(y0, i0 + kStep, 0);
+      product(y1, 1);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {  // Re: Yr Wr - Yi Wi, Im: Yr Wi + Yi Wr
+        const double o = swap8(P2[v]);
+        if (i0 + q + 4 * v < m) zl[(r0 + i0 + q + 4 * v) * 16 + j] -= j < kApCols ? P1[v] - o : P1[v] + o;
+      }
+    }
+    __syncthreads();
+  }
+  for (int e = tid; e < kApCols * (n + 7); e += kApNT) {
+    const int c = e / 8 % kApCols, r = e / 64 * 8 + e % 8;
+    if (c < nc && r < n) a.Z[(long)(c0 + c) * n + r] = make_double2(zl[r * 16 + c], zl[r * 16 + kApCols + c]);
+  }
+}
+
 }  // namespace
 
 static int bt_nblocks(int n) { return n > 1 ? (n - 2) / kBtNb + 1 : 0; }
@@ -319,6 +444,13 @@ hipError_t launch_backtransform(const BackTrArgs& b, hipStream_t s) {
   k_bt_tmat<<<dim3(ng, nb), kTmatThreads, 0, s>>>(a);
   a.nsplit = 1;
   k_bt_gemm<BT_YMAT><<<dim3(kBtNb / kTN, mt, nb * ng), 256, 0, s>>>(a, ng);
+  if (bt_apply_lds(n) <= kApLds) {  // n <= 1151: the columns of Z fit a workgroup's LDS
+    static LdsLimit lim;
+    const hipError_t e = lim.ensure((const void*)k_bt_apply, kApLds);
+    if (e != hipSuccess) return e;
+    k_bt_apply<<<dim3((n + kApCols - 1) / kApCols, nb), kApNT, bt_apply_lds(n), s>>>(a);
+    return hipGetLastError();
+  }
   const int nt = (n + kTN - 1) / kTN;
   a.nsplit = kBtSplitW;
   for (int g = ng - 1; g >= 0; --g) {
