@@ -449,33 +449,52 @@ SLRX_DEV double quad_prod(double v) {
   return v;
 }
 
+// 1 / d by Newton's iteration from the hardware's estimate, within an ulp for finite d
+// whose reciprocal is normal (the divider's scaling steps are twice as long a chain).
+SLRX_DEV double recip(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return fma(r, fma(-d, r, 1.0), r);
+}
+
 // Terms of f = 1 + psi + phi at offset tau from the origin pole, over a group of
-// G lanes: psi sums the poles at or left of d_j, phi the poles right of it
-// (values and derivatives), fa the magnitudes (rounding bound of f).
+// G lanes: psi sums the poles at or left of d_j (terms <= 0), phi the poles right of
+// it (terms >= 0), values and derivatives; fa the magnitudes (rounding bound of f).
 struct SecTerms {
   double psi, dpsi, phi, dphi, fa;
 };
 template <int G>
 SLRX_DEV SecTerms secular(const double* dl, const double* z2, int k, int j, double dor, double rho, double tau) {
-  double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int i = threadIdx.x & (G - 1); i < k; i += G) {
-    const double r = 1.0 / ((dl[i] - dor) - tau);
-    const double w = z2[i] * r;
-    if (i <= j) {
-      v[0] += w;
-      v[1] += w * r;
-    } else {
-      v[2] += w;
-      v[3] += w * r;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  // a quad takes four terms at a time (the last ones padded by zero couplings): their chains
+  // overlap; a wave has one or a few
+  constexpr int N = G == 4 ? 4 : 1;
+  for (int i0 = threadIdx.x & (G - 1); i0 < k; i0 += N * G) {
+    double p[N], z[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = min(i0 + u * G, k - 1);
+      p[u] = dl[i];
+      z[u] = z2[i];
     }
-    v[4] += fabs(w);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = i0 + u * G;
+      const double r = recip((p[u] - dor) - tau);
+      const double w = (i < k ? z[u] : 0.0) * r, wr = w * r;
+      const bool left = i <= j;
+      v[0] += left ? w : 0.0;
+      v[1] += left ? wr : 0.0;
+      v[2] += left ? 0.0 : w;
+      v[3] += left ? 0.0 : wr;
+    }
   }
   SecTerms t;
   t.psi = rho * group_sum<G>(v[0]);
   t.dpsi = rho * group_sum<G>(v[1]);
   t.phi = rho * group_sum<G>(v[2]);
   t.dphi = rho * group_sum<G>(v[3]);
-  t.fa = rho * group_sum<G>(v[4]);
+  t.fa = t.phi - t.psi;
   return t;
 }
 
@@ -499,9 +518,10 @@ SLRX_DEV void secular_root(const double* dl, const double* z2, int k, int j, dou
   const bool last = j == k - 1;
   int o;
   double sign, hiv;
+  SecTerms t;
   if (!last) {
     const double gap = dl[j + 1] - dl[j];
-    const SecTerms t = secular<G>(dl, z2, k, j, dl[j], rho, 0.5 * gap);
+    t = secular<G>(dl, z2, k, j, dl[j], rho, 0.5 * gap);
     if (1.0 + t.psi + t.phi >= 0.0) {
       o = j;
       sign = 1.0;
@@ -524,7 +544,7 @@ SLRX_DEV void secular_root(const double* dl, const double* z2, int k, int j, dou
   double x = sign * hiv;  // the midpoint (the far end for the last root)
   double prev_step = 1e300, fprev = 0.0;
   for (int it = 0; it < 200; ++it) {
-    const SecTerms t = secular<G>(dl, z2, k, j, dor, rho, x);
+    if (it > 0 || last) t = secular<G>(dl, z2, k, j, dor, rho, x);  // the midpoint's terms are known
     const double f = 1.0 + t.psi + t.phi;
     if (fabs(f) <= 4.0 * __DBL_EPSILON__ * (1.0 + t.fa)) break;
     if (f < 0.0) lo = x;
@@ -534,43 +554,44 @@ SLRX_DEV void secular_root(const double* dl, const double* z2, int k, int j, dou
     if (nb <= 1) break;
     double xn = 0.0;
     bool ok = false;
-    const double S = t.dpsi * (pa - x) * (pa - x);
+    const double da = pa - x, db = pb - x, ra = recip(da), rb = recip(db);
+    const double S = t.dpsi * da * da;
     if (last) {
-      const double c = f - S / (pa - x);
+      const double c = f - S * ra;
       if (c > 0.0) {
-        xn = pa + S / c;
+        xn = pa + S * recip(c);
         ok = true;
       }
     } else {
       // When the last step cut |f| by less than 10x (a root close to a pole whose
       // coupling is tiny: the curvature of the other poles is then fitted onto it),
       // the nearer pole keeps its exact weight and the rest of f' goes to the other.
-      double Sm = S, T = t.dphi * (pb - x) * (pb - x);
+      double Sm = S, T = t.dphi * db * db;
       if (it > 0 && fabs(f) > 0.1 * fabs(fprev)) {
         const double fp = t.dpsi + t.dphi;
         if (o == j) {
           Sm = rho * z2[j];
-          T = (fp - Sm / ((pa - x) * (pa - x))) * (pb - x) * (pb - x);
+          T = (fp - Sm * ra * ra) * db * db;
         } else {
           T = rho * z2[j + 1];
-          Sm = (fp - T / ((pb - x) * (pb - x))) * (pa - x) * (pa - x);
+          Sm = (fp - T * rb * rb) * da * da;
         }
       }
-      const double c = f - Sm / (pa - x) - T / (pb - x);
+      const double c = f - Sm * ra - T * rb;
       // c (pa - y)(pb - y) + S (pb - y) + T (pa - y) = 0
       const double qa = c, qb = -(c * (pa + pb) + Sm + T), qc = c * pa * pb + Sm * pb + T * pa;
       const double disc = qb * qb - 4.0 * qa * qc;
       if (disc >= 0.0) {
         const double q = -0.5 * (qb + copysign(sqrt(disc), qb));
         if (qa != 0.0) {
-          const double y = q / qa;
+          const double y = q * recip(qa);
           if (y > lo && y < hi) {
             xn = y;
             ok = true;
           }
         }
         if (q != 0.0) {
-          const double y = qc / q;
+          const double y = qc * recip(q);
           if (y > lo && y < hi) {
             xn = y;
             ok = true;
@@ -775,7 +796,7 @@ struct LeafLds {
   double zsign[kLeafN];           // the kept couplings (their signs)
   double rc[kLeafN], rs[kLeafN], tau[kLeafN], zh[kLeafN];
   int perm[kLeafN], order[kLeafN], flag[kLeafN], ki[kLeafN], rec[kLeafN], rp[kLeafN], rq[kLeafN], orig[kLeafN];
-  int node[kLeafN];               // node of every entry at this level
+  int node[kLeafN], ns[kLeafN], nm[kLeafN];  // every entry's node at this level, its start and size
   int k[kLeafN / kLeafBase], nrot[kLeafN / kLeafBase];
 };
 
@@ -821,6 +842,8 @@ SLRX_DEV void leaf_deflate(LeafLds& L, const double* Q, int q, int s, int m) {
     L.ds[s + r] = d;
     L.zs[s + r] = z;
     L.node[s + t] = q;
+    L.ns[s + t] = s;
+    L.nm[s + t] = m;
   }
   const double mx = wave_max(fmax(fabs(d), fabs(z)));
   const double tol = 8.0 * __DBL_EPSILON__ * mx;
@@ -938,56 +961,105 @@ SLRX_DEV void leaf_deflate(LeafLds& L, const double* Q, int q, int s, int m) {
   }
 }
 
+// (r, 1 / r) of r = sqrt(x^2 + y^2): Goldschmidt's iteration from the hardware's estimate
+// in the middle of the exponent range, each ending with a residual correction.
+SLRX_DEV void norm2(double x, double y, double& r, double& inv) {
+  const double N = fma(x, x, y * y);
+  if (N > 0x1p-900 && N < 0x1p900) {
+    const double e0 = __builtin_amdgcn_rsq(N);
+    double g = N * e0, h = 0.5 * e0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const double d = fma(-h, g, 0.5);
+      g = fma(g, d, g);
+      h = fma(h, d, h);
+    }
+    r = fma(fma(-g, g, N), h, g);
+    inv = h + h;
+    inv = fma(inv, fma(-r, inv, 1.0), inv);
+  } else {
+    r = hypot(x, y);
+    inv = 1.0 / r;
+  }
+}
+
 // Eigenpairs of the m <= kLeafBase entries from s on by implicit QR steps with
 // Wilkinson's shift (Golub and Van Loan, Matrix Computations, 8.3), by eight lanes: every
-// lane carries the same tridiagonal (d in L.D, its couplings in L.zs) and rotates its own
-// row of Q.  A coupling within rounding of its block counts as zero (the criterion of the
-// merges' deflation); the step count is bounded.
-SLRX_DEV void leaf_base(LeafLds& L, double* Q, int s, int m, int row) {
-  double* d = L.D + s;
-  double* e = L.zs + s;
-  double* z = Q + (s + row) * kLeafLd + s;
-  double anorm = 0.0;
-  for (int i = 0; i < m; ++i) {
-    e[i] = L.E[s + i];
-    anorm = fmax(anorm, fmax(fabs(d[i]), i < m - 1 ? fabs(L.E[s + i]) : 0.0));
-  }
-  int hi = m - 1;
-  for (int step = 0; hi > 0 && step < 40 * kLeafBase; ++step) {
-    auto small = [&](int k) {
-      return fabs(e[k]) <= __DBL_EPSILON__ * fmax(0.5 * anorm, fabs(d[k]) + fabs(d[k + 1]));
-    };
-    if (small(hi - 1)) {
-      --hi;
-      continue;
-    }
-    int lo = hi - 1;
-    while (lo > 0 && !small(lo - 1)) --lo;
-    // the eigenvalue of the trailing 2 x 2 block nearer to d[hi]
-    const double eh = e[hi - 1], del = 0.5 * (d[hi - 1] - d[hi]);
-    const double root = hypot(del, eh);
-    const double mu = d[hi] - eh * (eh / (del + copysign(root, del)));
-    double x = d[lo] - mu, y = e[lo];
-    for (int k = lo; k < hi; ++k) {
-      const double r = hypot(x, y);
-      const double c = r > 0.0 ? x / r : 1.0, t = r > 0.0 ? y / r : 0.0;
-      if (k > lo) e[k - 1] = r;
-      const double d0 = d[k], d1 = d[k + 1], ek = e[k];
+// lane carries the same tridiagonal and rotates its own row of Q, all in registers (indices
+// known at compile time; a rotation is a serial chain, and with the tridiagonal in LDS, hypot
+// and two divisions it took 1800 cycles: 92000 -> 49000 for the 6 and 7 entries of s = 405).
+// A coupling within rounding of its block counts as zero (the criterion of the merges'
+// deflation); the step count is bounded.
+struct LeafBase {
+  double d[kLeafBase], e[kLeafBase], z[kLeafBase];  // diagonal, couplings, row of Q
+  double anorm;
+  int m, step;
+};
+template <int HI>
+SLRX_DEV void leaf_base_steps(LeafBase& b) {
+  auto small = [&](int k) {
+    return fabs(b.e[k]) <= __DBL_EPSILON__ * fmax(0.5 * b.anorm, fabs(b.d[k]) + fabs(b.d[k + 1]));
+  };
+  while (HI < b.m && b.step < 40 * kLeafBase && !small(HI - 1)) {
+    ++b.step;
+    bool act[HI];  // couplings of the unreduced block that ends at HI
+    act[HI - 1] = true;
+#pragma unroll
+    for (int k = HI - 2; k >= 0; --k) act[k] = act[k + 1] && !small(k);
+    // the eigenvalue of the trailing 2 x 2 block nearer to d[HI]
+    const double eh = b.e[HI - 1], del = 0.5 * (b.d[HI - 1] - b.d[HI]);
+    double root, inv;
+    norm2(del, eh, root, inv);
+    const double mu = b.d[HI] - eh * (eh / (del + copysign(root, del)));
+    double x = 0.0, y = 0.0;
+#pragma unroll
+    for (int k = 0; k < HI; ++k) {
+      if (!act[k]) continue;
+      const bool first = k == 0 || !act[k > 0 ? k - 1 : 0];
+      if (first) {
+        x = b.d[k] - mu;
+        y = b.e[k];
+      }
+      double r;
+      norm2(x, y, r, inv);
+      const double c = r > 0.0 ? x * inv : 1.0, t = r > 0.0 ? y * inv : 0.0;
+      if (k > 0 && !first) b.e[k > 0 ? k - 1 : 0] = r;
+      const double d0 = b.d[k], d1 = b.d[k + 1], ek = b.e[k];
       const double g = 2.0 * c * t * ek;
-      d[k] = c * c * d0 + g + t * t * d1;
-      d[k + 1] = t * t * d0 - g + c * c * d1;
+      b.d[k] = c * c * d0 + g + t * t * d1;
+      b.d[k + 1] = t * t * d0 - g + c * c * d1;
       const double en = c * t * (d1 - d0) + (c - t) * (c + t) * ek;
-      e[k] = en;
-      if (k < hi - 1) {
+      b.e[k] = en;
+      if (k < HI - 1) {
         x = en;
-        y = t * e[k + 1];
-        e[k + 1] = c * e[k + 1];
+        y = t * b.e[k + 1];
+        b.e[k + 1] = c * b.e[k + 1];
       }
-      if (row < m) {
-        const double z0 = z[k], z1 = z[k + 1];
-        z[k] = c * z0 + t * z1;
-        z[k + 1] = c * z1 - t * z0;
-      }
+      const double z0 = b.z[k], z1 = b.z[k + 1];
+      b.z[k] = c * z0 + t * z1;
+      b.z[k + 1] = c * z1 - t * z0;
+    }
+  }
+  if constexpr (HI > 1) leaf_base_steps<HI - 1>(b);
+}
+SLRX_DEV void leaf_base(LeafLds& L, double* Q, int s, int m, int row) {
+  LeafBase b;
+  b.anorm = 0.0;
+  b.m = m;
+  b.step = 0;
+#pragma unroll
+  for (int i = 0; i < kLeafBase; ++i) {
+    b.d[i] = i < m ? L.D[s + i] : 0.0;
+    b.e[i] = i < m - 1 ? L.E[s + i] : 0.0;
+    b.z[i] = i == row ? 1.0 : 0.0;
+    b.anorm = fmax(b.anorm, fmax(fabs(b.d[i]), fabs(b.e[i])));
+  }
+  leaf_base_steps<kLeafBase - 1>(b);
+  if (row < m) {
+#pragma unroll
+    for (int i = 0; i < kLeafBase; ++i) {
+      if (i < m) Q[(s + row) * kLeafLd + s + i] = b.z[i];
+      if (i == row) L.D[s + i] = b.d[i];
     }
   }
 }
@@ -1041,22 +1113,30 @@ __global__ __launch_bounds__(kLeafNT) void k_dc_leaf(DcArgs a0, int depth) {
       leaf_deflate(L, Q, q, s, m);
     }
     __syncthreads();
-    // sorted columns of diag(Q1, Q2), a wave per row
-    for (int r = wave; r < M; r += kWaves) {
-      int s, m;
-      leaf_node(M, dep, L.node[r], s, m);
-      const int n1 = m / 2;
-      if (lane < m) {
-        const int col = L.perm[s + lane];
-        Qn[r * kLeafLd + s + lane] = (r - s < n1) == (col < n1) ? Q[r * kLeafLd + s + col] : 0.0;
+    // sorted columns of diag(Q1, Q2): a wave per row, four rows' loads in flight
+    for (int r0 = wave; r0 < M; r0 += 4 * kWaves) {
+      double x[4];
+      int at[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = min(r0 + u * kWaves, M - 1);
+        const int s = L.ns[r], m = L.nm[r];
+        const int n1 = m / 2, col = L.perm[s + min(lane, m - 1)];
+        const double v = Q[r * kLeafLd + s + col];
+        x[u] = (r - s < n1) == (col < n1) ? v : 0.0;
+        at[u] = lane < m ? r * kLeafLd + s + lane : -1;
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (at[u] >= 0) Qn[at[u]] = x[u];
     }
     // this level's node of column (tid / 4) for the roots
     const int g = tid >> 2, gl = tid & 3;
     int gs = 0, gm = 0, gk = 0;
     double rho = 0.0;
     if (g < M) {
-      leaf_node(M, dep, L.node[g], gs, gm);
+      gs = L.ns[g];
+      gm = L.nm[g];
       gk = L.k[L.node[g]];
       rho = 2.0 * fabs(L.E[gs + gm / 2 - 1]);
     }
@@ -1074,9 +1154,7 @@ __global__ __launch_bounds__(kLeafNT) void k_dc_leaf(DcArgs a0, int depth) {
     }
     __syncthreads();
     if (tid < M) {  // deflation rotations of row tid
-      const int q = L.node[tid];
-      int s, m;
-      leaf_node(M, dep, q, s, m);
+      const int q = L.node[tid], s = L.ns[tid];
       double* row = Qn + tid * kLeafLd + s;
       for (int e = 0; e < L.nrot[q]; ++e) {
         const int p0 = L.rp[s + e], p1 = L.rq[s + e];
@@ -1097,10 +1175,19 @@ __global__ __launch_bounds__(kLeafNT) void k_dc_leaf(DcArgs a0, int depth) {
       if (gl == 0) L.zh[g] = copysign(sqrt(fmax(p, 0.0)), L.zsign[g]);
     }
     __syncthreads();
-    for (int r = wave; r < M; r += kWaves) {  // final column order, back into Q
-      int s, m;
-      leaf_node(M, dep, L.node[r], s, m);
-      if (lane < m) Q[r * kLeafLd + s + lane] = Qn[r * kLeafLd + s + L.order[s + lane]];
+    for (int r0 = wave; r0 < M; r0 += 4 * kWaves) {  // final column order, back into Q
+      double x[4];
+      int at[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = min(r0 + u * kWaves, M - 1);
+        const int s = L.ns[r], m = L.nm[r];
+        x[u] = Qn[r * kLeafLd + s + L.order[s + min(lane, m - 1)]];
+        at[u] = lane < m ? r * kLeafLd + s + lane : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (at[u] >= 0) Q[at[u]] = x[u];
     }
     if (root) {  // vectors of the merge
       const double dor = L.dl[gs + L.orig[g]], tau = L.tau[g];
@@ -1115,28 +1202,38 @@ __global__ __launch_bounds__(kLeafNT) void k_dc_leaf(DcArgs a0, int depth) {
       for (int i = gl; i < gk; i += 4) u[i] *= sc;
     }
     __syncthreads();
-    // Q_node(:, 0:k) = Q(:, 0:k) U, the deflated columns copied: 16 x 16 tiles over the waves
+    // Q_node(:, 0:k) = Q(:, 0:k) U, the deflated columns copied: a wave per 16 rows, their
+    // (at most four) tiles of 16 columns together.  Indices are clamped: terms beyond k are
+    // zero in Q's operand, rows beyond m and columns beyond k are not taken from the product.
     int job = 0;
     for (int q = 0; q < nodes; ++q) {
       int s, m;
       leaf_node(M, dep, q, s, m);
       const int k = L.k[q], nt = (m + 15) / 16;
-      for (int t = 0; t < nt * nt; ++t, ++job) {
+      for (int t = 0; t < nt; ++t, ++job) {
         if (job % kWaves != wave) continue;
-        const int i0 = t / nt * 16, j0 = t % nt * 16;
         const int l = lane & 15, h = lane >> 4;
-        v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+        const double* Qr = Q + (s + min(16 * t + l, m - 1)) * kLeafLd + s;
+        v4d acc[kLeafN / 16];
+#pragma unroll
+        for (int c = 0; c < kLeafN / 16; ++c) acc[c] = v4d{0.0, 0.0, 0.0, 0.0};
         for (int kq = 0; kq < k; kq += 4) {
-          const int kk = kq + h;
-          const double av = i0 + l < m && kk < k ? Q[(s + i0 + l) * kLeafLd + s + kk] : 0.0;
-          const double bv = j0 + l < k && kk < k ? L.U[(s + j0 + l) * kLeafLd + s + kk] : 0.0;
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+          const int kk = min(kq + h, k - 1);
+          const double qv = Qr[kk], av = kq + h < k ? qv : 0.0;
+#pragma unroll
+          for (int c = 0; c < kLeafN / 16; ++c)
+            if (c < nt)
+              acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, L.U[(s + min(16 * c + l, k - 1)) * kLeafLd + s + kk],
+                                                            acc[c], 0, 0, 0);
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = i0 + h + 4 * v, c = j0 + l;
-          if (r < m && c < m) Qn[(s + r) * kLeafLd + s + c] = c < k ? acc[v] : Q[(s + r) * kLeafLd + s + c];
-        }
+        for (int c = 0; c < kLeafN / 16; ++c)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int r = 16 * t + h + 4 * v, col = 16 * c + l;
+            if (r < m && col < m)
+              Qn[(s + r) * kLeafLd + s + col] = col < k ? acc[c][v] : Q[(s + r) * kLeafLd + s + col];
+          }
       }
     }
     cur ^= 1;
