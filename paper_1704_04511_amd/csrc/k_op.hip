@@ -204,7 +204,8 @@ SLRX_DEV void cols_pen_body(const PenArgs& a, const Blk& b, float2* lds, float2*
   const long fs = (long)P * Q;
   fft_twiddles<N, kPenNT>(twt, a.tw);
   const int per_t = CB * BS;  // LDS stride of a frame
-  const int pix = threadIdx.x & 255, h = threadIdx.x >> 8;  // CB * N <= 256 pixels
+  const int pix = threadIdx.x & 255;  // CB * N <= 256 pixels
+  const int h = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   const bool has_pix = pix < CB * N;
   const int pl = (pix / N) * BS + fft_pidx(pix % N);  // the pixel's slot in a frame
   const long po = (long)c0 * P + pix;  // pixel (row pix % N, column c0 + pix / N) in a frame
@@ -245,7 +246,6 @@ SLRX_DEV void cols_pen_body(const PenArgs& a, const Blk& b, float2* lds, float2*
     return make_float2(acc.x + c.x * x.x - c.y * x.y, acc.y + c.x * x.y + c.y * x.x);
   };
   auto E = [&](int m, int mp) { return (m <= mp) ? e[pair_id(m, mp, M)] : cconj(e[pair_id(mp, m, M)]); };
-  float2 rho[kTMax], rt[ME];  // rt[i] = rho_{T-1-i}
   // GIRAF: every window is complete and G is circulant along the frames,
   // (G rho)_t = sum_{d=-(M-1)}^{M-1} g_d rho_{(t+d) mod T}, g_{-d} = u_d, g_d = conj(u_d);
   // outputs of parity h kept in registers until every input is read
@@ -275,19 +275,44 @@ SLRX_DEV void cols_pen_body(const PenArgs& a, const Blk& b, float2* lds, float2*
       gout[i] = cscale(acc, sc);
     }
   }
+  // Outputs of parity h wait in registers until every input is read: gout[i] frame 2 i + h,
+  // glast[q] frame T - 1 - q.  Inputs come from LDS through a window of 2M - 1 frames: with
+  // all kTMax of them in registers one workgroup filled a CU (176 registers a thread, 218 in
+  // the grouped pass), and loads, transforms and stores took turns: the grouped pass of 32
+  // problems of 96 to 256 rows takes 189 -> 121 us, 64 x 64 x 8 alone 8.2 -> 7.3 us.
+  float2 glast[M > 1 ? M - 1 : 1];
   if (split && has_pix) {
+    const float2* x = lds + pl;
+    if (M > 1) {
+      // first frames t < M-1: n = t + m for m >= M-1-t
+      float2 rho[ME];
 #pragma unroll
-    for (int t = 0; t < kTMax; ++t) rho[t] = t < T ? lds[t * per_t + pl] : make_float2(0.f, 0.f);
+      for (int i = 0; i < ME; ++i) rho[i] = x[i * per_t];
 #pragma unroll
-    for (int i = 0; i < ME; ++i) rt[i] = lds[(T - 1 - i) * per_t + pl];
-  }
-  __syncthreads();  // every input read before any output is written in place
-  if (circ && has_pix) {
+      for (int t = 0; t < M - 1; ++t) {
+        if ((t & 1) != h) continue;
+        float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int i = 0; i < kTMax / 2; ++i)
-      if (2 * i + h < T) lds[(2 * i + h) * per_t + pl] = gout[i];
-  }
-  if (split && has_pix) {
+        for (int m = M - 1 - t; m < M; ++m)
+#pragma unroll
+          for (int mp = 0; mp < M; ++mp) acc = mac(acc, E(m, mp), rho[t + m - mp]);
+        gout[t / 2] = cscale(acc, sc);
+      }
+      // last frames t = T-1-q, q < M-1: n = t + m for m <= q; rho_{t+m-m'} = rt[q-m+m']
+#pragma unroll
+      for (int i = 0; i < ME; ++i) rho[i] = x[(T - 1 - i) * per_t];
+#pragma unroll
+      for (int q = 0; q < M - 1; ++q) {
+        if (((T - 1 - q) & 1) != h) continue;
+        float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int m = 0; m <= q; ++m)
+#pragma unroll
+          for (int mp = 0; mp < M; ++mp) acc = mac(acc, E(m, mp), rho[q - m + mp]);
+        glast[q] = cscale(acc, sc);
+      }
+    }
+    // Toeplitz part
     float2 u[M];
 #pragma unroll
     for (int d = 0; d < M; ++d) {
@@ -296,41 +321,43 @@ SLRX_DEV void cols_pen_body(const PenArgs& a, const Blk& b, float2* lds, float2*
       for (int m = 1; m + d < M; ++m) s = cadd(s, e[pair_id(m, m + d, M)]);
       u[d] = s;
     }
-    // first frames t < M-1: n = t + m for m >= M-1-t
+    constexpr int I0 = (M - 1) / 2;  // first i with 2 i + 1 >= M - 1
+    float2 win[2 * M - 1];           // frames t - (M - 1) .. t + M - 1
 #pragma unroll
-    for (int t = 0; t < M - 1; ++t) {
-      if ((t & 1) != h) continue;
-      float2 acc = make_float2(0.f, 0.f);
+    for (int i = 0; i < 2 * M - 1; ++i) win[i] = x[max(0, min(T - 1, 2 * I0 + h - (M - 1) + i)) * per_t];
 #pragma unroll
-      for (int m = M - 1 - t; m < M; ++m)
+    for (int i = I0; i < kTMax / 2; ++i) {
+      const int t = 2 * i + h;
+      if (t > T - M) break;
+      if (t >= M - 1) {
+        float2 acc = mac(make_float2(0.f, 0.f), u[0], win[M - 1]);
 #pragma unroll
-        for (int mp = 0; mp < M; ++mp) acc = mac(acc, E(m, mp), rho[t + m - mp]);
-      lds[t * per_t + pl] = cscale(acc, sc);
-    }
-    // Toeplitz part
-#pragma unroll
-    for (int t = M - 1; t < kTMax; ++t) {
-      if (t > T - M || (t & 1) != h) continue;
-      float2 acc = mac(make_float2(0.f, 0.f), u[0], rho[t]);
-#pragma unroll
-      for (int d = 1; d < M; ++d) {
-        acc = mac(acc, u[d], rho[t - d]);
-        acc = mac(acc, cconj(u[d]), rho[t + d < kTMax ? t + d : kTMax - 1]);
+        for (int d = 1; d < M; ++d) {
+          acc = mac(acc, u[d], win[M - 1 - d]);
+          acc = mac(acc, cconj(u[d]), win[M - 1 + d]);
+        }
+        gout[i] = cscale(acc, sc);
       }
-      lds[t * per_t + pl] = cscale(acc, sc);
+#pragma unroll
+      for (int k = 0; k + 2 < 2 * M - 1; ++k) win[k] = win[k + 2];
+#pragma unroll
+      for (int k = M > 1 ? 2 * M - 3 : 0; k < 2 * M - 1; ++k)
+        win[k] = x[min(T - 1, t + 2 - (M - 1) + k) * per_t];
     }
-    // last frames t = T-1-q, q < M-1: n = t + m for m <= q; rho_{t+m-m'} = rt[q-m+m']
+  }
+  __syncthreads();  // every input read before any output is written in place
+  if (circ && has_pix) {
 #pragma unroll
-    for (int q = 0; q < M - 1; ++q) {
-      const int t = T - 1 - q;
-      if ((t & 1) != h) continue;
-      float2 acc = make_float2(0.f, 0.f);
+    for (int i = 0; i < kTMax / 2; ++i)
+      if (2 * i + h < T) lds[(2 * i + h) * per_t + pl] = gout[i];
+  }
+  if (split && has_pix) {
 #pragma unroll
-      for (int m = 0; m <= q; ++m)
+    for (int i = 0; i < kTMax / 2; ++i)
+      if (2 * i + h <= T - M) lds[(2 * i + h) * per_t + pl] = gout[i];
 #pragma unroll
-        for (int mp = 0; mp < M; ++mp) acc = mac(acc, E(m, mp), rt[q - m + mp]);
-      lds[t * per_t + pl] = cscale(acc, sc);
-    }
+    for (int q = 0; q < M - 1; ++q)
+      if (((T - 1 - q) & 1) == h) lds[(T - 1 - q) * per_t + pl] = glast[q];
   } else if (!circ && !split && has_pix && h == 0) {
     // windowed sum over n with a sliding register window: z[m] = rho_{n-m};
     // acc[m] collects output frame n - m, written once complete
@@ -677,8 +704,9 @@ __global__ __launch_bounds__(kNT) void k_group_rows(const CgSlice* tab, int ns, 
   SLRX_SWITCH_N(c.Q, rows_t_body<N_, +1>(a, b, lds, twt, red))
 }
 
+// Two workgroups per CU up to M = 5 (a few spilled registers cost less than half the waves).
 template <int M>
-__global__ __launch_bounds__(kPenNT) void k_group_pen(const CgSlice* tab, int ns) {
+__global__ __launch_bounds__(kPenNT, M <= 5 ? 4 : 2) void k_group_pen(const CgSlice* tab, int ns) {
   extern __shared__ float2 lds[];
   __shared__ float2 twt[kTwMax];
   const int gb = (int)blockIdx.x;
