@@ -32,13 +32,25 @@ void* g_scratch[kMaxDevices] = {};  // device address of `scratch` per device
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// e^{-2 pi i t / N} for t < N, rounded to complex64 (the FFT passes' table).
-__global__ void k_twiddles(float2* tw, int N) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= N) return;
-  double s, c;
-  sincospi(-2.0 * (double)t / (double)N, &s, &c);
-  tw[t] = make_float2((float)c, (float)s);
+// The call's tables in one launch (its smallest calls are bound by launches: six take 26 us
+// at 64 x 64 x 8, four 20): blocks 0 and 1 write the twiddles e^{-2 pi i t / N}, t < N, of the
+// two transform lengths (at most 256), rounded to complex64; the others transpose the masks
+// [W][P][Q] -> [W][Q][P].
+__global__ __launch_bounds__(256) void k_tables(float2* twP, int P, float2* twQ, int Q, int W, const float2* E,
+                                                float2* Et) {
+  if (blockIdx.x < 2) {
+    const int t = threadIdx.x, N = blockIdx.x == 0 ? P : Q;
+    if (t >= N) return;
+    double s, c;
+    sincospi(-2.0 * (double)t / (double)N, &s, &c);
+    (blockIdx.x == 0 ? twP : twQ)[t] = make_float2((float)c, (float)s);
+    return;
+  }
+  const long o = (long)(blockIdx.x - 2) * 256 + threadIdx.x, PQ = (long)P * Q;
+  if (o >= W * PQ) return;
+  const long w = o / PQ;
+  const int rem = (int)(o % PQ), j = rem / P, i = rem % P;  // output index [w][j][i]
+  Et[o] = E[(w * P + i) * Q + j];
 }
 
 // Device address of the scratch array on the current device (looked up once per device).
@@ -92,12 +104,9 @@ extern "C" slrx_status slrx_apply_noalloc(const slrx_dims* dims, double lambda, 
   float2* twQ = twP + 256;
   double* part = (double*)(base + kPartOff);
   auto chk = [](hipError_t e) { return e == hipSuccess ? SLRX_OK : fail(SLRX_EDEVICE, "launch failed: %s", hipGetErrorString(e)); };
-  k_twiddles<<<1, 256, 0, s>>>(twP, d.P);
-  k_twiddles<<<1, 256, 0, s>>>(twQ, d.Q);
+  const size_t planes = (size_t)W * d.P * d.Q;
+  k_tables<<<(unsigned)(2 + (planes + 255) / 256), 256, 0, s>>>(twP, d.P, twQ, d.Q, W, (const float2*)E, Et);
   slrx_status r = chk(hipGetLastError());
-  if (r != SLRX_OK) return r;
-  // masks [W][P][Q] -> transposed planes [W][Q][P]
-  r = chk(launch_transpose_planes(W, d.P, d.Q, (const float2*)E, Et, s));
   if (r != SLRX_OK) return r;
   RowArgs ra{};
   ra.P = d.P; ra.Q = d.Q; ra.T = d.T;
