@@ -783,8 +783,8 @@ __global__ __launch_bounds__(256) void k_dc_gemm(DcArgs a0) {
 // entry), a quad finds a root, recomputes a z entry or forms a vector, a wave multiplies
 // a 16 x 16 tile.  These levels are latency: as six launches each (4 to 10 us) the six
 // levels up to 51 entries took about 200 us of a decomposition at s = 405, all seven 245 us
-// at s = 75; here 90 us, bounded by the chain of divisions of the slowest root of a level
-// (10 to 17 us) and, below, of the QR steps (10 us); starting from single entries as the
+// at s = 75; here 96 and 72 us, bounded by the chain of the slowest root of a level (8 to 18
+// us) and, below, of the QR steps (10 to 20 us); starting from single entries as the
 // larger levels do took 120 us.
 constexpr int kLeafN = 64, kLeafLd = kLeafN + 1, kLeafNT = 256, kLeafBase = 8;
 struct LeafLds {

@@ -523,14 +523,18 @@ SLRX_DEV void rows_fin_body(const FinArgs& a, const Blk& b, float2* lds, float2*
   }
   for (int e = threadIdx.x + U * kNT; e < nel; e += kNT)
     combine(e, a.v[g0 + e], a.S[g0 + e], yp ? yp[g0 + e] : make_float2(0.f, 0.f));
-  block_sums<kNT>(dot, red);
   const int bid = b.by * b.gx + b.bx;
-  if (threadIdx.x == 0) {
-    a.part[bid] = dot[0];
-    if (!a.init && a.r) {
+  if (!a.init && a.r) {
+    block_sums<kNT>(dot, red);
+    if (threadIdx.x == 0) {
       a.part[kFinPart + bid] = dot[1];
       a.part[2 * kFinPart + bid] = dot[2];
     }
+  } else {
+    dot[0] = block_sum<kNT>(dot[0], red);
+  }
+  if (threadIdx.x == 0) {
+    a.part[bid] = dot[0];
     if (a.init && bid == 0) *a.flag = 0;
   }
   if (bid == 0 && a.part_rr) {
