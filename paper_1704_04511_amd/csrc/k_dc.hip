@@ -13,7 +13,10 @@
 //   rho = 2 |E[c-1]|:
 //   1. deflate (one thread, in sorted order): entries with rho |z_i| <= tol keep
 //      (d_i, e_i); nearly equal d_i, d_j are rotated so that one z entry vanishes
-//      (tol = 8 eps max(max |d|, max |z|), the usual criterion);
+//      (tol = 8 eps max(max |d|, min(1, rho) max |z|): relative to the node's own size,
+//      since z has norm 1 whatever the matrix, and rho z z^T the size rho; a tolerance of
+//      8 eps max |z| drops every coupling of a matrix below 1e-15, as the Gram matrix of
+//      small data is);
 //   2. every remaining root lambda_j of 1 + rho sum z_i^2 / (d_i - lambda) lies in
 //      (d_j, d_{j+1}) (the last in (d_k, d_k + rho |z|^2)); it is found by
 //      bisection on the bit pattern of its offset tau from the nearer pole, so
@@ -201,7 +204,7 @@ __global__ __launch_bounds__(kDefNT) void k_dc_deflate(DcArgs a0) {
     zs[t] = zv[perm[t]];
   }
   double mx = 0.0;
-  for (int w = 0; w < nt / 64; ++w) mx = fmax(mx, fmax(red[0][w], red[1][w]));
+  for (int w = 0; w < nt / 64; ++w) mx = fmax(mx, fmax(red[0][w], fmin(1.0, rho) * red[1][w]));
   const double tol = 8.0 * __DBL_EPSILON__ * mx;
   __syncthreads();
   // Deflation with LAPACK's criteria, in sorted order. An entry whose coupling
@@ -668,6 +671,13 @@ __global__ __launch_bounds__(256) void k_dc_zhat(DcArgs a0) {
   if ((threadIdx.x & 63) == 0) a.ws_d[5 * n + s + i] = copysign(sqrt(fmax(p, 0.0)), zl[i]);
 }
 
+// rho rounded down to a power of two: the entries of u_j are of the order of 1 / rho, so their
+// squares leave the exponent range for matrices below about 1e-140 unless they are scaled by it
+// (exactly, so it changes no bit elsewhere).
+SLRX_DEV double rho_scale(double rho) {
+  return fmax(__longlong_as_double(__double_as_longlong(rho) & 0x7ff0000000000000ll), __DBL_MIN__);
+}
+
 // u_j = z_hat / (d - lambda_j), normalised; one wave per column j (column-major U block).
 __global__ __launch_bounds__(256) void k_dc_vectors(DcArgs a0) {
   const DcArgs a = dc_at(a0, blockIdx.z);
@@ -681,10 +691,11 @@ __global__ __launch_bounds__(256) void k_dc_vectors(DcArgs a0) {
   const double* zh = a.ws_d + 5 * n + s;
   const double dor = dl[a.ws_orig[s + j]];
   const double tau = a.ws_d[4 * n + s + j];
+  const double sg = rho_scale(2.0 * fabs(a.E[s + nd.z - 1]));
   double* u = a.U + (long)(s + j) * n + s;
   double ss = 0.0;
   for (int i = threadIdx.x & 63; i < k; i += 64) {
-    const double v = zh[i] / ((dl[i] - dor) - tau);
+    const double v = zh[i] * sg / ((dl[i] - dor) - tau);
     u[i] = v;
     ss += v * v;
   }
@@ -845,7 +856,7 @@ SLRX_DEV void leaf_deflate(LeafLds& L, const double* Q, int q, int s, int m) {
     L.ns[s + t] = s;
     L.nm[s + t] = m;
   }
-  const double mx = wave_max(fmax(fabs(d), fabs(z)));
+  const double mx = wave_max(fmax(fabs(d), fmin(1.0, rho) * fabs(z)));
   const double tol = 8.0 * __DBL_EPSILON__ * mx;
   wave_lds_sync();
   bool kept = false;
@@ -1190,11 +1201,11 @@ __global__ __launch_bounds__(kLeafNT) void k_dc_leaf(DcArgs a0, int depth) {
         if (at[u] >= 0) Q[at[u]] = x[u];
     }
     if (root) {  // vectors of the merge
-      const double dor = L.dl[gs + L.orig[g]], tau = L.tau[g];
+      const double dor = L.dl[gs + L.orig[g]], tau = L.tau[g], sg = rho_scale(rho);
       double* u = L.U + g * kLeafLd + gs;
       double ss = 0.0;
       for (int i = gl; i < gk; i += 4) {
-        const double v = L.zh[gs + i] / ((L.dl[gs + i] - dor) - tau);
+        const double v = L.zh[gs + i] * sg / ((L.dl[gs + i] - dor) - tau);
         u[i] = v;
         ss += v * v;
       }
