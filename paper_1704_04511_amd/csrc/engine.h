@@ -33,6 +33,7 @@ struct DevTable {
   size_t cap = 0;                // entries of dev and pinned
   hipEvent_t copied = nullptr;   // the last upload from pinned has run
   bool pending = false;
+  long step = 0;                 // engine step that last used it
   DevTable() = default;
   DevTable(const DevTable&) = delete;
   DevTable& operator=(const DevTable&) = delete;
@@ -54,6 +55,7 @@ struct BatchEig {
   hipEvent_t ev_free = nullptr;  // every reader of the group buffers has run
   hipEvent_t ev_w = nullptr;     // the grouped weight updates so far have run
   bool have_free = false;
+  long step = 0;                 // engine steps so far
   std::map<int, EigGroup> groups;
   hipStream_t cg_stream = nullptr;  // grouped CG passes
   hipEvent_t ev_cg = nullptr;       // a group's CG has run
@@ -66,8 +68,9 @@ struct BatchEig {
 // Device bytes the shared eigen-decomposition buffers hold per problem of Gram
 // size n (an upper bound of what one more problem of that size adds).
 size_t engine_problem_bytes(int n);
-// Shrink the groups to at most keep[n] problems of size n (absent: none), after
-// the work that reads them has finished (synchronises the engine's stream).
+// Shrink the groups to at most keep[n] problems of size n (absent: none) and drop the
+// tables of grouped launches that the last step did not use (all of them if nothing is
+// kept), after the work that reads them has finished (synchronises the engine's streams).
 slrx_status engine_trim(BatchEig& be, const std::map<int, int>& keep);
 
 // Start a problem: masked data, initial iterate, start event, iteration 0.

@@ -139,6 +139,26 @@ size_t slrx::BatchEig::allocated() const {
 
 slrx_status slrx::engine_trim(BatchEig& be, const std::map<int, int>& keep) {
   bool synced = false;
+  auto sync = [&]() -> slrx_status {  // no reader of the buffers is left
+    if (synced) return SLRX_OK;
+    if (be.stream) HIPCHK(hipStreamSynchronize(be.stream));
+    if (be.cg_stream) HIPCHK(hipStreamSynchronize(be.cg_stream));
+    synced = true;
+    return SLRX_OK;
+  };
+  auto drop_tables = [&](auto& tables) -> slrx_status {
+    for (auto it = tables.begin(); it != tables.end();) {
+      if (!keep.empty() && it->second.step == be.step) {
+        ++it;
+        continue;
+      }
+      STCHK(sync());
+      it = tables.erase(it);
+    }
+    return SLRX_OK;
+  };
+  STCHK(drop_tables(be.cg_tables));
+  STCHK(drop_tables(be.weight_tables));
   for (auto it = be.groups.begin(); it != be.groups.end();) {
     const auto k = keep.find(it->first);
     const int want = k == keep.end() ? 0 : k->second;
@@ -146,10 +166,7 @@ slrx_status slrx::engine_trim(BatchEig& be, const std::map<int, int>& keep) {
       ++it;
       continue;
     }
-    if (!synced) {
-      if (be.stream) HIPCHK(hipStreamSynchronize(be.stream));  // no reader of the buffers is left
-      synced = true;
-    }
+    STCHK(sync());
     if (want == 0) {
       it = be.groups.erase(it);  // frees the buffers and the tree
       continue;
@@ -354,6 +371,7 @@ static slrx_status run_cg_group(BatchEig& be, const std::vector<slrx_plan*>& g, 
   }
   if (weights) HIPCHK(hipStreamWaitEvent(be.cg_stream, be.ev_w, 0));
   DevTable<CgSlice>& tb = be.cg_tables[std::make_pair(M, n_cg)];
+  tb.step = be.step;
   STCHK(tb.upload(host, be.cg_stream));
   CgGroup G{};
   G.tab = tb.dev;
@@ -436,6 +454,7 @@ static slrx_status weight_part_gram(BatchEig& be, const EighBufs& e, const std::
   }
   if (cg) HIPCHK(hipStreamWaitEvent(be.stream, be.ev_cg, 0));
   DevTable<WeightSlice>& tb = be.weight_tables[WeightKey(d0.N1, d0.N2, d0.M, part)];
+  tb.step = be.step;
   STCHK(tb.upload(host, be.stream));
   G.tab = tb.dev;
   HIPCHK(launch_group_images(G, be.stream));
@@ -448,6 +467,7 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
   struct PopRange {
     ~PopRange() { roctxRangePop(); }
   } pop;
+  ++be.step;
   std::map<int, std::vector<slrx_plan*>> groups;
   std::vector<slrx_plan*> live;
   for (slrx_plan* pl : plans)
