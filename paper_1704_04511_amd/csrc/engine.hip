@@ -241,7 +241,7 @@ static slrx_status group_reserve(BatchEig& be, int n, int nb, EigGroup*& out) {
     e.D = (double*)take(sd);
     e.E = (double*)take(sd);
     e.stall = (int*)take(256);
-    HIPCHK(hipMemset(e.stall, 0, 256));
+    HIPCHK(hipMemsetAsync(e.stall, 0, 256, be.stream));  // in order with the launches that read it
     e.sA = (long)(sA / sizeof(double2));
     e.sZ = e.sA;
     e.sQ = (long)(sQ / sizeof(double));
