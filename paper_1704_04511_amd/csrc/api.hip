@@ -909,29 +909,16 @@ static slrx_status step_weights_voxel(slrx_plan* pl, double eps, double* lam_out
   return SLRX_OK;
 }
 
-extern "C" slrx_status slrx_step_weights(slrx_plan* pl, double eps, double* lam_out, void* H_out, void* E_out,
-                                         slrx_mem mem) {
-  PlanScope scope(pl);
-  if (!(eps > 0.0) || !std::isfinite(eps)) return fail(SLRX_EINVAL, "eps must be finite and > 0");
-  if (pl && pl->voxel()) return step_weights_voxel(pl, eps, lam_out, H_out, E_out, mem);
-  if (pl && pl->direct()) return fail(SLRX_EINVAL, "SLRX_FLAG_DIRECT plans run whole reconstructions only");
-  STCHK(ensure_prepared(pl));
-  for (int attempt = 0;; ++attempt) {
-    HIPCHK(hipMemsetAsync(pl->info + kInfoStalled, 0, sizeof(rocblas_int), pl->stream));
-    STCHK(step_gram(pl));
-    STCHK(step_eigh(pl, -1));
-    HIPCHK(hipMemcpyAsync(pl->scal, &eps, sizeof(double), hipMemcpyHostToDevice, pl->stream));
-    HIPCHK(hipStreamSynchronize(pl->stream));
-    STCHK(step_weights(pl, -1, false, 1.0, nullptr, nullptr, H_out != nullptr));
-    int stalled = 0;
-    HIPCHK(hipMemcpyAsync(&stalled, pl->info + kInfoStalled, sizeof(int), hipMemcpyDeviceToHost, pl->stream));
-    HIPCHK(hipStreamSynchronize(pl->stream));
-    pl->tri_columns = false;
-    if (!stalled) break;
-    if (attempt > 0) return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running");
-    HIPCHK(hipMemsetAsync(pl->flag + 8, 0, sizeof(int), pl->stream));
-    pl->tri_columns = true;  // once more, by column launches
-  }
+// One attempt of slrx_step_weights; info: the eigensolver's status, the non-finite flag and
+// the give-up flag of the tridiagonalisation (then the outputs are to be computed again).
+static slrx_status weights_once(slrx_plan* pl, double eps, double* lam_out, void* H_out, void* E_out, slrx_mem mem,
+                                rocblas_int (&info)[3]) {
+  HIPCHK(hipMemsetAsync(pl->info + kInfoStalled, 0, sizeof(rocblas_int), pl->stream));
+  STCHK(step_gram(pl));
+  STCHK(step_eigh(pl, -1));
+  HIPCHK(hipMemcpyAsync(pl->scal, &eps, sizeof(double), hipMemcpyHostToDevice, pl->stream));
+  HIPCHK(hipStreamSynchronize(pl->stream));
+  STCHK(step_weights(pl, -1, false, 1.0, nullptr, nullptr, H_out != nullptr));
   const slrx_dims& d = pl->d;
   const size_t s = (size_t)d.N1 * d.N2 * d.M;
   const size_t W = (size_t)d.M * (d.M + 1) / 2;
@@ -956,9 +943,29 @@ extern "C" slrx_status slrx_step_weights(slrx_plan* pl, double eps, double* lam_
     STCHK(copy_out(pl, E_out, pl->Estage, W * d.P * d.Q * sizeof(float2), mem));
   }
   HIPCHK(hipStreamSynchronize(pl->stream));
-  int info = 0;
-  HIPCHK(hipMemcpy(&info, pl->info + SLRX_MAX_IRLS, sizeof(int), hipMemcpyDeviceToHost));
-  if (info != 0) return fail(SLRX_ENUMERIC, "eigen-decomposition did not converge (info %d)", info);
+  static_assert(kInfoNonfinite == SLRX_MAX_IRLS + 1 && kInfoStalled == SLRX_MAX_IRLS + 2, "read together");
+  HIPCHK(hipMemcpy(info, pl->info + SLRX_MAX_IRLS, sizeof info, hipMemcpyDeviceToHost));
+  return SLRX_OK;
+}
+
+extern "C" slrx_status slrx_step_weights(slrx_plan* pl, double eps, double* lam_out, void* H_out, void* E_out,
+                                         slrx_mem mem) {
+  PlanScope scope(pl);
+  if (!(eps > 0.0) || !std::isfinite(eps)) return fail(SLRX_EINVAL, "eps must be finite and > 0");
+  if (pl && pl->voxel()) return step_weights_voxel(pl, eps, lam_out, H_out, E_out, mem);
+  if (pl && pl->direct()) return fail(SLRX_EINVAL, "SLRX_FLAG_DIRECT plans run whole reconstructions only");
+  STCHK(ensure_prepared(pl));
+  rocblas_int info[3] = {};
+  STCHK(weights_once(pl, eps, lam_out, H_out, E_out, mem, info));
+  if (info[2] != 0) {  // once more, by column launches
+    HIPCHK(hipMemsetAsync(pl->flag + 8, 0, sizeof(int), pl->stream));
+    pl->tri_columns = true;
+    const slrx_status st = weights_once(pl, eps, lam_out, H_out, E_out, mem, info);
+    pl->tri_columns = false;
+    if (st != SLRX_OK) return st;
+    if (info[2] != 0) return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running");
+  }
+  if (info[0] != 0) return fail(SLRX_ENUMERIC, "eigen-decomposition did not converge (info %d)", (int)info[0]);
   return SLRX_OK;
 }
 
