@@ -31,6 +31,7 @@
 // stored as LAPACK's zhetrd (lower) stores them: v(k+2:n) in column k of the
 // column-major matrix Vst below the subdiagonal, tau(k), diagonal D, real
 // subdiagonal E.
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -834,6 +835,9 @@ SLRX_DEV bool res_columns(ResState<U, R>& st, ResLds<U, R>& q, const TriArgs& a,
 
 // U: column slots per thread (n <= 256 U); workgroup (g, problem b) = (blockIdx.x, blockIdx.y);
 // columns 0 .. k0-1, k0 = n - kTriTail.
+// Two workgroups have to fit a CU (res_capacity): 256 registers a thread, of which the largest
+// instance takes 251. Asking the compiler for it (two waves per SIMD in the launch bounds) made
+// 256 x 256 x 20 with s = 1125 0.7% slower, so a test reads the counts instead.
 template <int U, int R>
 __global__ __launch_bounds__(256) void k_tri_res(TriArgs a, TriResArgs x, int k0) {
   __shared__ ResLds<U, R> q;
@@ -984,21 +988,33 @@ struct ResDevice {
 ResDevice g_res[32];
 std::atomic<int> g_res_stall{0};  // tests: resident launches that give up at once
 
+// The fewest workgroups per CU over the kernels of U column slots and fewer.
+template <int U>
+hipError_t res_per_cu(int& per) {
+  int a = 0, b = 0;
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_tri_res<U, res_rows(U, true)>, 256, 0);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_tri_res<U, res_rows(U, false)>, 256, 0);
+  if (e != hipSuccess) return e;
+  per = std::min(per, std::min(a, b));
+  if constexpr (U > 1) return res_per_cu<U - 1>(per);
+  return hipSuccess;
+}
+
 // Workgroups of resident launches that the current device holds at a time (0: unknown),
-// by the kernel with the most registers and LDS; at most two per CU are counted.
+// whichever kernels they are of; at most two per CU are counted.
 int res_capacity() {
   static std::atomic<int> known[32];  // capacity + 1
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   std::atomic<int>& c = known[dev & 31];
   if (c.load() == 0) {
-    int cus = 0, per = 0;
+    int cus = 0, per = 2;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_tri_res<5, res_rows(5, true)>, 256, 0) != hipSuccess) {
+        res_per_cu<5>(per) != hipSuccess) {
       (void)hipGetLastError();
       return 0;
     }
-    c.store(cus * (per < 2 ? per : 2) + 1);
+    c.store(cus * per + 1);
   }
   return c.load() - 1;
 }
