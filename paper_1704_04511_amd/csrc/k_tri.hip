@@ -968,12 +968,15 @@ hipError_t launch_tridiag(const TriArgs& base, int nbatch, hipStream_t s, int ca
 
 // Workgroups of a resident launch wait for each other, so all of them have to fit the
 // chip together with those of the other resident launches that may run.  256 threads of
-// at most 256 registers leave room for two workgroups per CU (512 on 256 CUs, spread
-// evenly over the XCDs by the dispatcher).  Per stream (its launches run one after
-// another) the last launch is kept; a new one waits, on the device, for the streams whose
-// launches would not fit beside it, the ones used longest ago first.  So of launches that
-// may run together the one admitted last has left room for all the others.  Ordinary
-// kernels only delay a resident launch.
+// at most 256 registers leave room for two workgroups per CU (512 on 256 CUs).  The
+// dispatcher deals the workgroups of a launch to the XCDs in turn, whatever they already
+// hold, so a launch counts as a multiple of their number: what the fullest XCD gets.
+// (Seven launches of 73 are 511 workgroups, but 70 on one XCD, which holds 64.)  Per stream
+// (its launches run one after another) the last launch is kept; a new one waits, on the
+// device, for the streams whose launches would not fit beside it, the ones used longest ago
+// first.  So of launches that may run together the one admitted last has left room for all
+// the others.  Ordinary kernels only delay a resident launch.
+constexpr int kXcds = 8;
 namespace {
 struct ResStream {
   hipStream_t s;
@@ -1014,13 +1017,14 @@ int res_capacity() {
       (void)hipGetLastError();
       return 0;
     }
-    c.store(cus * per + 1);
+    c.store(cus / kXcds * kXcds * per + 1);
   }
   return c.load() - 1;
 }
 
 // Room for wgs workgroups on stream s (d.mu held); the stream's entry is the last one then.
 hipError_t res_admit(ResDevice& d, int wgs, hipStream_t s) {
+  wgs = (wgs + kXcds - 1) / kXcds * kXcds;
   ResStream mine{s, nullptr, wgs};
   std::vector<ResStream> keep;
   for (const ResStream& t : d.streams) {
