@@ -34,6 +34,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -980,6 +981,7 @@ constexpr int kXcds = 8;
 namespace {
 struct ResStream {
   hipStream_t s;
+  std::thread::id by;  // of hipStreamPerThread, one handle for a stream of every thread
   hipEvent_t done;  // its last launch
   int wgs;          // its largest launch that may not have run yet
 };
@@ -1025,13 +1027,14 @@ int res_capacity() {
 // Room for wgs workgroups on stream s (d.mu held); the stream's entry is the last one then.
 hipError_t res_admit(ResDevice& d, int wgs, hipStream_t s) {
   wgs = (wgs + kXcds - 1) / kXcds * kXcds;
-  ResStream mine{s, nullptr, wgs};
+  const std::thread::id by = s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+  ResStream mine{s, by, nullptr, wgs};
   std::vector<ResStream> keep;
   for (const ResStream& t : d.streams) {
     // an event of a stream that is gone gives an error: its work has run
     const bool ran = hipEventQuery(t.done) != hipErrorNotReady;
     (void)hipGetLastError();
-    if (t.s == s) {
+    if (t.s == s && t.by == by) {
       mine.done = t.done;
       if (!ran && t.wgs > mine.wgs) mine.wgs = t.wgs;
     } else if (ran) {

@@ -61,3 +61,27 @@ def test_launches_that_fill_one_xcd_more_than_the_others():
     for pl, ref in zip(plans, refs):
         np.testing.assert_array_equal(pl.images(), ref)
         pl.close()
+
+
+def test_the_per_thread_stream_is_another_stream_in_every_thread():
+    """Plans on hipStreamPerThread (handle 2): eight threads, 88 workgroups each, on eight
+    streams behind one handle, so that they do not wait for each other by themselves."""
+    say("eight threads on hipStreamPerThread, 88 workgroups each")
+    refs = []
+    for i in range(8):
+        with plan(720 + i, N2=88) as pl:
+            pl.run()
+            pl.sync()
+            refs.append(pl.images())
+    out = [None] * 8
+
+    def job(i):
+        with plan(720 + i, N2=88, stream=2) as pl:
+            for _ in range(4):
+                pl.run()
+                pl.sync()
+            out[i] = pl.images()
+
+    together([lambda i=i: job(i) for i in range(8)])
+    for a, ref in zip(out, refs):
+        np.testing.assert_array_equal(a, ref)
