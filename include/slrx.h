@@ -392,8 +392,12 @@ void slrx_fault_alloc(int32_t n);
 /* Test hook: the next n launches of the register-resident tridiagonalisation give up
  * waiting at once, as they do after 2 s when the device keeps some of their workgroups
  * from running (other processes on the GPU); the call that collects the result then
- * repeats the run by column launches.  n <= 0 switches it off. */
+ * repeats the run by column launches, from the inputs the plan still holds: where inputs or
+ * parameters were set between the end of the run and that call, it returns SLRX_EDEVICE
+ * instead and the run has to be started again.  n <= 0 switches it off.
+ * slrx_fault_stall_wait: they give up after ms milliseconds (default 0, at most 2000). */
 void slrx_fault_stall(int32_t n);
+void slrx_fault_stall_wait(int32_t ms);
 
 /* CG strategy of lock-step batches and servers (process-wide): -1 (default)
  * picks, per step shape, by timing both on the first steps (online tuner, after

@@ -97,6 +97,7 @@ _SIGS = {
     "slrx_default_params": (None, [ctypes.POINTER(Params)]),
     "slrx_fault_alloc": (None, [ctypes.c_int32]),
     "slrx_fault_stall": (None, [ctypes.c_int32]),
+    "slrx_fault_stall_wait": (None, [ctypes.c_int32]),
     "slrx_set_cg_grouping": (None, [ctypes.c_int32]),
     "slrx_validate": (_I, [ctypes.POINTER(Dims), ctypes.POINTER(Params)]),
     "slrx_footprint": (ctypes.c_size_t, [ctypes.POINTER(Dims)]),

@@ -648,6 +648,7 @@ slrx_status slrx::enqueue_run(slrx_plan* pl) {
   pl->run_irls = nirls;
   pl->run_timing = timing;
   pl->inputs_kept = true;
+  pl->gave_up = false;
   return SLRX_OK;
 }
 
@@ -671,11 +672,11 @@ slrx_status slrx::finish(slrx_plan* pl) {
     if (pl->tri_columns || !pl->inputs_kept)
       return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running%s",
                   pl->tri_columns ? "" : ", and inputs were set before the result was collected");
-    HIPCHK(hipMemsetAsync(pl->flag + 8, 0, sizeof(int), pl->stream));
     pl->tri_columns = true;
     slrx_status again = enqueue_run(pl);
     if (again == SLRX_OK) again = finish(pl);
     pl->tri_columns = false;
+    pl->gave_up = true;
     return again;
   }
   if (info[kInfoNonfinite] != 0) {
@@ -846,6 +847,7 @@ extern "C" slrx_status slrx_run_batch(slrx_plan* const* plans, int32_t n, void* 
   }
   std::lock_guard<std::mutex> lk(g_batch_mu);
   if (!g_batch_eig) g_batch_eig = new BatchEig();
+  engine_clear_stalls(*g_batch_eig);
   std::vector<slrx_plan*> v(plans, plans + n);
   slrx_status st = SLRX_OK;
   size_t begun = 0;
@@ -958,7 +960,6 @@ extern "C" slrx_status slrx_step_weights(slrx_plan* pl, double eps, double* lam_
   rocblas_int info[3] = {};
   STCHK(weights_once(pl, eps, lam_out, H_out, E_out, mem, info));
   if (info[2] != 0) {  // once more, by column launches
-    HIPCHK(hipMemsetAsync(pl->flag + 8, 0, sizeof(int), pl->stream));
     pl->tri_columns = true;
     const slrx_status st = weights_once(pl, eps, lam_out, H_out, E_out, mem, info);
     pl->tri_columns = false;

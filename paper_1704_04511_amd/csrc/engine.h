@@ -19,6 +19,7 @@ struct EigGroup {
   EighBufs bufs;        // pointers into mem, strides for problem b
   int* tree = nullptr;  // divide-and-conquer tree for n (device)
   std::vector<int> level_start, node_sizes;
+  bool clear_stall = false;  // the next resident tridiagonalisation clears the give-up flag
   ~EigGroup();
 };
 
@@ -78,6 +79,9 @@ slrx_status engine_begin(slrx_plan* pl);
 // Enqueue one outer iteration for every given problem that has iterations
 // left (no host synchronisation).
 slrx_status engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be);
+// Forget that resident tridiagonalisations gave up: each group's next one clears its flag.
+// Called when no run that met the flag goes on, or once the first of them is known.
+void engine_clear_stalls(BatchEig& be);
 // Wait for everything the engine has enqueued (after a failed step).
 void engine_drain(BatchEig& be);
 // Record the completion event of a problem whose iterations are done.

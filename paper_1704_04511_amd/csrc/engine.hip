@@ -83,6 +83,10 @@ slrx_status slrx::DevTable<T>::upload(const std::vector<T>& h, hipStream_t s) {
   return SLRX_OK;
 }
 
+void slrx::engine_clear_stalls(BatchEig& be) {
+  for (auto& kv : be.groups) kv.second.clear_stall = true;
+}
+
 void slrx::engine_drain(BatchEig& be) {
   if (be.stream) (void)hipStreamSynchronize(be.stream);
   if (be.cg_stream) (void)hipStreamSynchronize(be.cg_stream);
@@ -272,6 +276,7 @@ slrx_status slrx::engine_begin(slrx_plan* pl) {
   pl->run_irls = pl->prm.n_irls;
   pl->run_timing = false;
   pl->inputs_kept = true;
+  pl->gave_up = false;
   return SLRX_OK;
 }
 
@@ -526,6 +531,8 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
     STCHK(group_reserve(be, n, nb, G));
     EighBufs e = G->bufs;
     e.nb = nb;
+    e.clear_stall = G->clear_stall;
+    G->clear_stall = false;
     // problems of one filter share launches of the weight update's kernels too (two or
     // more: one launch for all of them is never slower than their own, run at once)
     std::map<std::tuple<int, int, int>, std::vector<int>> filters;

@@ -575,8 +575,9 @@ __global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0, const d
 // reading and writing the trailing block).
 //   Every wait ends: a thread that has polled for `wait` ticks, or sees that another has,
 // gives up, raises `stall`, and its workgroup leaves the kernel at the next barrier.  The
-// last-columns kernel then writes zeros for the problem and the host, which finds the
-// flag, repeats the run by column launches.  This only happens where workgroups of the
+// last-columns kernel then writes zeros for the problem, the launches of the run's later
+// decompositions leave at once, and the host, which finds the flag, repeats the run by
+// column launches.  This only happens where workgroups of the
 // launch are kept from running (the launches of this process that may run at a time are
 // limited to what fits the chip, res_admit).
 constexpr int kTriResMin = 128;   // largest n left to the column launches
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(256) void k_tri_res_fill(TriResArgs x, long n2, int
     ulonglong2* C = (ulonglong2*)(x.C + b * x.sC);
     for (long i = i0; i < n2; i += stride) P[i] = C[i] = make_ulonglong2(e, e);
   }
-  if (i0 == 0) *x.stall = 0;
+  if (i0 == 0 && x.clear) *x.stall = 0;
 }
 
 // Rows per workgroup by column slots U.  One problem (or few) is split finely: a column
@@ -862,12 +863,13 @@ __global__ __launch_bounds__(256) void k_tri_res(TriArgs a, TriResArgs x, int k0
   }
   st.tau = zero;
   if (tid < R) q.pown[tid] = zero;
-  if (tid == 0) q.dead = x.wait == 0 && g == G - 1;  // wait 0: give up at once (tests)
-  __syncthreads();
-  if (q.dead) {
-    if (tid == 0) __hip_atomic_store(x.stall, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return;
+  if (tid == 0) {  // a launch before this one gave up, or (tests) this workgroup is the missing one
+    const bool missing = x.missing && g == G - 1;
+    q.dead = missing || __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    if (missing && x.wait == 0) __hip_atomic_store(x.stall, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  __syncthreads();
+  if (q.dead) return;
   if (!res_columns<U, R, 0>(st, q, a, x, g, G, b, 0, min(k0, 256))) return;
   if constexpr (U > 1)
     if (!res_columns<U, R, 1>(st, q, a, x, g, G, b, 256, min(k0, 512))) return;
@@ -991,7 +993,8 @@ struct ResDevice {
   std::vector<hipEvent_t> spare;
 };
 ResDevice g_res[32];
-std::atomic<int> g_res_stall{0};  // tests: resident launches that give up at once
+std::atomic<int> g_res_stall{0};       // tests: resident launches that miss a workgroup
+std::atomic<int> g_res_stall_wait{0};  // and how long they wait for it in ms
 
 // The fewest workgroups per CU over the kernels of U column slots and fewer.
 template <int U>
@@ -1109,7 +1112,8 @@ hipError_t launch_tridiag_resident(const TriArgs& base, const TriResArgs& xbase,
   const ResShape r = res_shape(n, nbatch);
   TriResArgs x = xbase;
   x.wait = kTriResWait;
-  if (g_res_stall.load() > 0 && g_res_stall.fetch_sub(1) > 0) x.wait = 0;
+  x.missing = g_res_stall.load() > 0 && g_res_stall.fetch_sub(1) > 0;
+  if (x.missing) x.wait = (unsigned long long)g_res_stall_wait.load() * 100000;
   k_tri_res_fill<<<512, 256, 0, s>>>(x, (long)n * n, nbatch);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   for (int b = 0; b < nbatch; b += r.per) {
@@ -1143,3 +1147,6 @@ hipError_t launch_tridiag_resident(const TriArgs& base, const TriResArgs& xbase,
 }  // namespace slrx
 
 extern "C" void slrx_fault_stall(int32_t n) { slrx::g_res_stall.store(n < 0 ? 0 : n); }
+extern "C" void slrx_fault_stall_wait(int32_t ms) {
+  slrx::g_res_stall_wait.store(ms < 0 ? 0 : ms > 2000 ? 2000 : ms);
+}

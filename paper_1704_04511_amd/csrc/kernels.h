@@ -270,7 +270,7 @@ struct WeightArgs {
   double* eps_out;          // per-iteration record (may be null)
   int first;                // 1 on the first IRLS iteration
   double eps0_frac, gamma, p;
-  const int* stall;         // the eigensolver's give-up flag (may be null) ..
+  const int* stall;         // the give-up flag of a shared eigen-decomposition (or null) ..
   int* stalled;             // .. recorded here
 };
 hipError_t launch_eps(const WeightArgs& a, hipStream_t s);  // the eps update alone
@@ -298,13 +298,17 @@ struct TriArgs {
 hipError_t launch_tridiag(const TriArgs& a, int nbatch, hipStream_t s, int cand, bool stream);
 // The same in one launch with the matrix in registers (tri_resident(n)), then the last
 // columns; vbuf[0] and pbuf[0] hold the pending reflector between the two.  P, C: write-once
-// vectors of the exchange, n x n elements per problem each.  stall is set to 1 when a wait
-// was given up: every output of the launch is then finite but not a result.
+// vectors of the exchange, n x n elements per problem each.  stall is set when a wait was
+// given up: every output of the launch is then finite but not a result.  It stays set, and
+// launches that find it set leave at once, so that a run waits only once; it is cleared by
+// whoever starts the next run, or by a launch with `clear`.
 struct TriResArgs {
   double2* P;
   double2* C;
   long sP, sC;              // elements between the problems of a batch
   int* stall;
+  bool clear;
+  bool missing;             // tests: the last workgroup of every problem leaves at once
   unsigned long long wait;  // longest wait of a thread in ticks of 10 ns (0: give up at once)
 };
 constexpr unsigned long long kTriResWait = 200000000ull;  // 2 s

@@ -15,7 +15,7 @@ constexpr int kMaxS = 3000;    // largest filter size s = N1 N2 M (own eigensolv
 constexpr int kMaxCg = 10000;  // largest CG iteration count
 // info: eigensolver status per outer iteration, the single-step slot
 // (SLRX_MAX_IRLS), a flag raised by the Gram pass on a non-finite entry, and one
-// raised when a resident tridiagonalisation gave up waiting
+// raised when a resident tridiagonalisation gave up waiting (both for the whole run)
 constexpr int kInfoNonfinite = SLRX_MAX_IRLS + 1;
 constexpr int kInfoStalled = SLRX_MAX_IRLS + 2;
 constexpr int kInfoEntries = SLRX_MAX_IRLS + 3;
@@ -131,6 +131,7 @@ struct slrx_plan {
   bool prepared = false, running = false, ran = false;
   bool tri_columns = false;  // tridiagonalise by column launches (after a resident launch gave up)
   bool inputs_kept = false;  // nothing was set since the run was started
+  bool gave_up = false;      // a resident launch of the last run gave up (the run was repeated)
   int run_irls = 0;
   bool run_timing = false;
 
@@ -175,6 +176,7 @@ struct EighBufs {
   const std::vector<int>* node_sizes = nullptr;
   long sA = 0, sZ = 0, sQ = 0, s_wsi = 0, s_wsd = 0, s_bts = 0;
   int* stall = nullptr;        // give-up flag of the resident tridiagonalisation
+  bool clear_stall = false;    // its launch clears the flag first
   bool tri_columns = false;    // column launches instead of it
 };
 EighBufs plan_eigh_bufs(slrx_plan* pl);

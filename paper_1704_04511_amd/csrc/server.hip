@@ -285,6 +285,7 @@ static void scheduler_main(slrx_server* s) {
       }
       if (st != SLRX_OK) {  // device-side state of the step is unknown: fail every active request
         engine_drain(s->eig);
+        engine_clear_stalls(s->eig);
         for (Req* r : active) {
           (void)hipStreamSynchronize(r->plan->stream);
           r->plan->running = false;
@@ -315,7 +316,9 @@ static void scheduler_main(slrx_server* s) {
       Req* r = finishing[i];
       const bool must_wait = active.empty() && i == 0;
       if (must_wait || hipEventQuery(r->plan->ev_run[1]) != hipErrorNotReady) {
-        complete_request(s, r, collect_request(r));
+        const slrx_status sr = collect_request(r);
+        if (r->plan->gave_up) engine_clear_stalls(s->eig);
+        complete_request(s, r, sr);
         finishing.erase(finishing.begin() + i);
       } else {
         ++i;

@@ -162,7 +162,7 @@ EighBufs slrx::plan_eigh_bufs(slrx_plan* pl) {
   e.tree = pl->dc_tree;
   e.level_start = &pl->dc_level_start;
   e.node_sizes = &pl->dc_node_sizes;
-  e.stall = pl->flag + 8;
+  e.stall = pl->info + kInfoStalled;
   e.tri_columns = pl->tri_columns;
   return e;
 }
@@ -194,6 +194,7 @@ hipError_t slrx::eigh_tri(const EighBufs& e, hipStream_t st) {
       x.C = (double2*)e.Q;  // Q and Qs
       x.sC = e.sQ / 2;
       x.stall = e.stall;
+      x.clear = e.clear_stall;
       return launch_tridiag_resident(ta, x, e.nb, st);
     }
   }
@@ -323,7 +324,7 @@ void slrx::weight_args(slrx_plan* pl, int it, bool first, double gamma, const do
   wa.eps0_frac = pl->prm.eps0_frac;
   wa.gamma = gamma;
   wa.p = pl->prm.p;
-  wa.stall = stall ? stall : pl->flag + 8;
+  wa.stall = stall;
   wa.stalled = pl->info + kInfoStalled;
   const int ng = spec_supported(d.N1, d.N2, d.M) ? spec_groups(d.N1, d.N2, d.M, (size_t)s * s) : 0;
   sa = SpecArgs{};
@@ -455,8 +456,6 @@ slrx_status slrx::step_direct_weights(slrx_plan* pl, int it, bool first, double 
   wa.eps0_frac = pl->prm.eps0_frac;
   wa.gamma = gamma;
   wa.p = pl->prm.p;
-  wa.stall = pl->flag + 8;
-  wa.stalled = pl->info + kInfoStalled;
   HIPCHK(launch_weights(wa, pl->stream));
   HIPCHK(launch_filter_product(s, pl->VT, pl->Hre, pl->Him, pl->stream));
   HIPCHK(launch_hf((long)s * s, pl->Hre, pl->Him, pl->Hf, pl->stream));

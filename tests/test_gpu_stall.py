@@ -1,0 +1,95 @@
+"""Resident tridiagonalisations that have to give up (slrx_fault_stall: a workgroup is missing
+and every other one leaves after its bounded wait): what that may cost, and whom.  Results of
+repeated runs are those of column launches, which round differently: FP64 reductions, then a
+few steps of complex64 CG, 1e-5 as in the tests of the sizes."""
+import time
+
+import numpy as np
+import pytest
+
+import workload
+from tests.gpu_util import nrmse, say
+
+pytestmark = pytest.mark.gpu
+
+slrx = pytest.importorskip("paper_1704_04511_amd")
+
+
+@pytest.fixture(autouse=True)
+def disarm():
+    yield
+    slrx.lib().slrx_fault_stall(0)
+    slrx.lib().slrx_fault_stall_wait(0)
+
+
+def stall(n, ms=0):
+    slrx.lib().slrx_fault_stall_wait(ms)
+    slrx.lib().slrx_fault_stall(n)
+
+
+def problem(seed, n_irls=6, N=7, M=4):
+    return workload.make_problem(seed=seed, P=64, Q=64, T=8, K=2, R=4, N1=N, N2=N, M=M, n_irls=n_irls, n_cg=4)
+
+
+def plan_of(pb, stream=None):
+    T, P, Q = pb.b.shape
+    pl = slrx.Plan(P, Q, T, pb.N1, pb.N2, pb.M, slrx.make_params(lam=pb.lam, n_irls=pb.n_irls, n_cg=pb.n_cg), stream=stream)
+    pl.set_kspace(pb.b)
+    pl.set_mask(pb.S)
+    return pl
+
+
+def run(pl):
+    pl.run()
+    pl.sync()
+    return pl.images()
+
+
+def test_a_run_waits_once():
+    """Six decompositions that would each wait 200 ms: the run waits for the first one alone."""
+    say("six stalled launches of 200 ms, one plan")
+    pl = plan_of(problem(800))
+    ref = run(pl)
+    stall(6, 200)
+    t0 = time.perf_counter()
+    img = run(pl)
+    dt = time.perf_counter() - t0
+    say(f"{dt * 1e3:.0f} ms")
+    assert 0.2 <= dt <= 0.6
+    assert nrmse(img, ref) <= 1e-5
+    stall(0)
+    np.testing.assert_array_equal(run(pl), ref)  # the next run takes resident launches again
+    pl.close()
+
+
+def submit(srv, pb):
+    return srv.submit_data(pb.b, pb.S, pb.N1, pb.N2, pb.M, slrx.make_params(lam=pb.lam, n_irls=pb.n_irls, n_cg=pb.n_cg))
+
+
+def test_requests_wait_once():
+    """The same for a server's group of two, and a request after them is not touched by it."""
+    say("six stalled launches of 200 ms, two requests")
+    pbs = [problem(802 + i) for i in range(3)]
+    refs = []
+    for pb in pbs:
+        with plan_of(pb) as pl:
+            refs.append(run(pl))
+    srv = slrx.Server(1 << 30, max_slots=4)
+    try:
+        stall(6, 200)
+        t0 = time.perf_counter()
+        ts = [submit(srv, pb) for pb in pbs[:2]]
+        for t in ts:
+            srv.wait(t)
+        dt = time.perf_counter() - t0
+        say(f"{dt * 1e3:.0f} ms")
+        assert dt <= 0.8  # at most two groups: the first request may have started alone
+        stall(0)
+        ts.append(submit(srv, pbs[2]))
+        srv.wait(ts[2])
+        out = [srv.fetch(t, pb.b.shape) for t, pb in zip(ts, pbs)]
+    finally:
+        srv.close()
+    for img, ref in zip(out[:2], refs):
+        assert nrmse(img, ref) <= 1e-5
+    np.testing.assert_array_equal(out[2], refs[2])
