@@ -435,7 +435,10 @@ extern "C" void slrx_plan_destroy(slrx_plan* pl) {
   if (pl->blas_ws) (void)hipFree(pl->blas_ws);
   if (pl->coil_mem) (void)hipFree(pl->coil_mem);
   if (pl->arena) (void)hipFree(pl->arena);
-  if (pl->own_stream && pl->stream) (void)hipStreamDestroy(pl->stream);
+  if (pl->own_stream && pl->stream) {
+    tri_resident_forget(pl->stream);
+    (void)hipStreamDestroy(pl->stream);
+  }
   delete pl;
 }
 
@@ -649,6 +652,7 @@ slrx_status slrx::enqueue_run(slrx_plan* pl) {
   pl->run_timing = timing;
   pl->inputs_kept = true;
   pl->gave_up = false;
+  pl->tri_stream = pl->stream;
   return SLRX_OK;
 }
 
@@ -669,6 +673,7 @@ slrx_status slrx::finish(slrx_plan* pl) {
     // a resident tridiagonalisation gave up waiting for its workgroups: once more, by
     // column launches, from the inputs the plan still holds
     pl->ran = false;
+    tri_resident_gave_up(pl->tri_stream, info[kInfoStalled]);
     if (pl->tri_columns || !pl->inputs_kept)
       return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running%s",
                   pl->tri_columns ? "" : ", and inputs were set before the result was collected");
@@ -960,6 +965,7 @@ extern "C" slrx_status slrx_step_weights(slrx_plan* pl, double eps, double* lam_
   rocblas_int info[3] = {};
   STCHK(weights_once(pl, eps, lam_out, H_out, E_out, mem, info));
   if (info[2] != 0) {  // once more, by column launches
+    tri_resident_gave_up(pl->stream, info[2]);
     pl->tri_columns = true;
     const slrx_status st = weights_once(pl, eps, lam_out, H_out, E_out, mem, info);
     pl->tri_columns = false;

@@ -102,7 +102,10 @@ slrx::BatchEig::~BatchEig() {
   if (ev_w) (void)hipEventDestroy(ev_w);
   if (ev_free) (void)hipEventDestroy(ev_free);
   if (ev_cg) (void)hipEventDestroy(ev_cg);
-  if (stream) (void)hipStreamDestroy(stream);
+  if (stream) {
+    tri_resident_forget(stream);
+    (void)hipStreamDestroy(stream);
+  }
   if (cg_stream) (void)hipStreamDestroy(cg_stream);
 }
 
@@ -299,6 +302,7 @@ static bool cg_groupable(const slrx_plan* pl) { return pl->ncoils == 0 && !pl->d
 // (its weights-done event recorded).
 static slrx_status step_single(slrx_plan* pl, std::vector<slrx_plan*>* deferred = nullptr) {
   const int it = pl->it_next;
+  pl->tri_stream = pl->stream;
   if (pl->direct()) {
     STCHK(step_direct_gram(pl));
     STCHK(step_eigh(pl, it));
@@ -531,8 +535,15 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
     STCHK(group_reserve(be, n, nb, G));
     EighBufs e = G->bufs;
     e.nb = nb;
-    e.clear_stall = G->clear_stall;
-    G->clear_stall = false;
+    // column launches neither read nor clear the group's flag: the word after it stays 0
+    e.tri_columns = !tri_resident(n) || tri_resident_held(be.stream);
+    if (e.tri_columns) {
+      e.stall += 1;
+    } else {
+      e.clear_stall = G->clear_stall;
+      G->clear_stall = false;
+    }
+    for (slrx_plan* pl : g) pl->tri_stream = be.stream;
     // problems of one filter share launches of the weight update's kernels too (two or
     // more: one launch for all of them is never slower than their own, run at once)
     std::map<std::tuple<int, int, int>, std::vector<int>> filters;

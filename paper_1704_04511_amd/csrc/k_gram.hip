@@ -198,7 +198,7 @@ SLRX_DEV void eps_body(const WeightArgs& a) {
   *a.eps = e;
   if (a.lam_max_out) *a.lam_max_out = lmax;
   if (a.eps_out) *a.eps_out = e;
-  if (a.stall && *a.stall) *a.stalled = 1;
+  if (a.stall && *a.stall && *a.stalled == 0) *a.stalled = *a.stall;
 }
 __global__ void k_eps(WeightArgs a) {
   if (threadIdx.x == 0 && blockIdx.x == 0) eps_body(a);

@@ -33,6 +33,7 @@
 // subdiagonal E.
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <mutex>
 #include <thread>
 #include <type_traits>
@@ -700,7 +701,7 @@ SLRX_DEV bool res_columns(ResState<U, R>& st, ResLds<U, R>& q, const TriArgs& a,
           if (t0 == 0) t0 = t;
           if (t - t0 > x.wait || __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
             if (lane == 0) {
-              __hip_atomic_store(x.stall, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(x.stall, x.id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               q.dead = 1;
             }
             break;
@@ -866,7 +867,7 @@ __global__ __launch_bounds__(256) void k_tri_res(TriArgs a, TriResArgs x, int k0
   if (tid == 0) {  // a launch before this one gave up, or (tests) this workgroup is the missing one
     const bool missing = x.missing && g == G - 1;
     q.dead = missing || __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    if (missing && x.wait == 0) __hip_atomic_store(x.stall, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (missing && x.wait == 0) __hip_atomic_store(x.stall, x.id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
   if (q.dead) return;
@@ -987,12 +988,22 @@ struct ResStream {
   hipEvent_t done;  // its last launch
   int wgs;          // its largest launch that may not have run yet
 };
+struct ResHeld {  // a stream whose launches gave up
+  hipStream_t s;
+  std::thread::id by;
+  int stall;  // the last launch that did
+  std::chrono::steady_clock::time_point last, until;
+};
+constexpr std::chrono::seconds kResHold(60);
+constexpr size_t kResHeldMax = 64;  // streams remembered
 struct ResDevice {
   std::mutex mu;
+  std::vector<ResHeld> held;
   std::vector<ResStream> streams;  // in order of their last launch; those that have run are dropped
   std::vector<hipEvent_t> spare;
 };
 ResDevice g_res[32];
+std::atomic<int> g_res_id{0};
 std::atomic<int> g_res_stall{0};       // tests: resident launches that miss a workgroup
 std::atomic<int> g_res_stall_wait{0};  // and how long they wait for it in ms
 
@@ -1027,10 +1038,23 @@ int res_capacity() {
   return c.load() - 1;
 }
 
+// The thread that tells the streams behind one handle apart.
+std::thread::id res_thread(hipStream_t s) {
+  return s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+}
+ResDevice* res_device() {
+  int dev = 0;
+  return hipGetDevice(&dev) == hipSuccess ? &g_res[dev & 31] : nullptr;
+}
+std::vector<ResHeld>::iterator res_held(ResDevice& d, hipStream_t s) {
+  const std::thread::id by = res_thread(s);
+  return std::find_if(d.held.begin(), d.held.end(), [&](const ResHeld& h) { return h.s == s && h.by == by; });
+}
+
 // Room for wgs workgroups on stream s (d.mu held); the stream's entry is the last one then.
 hipError_t res_admit(ResDevice& d, int wgs, hipStream_t s) {
   wgs = (wgs + kXcds - 1) / kXcds * kXcds;
-  const std::thread::id by = s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+  const std::thread::id by = res_thread(s);
   ResStream mine{s, by, nullptr, wgs};
   std::vector<ResStream> keep;
   for (const ResStream& t : d.streams) {
@@ -1087,6 +1111,36 @@ ResShape res_shape(int n, int nbatch) {
 }
 }  // namespace
 
+void tri_resident_gave_up(hipStream_t s, int stall) {
+  ResDevice* d = res_device();
+  if (!d) return;
+  std::lock_guard<std::mutex> lk(d->mu);
+  const auto now = std::chrono::steady_clock::now();
+  const auto it = res_held(*d, s);
+  if (it == d->held.end()) {
+    if (d->held.size() >= kResHeldMax) d->held.erase(d->held.begin());
+    d->held.push_back(ResHeld{s, res_thread(s), stall, now, now});
+  } else if (it->stall != stall) {  // several runs may report one launch
+    if (now - it->last < 2 * kResHold) it->until = now + kResHold;
+    it->stall = stall;
+    it->last = now;
+  }
+}
+bool tri_resident_held(hipStream_t s) {
+  ResDevice* d = res_device();
+  if (!d) return false;
+  std::lock_guard<std::mutex> lk(d->mu);
+  const auto it = res_held(*d, s);
+  return it != d->held.end() && std::chrono::steady_clock::now() < it->until;
+}
+void tri_resident_forget(hipStream_t s) {
+  ResDevice* d = res_device();
+  if (!d) return;
+  std::lock_guard<std::mutex> lk(d->mu);
+  const auto it = res_held(*d, s);
+  if (it != d->held.end()) d->held.erase(it);
+}
+
 // Sizes with more columns than the last-columns kernel takes plus a few (each is worth an
 // exchange then), whose rows fit the registers of 256 workgroups.
 bool tri_resident(int n) { return n > kTriResMin && n <= 256 * 5 && res_capacity() >= 256; }
@@ -1112,6 +1166,8 @@ hipError_t launch_tridiag_resident(const TriArgs& base, const TriResArgs& xbase,
   const ResShape r = res_shape(n, nbatch);
   TriResArgs x = xbase;
   x.wait = kTriResWait;
+  do x.id = g_res_id.fetch_add(1) + 1;
+  while (x.id == 0);
   x.missing = g_res_stall.load() > 0 && g_res_stall.fetch_sub(1) > 0;
   if (x.missing) x.wait = (unsigned long long)g_res_stall_wait.load() * 100000;
   k_tri_res_fill<<<512, 256, 0, s>>>(x, (long)n * n, nbatch);

@@ -307,12 +307,20 @@ struct TriResArgs {
   double2* C;
   long sP, sC;              // elements between the problems of a batch
   int* stall;
+  int id;                   // this launch, what stall is set to (never 0)
   bool clear;
   bool missing;             // tests: the last workgroup of every problem leaves at once
   unsigned long long wait;  // longest wait of a thread in ticks of 10 ns (0: give up at once)
 };
 constexpr unsigned long long kTriResWait = 200000000ull;  // 2 s
 bool tri_resident(int n);
+// A resident launch on s gave up (stall: what its flag was set to).  After two within two
+// minutes tri_resident_held(s) is true for one minute: column launches are the faster choice
+// while whatever keeps the workgroups from running lasts, and each further try would cost a
+// wait of 2 s and the repeated run.  tri_resident_forget: s is about to be destroyed.
+void tri_resident_gave_up(hipStream_t s, int stall);
+bool tri_resident_held(hipStream_t s);
+void tri_resident_forget(hipStream_t s);
 int tri_resident_workgroups(int n, int nbatch);  // of one launch
 hipError_t launch_tridiag_resident(const TriArgs& a, const TriResArgs& x, int nbatch, hipStream_t s);
 int tri_budget_candidates(int nbatch);

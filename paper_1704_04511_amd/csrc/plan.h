@@ -15,7 +15,7 @@ constexpr int kMaxS = 3000;    // largest filter size s = N1 N2 M (own eigensolv
 constexpr int kMaxCg = 10000;  // largest CG iteration count
 // info: eigensolver status per outer iteration, the single-step slot
 // (SLRX_MAX_IRLS), a flag raised by the Gram pass on a non-finite entry, and one
-// raised when a resident tridiagonalisation gave up waiting (both for the whole run)
+// set to the resident tridiagonalisation that gave up waiting (both for the whole run)
 constexpr int kInfoNonfinite = SLRX_MAX_IRLS + 1;
 constexpr int kInfoStalled = SLRX_MAX_IRLS + 2;
 constexpr int kInfoEntries = SLRX_MAX_IRLS + 3;
@@ -131,6 +131,7 @@ struct slrx_plan {
   bool prepared = false, running = false, ran = false;
   bool tri_columns = false;  // tridiagonalise by column launches (after a resident launch gave up)
   bool inputs_kept = false;  // nothing was set since the run was started
+  hipStream_t tri_stream = nullptr;  // the stream of the last run's tridiagonalisations
   bool gave_up = false;      // a resident launch of the last run gave up (the run was repeated)
   int run_irls = 0;
   bool run_timing = false;

@@ -163,7 +163,7 @@ EighBufs slrx::plan_eigh_bufs(slrx_plan* pl) {
   e.level_start = &pl->dc_level_start;
   e.node_sizes = &pl->dc_node_sizes;
   e.stall = pl->info + kInfoStalled;
-  e.tri_columns = pl->tri_columns;
+  e.tri_columns = pl->tri_columns || tri_resident_held(pl->stream);
   return e;
 }
 

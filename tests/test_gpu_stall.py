@@ -93,3 +93,73 @@ def test_requests_wait_once():
     for img, ref in zip(out[:2], refs):
         assert nrmse(img, ref) <= 1e-5
     np.testing.assert_array_equal(out[2], refs[2])
+
+
+def spectrum(pl):
+    """The largest eigenvalue of every iteration, in FP64: images are rounded too coarsely to tell
+    column launches from resident ones."""
+    pl.run()
+    pl.sync()
+    return pl.stats()["lambda_max"]
+
+
+def test_a_stream_whose_launches_gave_up_twice_takes_column_launches():
+    """Two give-ups on one stream: its next run takes column launches by itself (the bits of the
+    repeated runs, no wait); other streams and a new plan's stream are not touched."""
+    say("two stalled runs on one stream")
+    pb = problem(810)
+    pl, other = plan_of(pb), plan_of(pb)
+    ref = spectrum(pl)
+    stall(1)
+    cols = spectrum(pl)
+    np.testing.assert_allclose(cols, ref, rtol=1e-5)
+    assert cols != ref
+    assert spectrum(pl) == ref  # once is not enough
+    stall(1)
+    assert spectrum(pl) == cols
+    stall(0)
+    assert spectrum(pl) == cols
+    lam0 = pl.step_weights(100.0)[0]
+    assert spectrum(other) == ref
+    lam1 = other.step_weights(100.0)[0]
+    assert np.abs(lam0 - lam1).max() <= 80 * lam0.size * 2.0 ** -53 * lam0[-1] and not np.array_equal(lam0, lam1)
+    pl.close()
+    other.close()
+    with plan_of(pb) as pl:  # most likely on the handle of a stream just destroyed
+        assert spectrum(pl) == ref
+
+
+def test_a_plan_made_for_every_run_on_a_callers_stream():
+    """The stream is remembered, not the plan."""
+    import torch
+    say("two stalled plans on a caller's stream")
+    pb = problem(810)
+    st = torch.cuda.Stream()
+    with plan_of(pb) as pl:
+        ref = spectrum(pl)
+    for _ in range(2):
+        stall(1)
+        with plan_of(pb, stream=st.cuda_stream) as pl:
+            cols = spectrum(pl)
+    stall(0)
+    assert cols != ref
+    with plan_of(pb, stream=st.cuda_stream) as pl:
+        assert spectrum(pl) == cols
+
+
+def test_a_server_whose_launches_gave_up_twice_takes_column_launches():
+    say("two stalled requests of one server")
+    pb = problem(810)
+    with plan_of(pb) as pl:
+        ref = spectrum(pl)
+        srv = slrx.Server(1 << 30, max_slots=2)
+        try:
+            out = []
+            for n in (0, 1, 1, 0):
+                stall(n)
+                srv.wait(srv.submit(pl))
+                out.append(pl.stats()["lambda_max"])
+        finally:
+            srv.close()
+    assert out[0] == ref and out[1] != ref
+    assert out[2] == out[1] and out[3] == out[1]
