@@ -114,7 +114,7 @@ static size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 // Layout of the buffers for nb problems of size n: every matrix-sized buffer
 // per problem, the vectors for all of them.
 struct GroupLayout {
-  size_t sA, sQ, sWi, sWd, sB, sv, sd, total;  // and 256 bytes for the give-up flag
+  size_t sA, sQ, sWi, sWd, sB, sv, sd, total;
 };
 static GroupLayout group_layout(int n, int nb) {
   GroupLayout L;
@@ -126,10 +126,13 @@ static GroupLayout group_layout(int n, int nb) {
   L.sB = al(bt_scratch_elems(n) * sizeof(double2));
   L.sv = al((size_t)nb * n * sizeof(double2));
   L.sd = al((size_t)nb * n * sizeof(double));
-  L.total = (size_t)nb * (3 * L.sA + L.sQ + L.sWi + L.sWd + L.sB) + 5 * L.sv + 2 * L.sd + 256;
+  L.total = (size_t)nb * (3 * L.sA + L.sQ + L.sWi + L.sWd + L.sB) + 5 * L.sv + 2 * L.sd;
   return L;
 }
-static size_t tree_bytes(int n) { return std::max<size_t>((size_t)4 * n, 4) * sizeof(int); }
+// The divide-and-conquer tree, and 256 bytes for the give-up flag, which outlives the buffers
+// (they are reallocated when a problem joins).
+static size_t tree_ints(int n) { return std::max<size_t>((size_t)4 * n, 4); }
+static size_t tree_bytes(int n) { return tree_ints(n) * sizeof(int) + 256; }
 
 size_t slrx::engine_problem_bytes(int n) { return group_layout(n, 1).total + tree_bytes(n); }
 
@@ -207,6 +210,8 @@ static slrx_status group_reserve(BatchEig& be, int n, int nb, EigGroup*& out) {
     }
     if (!nodes.empty())
       HIPCHK(hipMemcpy(G.tree, nodes.data(), nodes.size() * sizeof(int), hipMemcpyHostToDevice));
+    G.bufs.stall = G.tree + tree_ints(n);
+    HIPCHK(hipMemsetAsync(G.bufs.stall, 0, 256, be.stream));  // in order with the launches that read it
     G.n = n;  // only once the tree is on the device
   }
   if (nb > G.cap) {
@@ -247,8 +252,6 @@ static slrx_status group_reserve(BatchEig& be, int n, int nb, EigGroup*& out) {
     e.trip[1] = (double2*)take(sv);
     e.D = (double*)take(sd);
     e.E = (double*)take(sd);
-    e.stall = (int*)take(256);
-    HIPCHK(hipMemsetAsync(e.stall, 0, 256, be.stream));  // in order with the launches that read it
     e.sA = (long)(sA / sizeof(double2));
     e.sZ = e.sA;
     e.sQ = (long)(sQ / sizeof(double));
