@@ -539,7 +539,7 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
     EighBufs e = G->bufs;
     e.nb = nb;
     // column launches neither read nor clear the group's flag: the word after it stays 0
-    e.tri_columns = !tri_resident(n) || tri_resident_held(be.stream);
+    e.tri_columns = !tri_resident(n) || !tri_resident_on(be.stream);
     if (e.tri_columns) {
       e.stall += 1;
     } else {

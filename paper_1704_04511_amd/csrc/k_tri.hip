@@ -1126,12 +1126,24 @@ void tri_resident_gave_up(hipStream_t s, int stall) {
     it->last = now;
   }
 }
-bool tri_resident_held(hipStream_t s) {
-  ResDevice* d = res_device();
-  if (!d) return false;
-  std::lock_guard<std::mutex> lk(d->mu);
-  const auto it = res_held(*d, s);
-  return it != d->held.end() && std::chrono::steady_clock::now() < it->until;
+bool tri_resident_on(hipStream_t s) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return false;
+  uint32_t mask[32] = {};  // without a mask: ones (0.5 us)
+  const int words = std::min((cus + 31) / 32, 32);
+  if (hipExtStreamGetCUMask(s, words, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int in = 0;
+  for (uint32_t w : mask) in += __builtin_popcount(w);
+  if (in < cus) return false;
+  ResDevice& d = g_res[dev & 31];
+  std::lock_guard<std::mutex> lk(d.mu);
+  const auto it = res_held(d, s);
+  return it == d.held.end() || std::chrono::steady_clock::now() >= it->until;
 }
 void tri_resident_forget(hipStream_t s) {
   ResDevice* d = res_device();

@@ -314,12 +314,15 @@ struct TriResArgs {
 };
 constexpr unsigned long long kTriResWait = 200000000ull;  // 2 s
 bool tri_resident(int n);
-// A resident launch on s gave up (stall: what its flag was set to).  After two within two
-// minutes tri_resident_held(s) is true for one minute: column launches are the faster choice
-// while whatever keeps the workgroups from running lasts, and each further try would cost a
-// wait of 2 s and the repeated run.  tri_resident_forget: s is about to be destroyed.
+// Whether resident launches may be made on s: not on a stream that is kept to some of the CUs
+// (a CU mask), where their workgroups may never run together, and not for one minute after two
+// of them gave up within two minutes: column launches are the faster choice while whatever
+// keeps the workgroups from running lasts, and each further try would cost a wait of 2 s and
+// the repeated run.
+bool tri_resident_on(hipStream_t s);
+// A resident launch on s gave up (stall: what its flag was set to).  tri_resident_forget: s is
+// about to be destroyed.
 void tri_resident_gave_up(hipStream_t s, int stall);
-bool tri_resident_held(hipStream_t s);
 void tri_resident_forget(hipStream_t s);
 int tri_resident_workgroups(int n, int nbatch);  // of one launch
 hipError_t launch_tridiag_resident(const TriArgs& a, const TriResArgs& x, int nbatch, hipStream_t s);

@@ -178,7 +178,7 @@ struct EighBufs {
   long sA = 0, sZ = 0, sQ = 0, s_wsi = 0, s_wsd = 0, s_bts = 0;
   int* stall = nullptr;        // give-up flag of the resident tridiagonalisation
   bool clear_stall = false;    // its launch clears the flag first
-  bool tri_columns = false;    // column launches instead of it
+  bool tri_columns = true;     // column launches instead of it
 };
 EighBufs plan_eigh_bufs(slrx_plan* pl);
 hipError_t eigh_tri(const EighBufs& e, hipStream_t s);     // Gram in A (row-major) -> D, E, tau, V

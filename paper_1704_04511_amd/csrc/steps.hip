@@ -163,7 +163,7 @@ EighBufs slrx::plan_eigh_bufs(slrx_plan* pl) {
   e.level_start = &pl->dc_level_start;
   e.node_sizes = &pl->dc_node_sizes;
   e.stall = pl->info + kInfoStalled;
-  e.tri_columns = pl->tri_columns || tri_resident_held(pl->stream);
+  e.tri_columns = pl->tri_columns || !tri_resident(s) || !tri_resident_on(pl->stream);
   return e;
 }
 
@@ -184,7 +184,7 @@ hipError_t slrx::eigh_tri(const EighBufs& e, hipStream_t st) {
   // its exchange); not while the stream is being captured, where it could not be ordered
   // against the resident launches of other streams
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (!e.tri_columns && tri_resident(e.n)) {
+  if (!e.tri_columns) {
     const hipError_t ec = hipStreamIsCapturing(st, &cap);
     if (ec != hipSuccess) return ec;
     if (cap == hipStreamCaptureStatusNone) {

@@ -163,3 +163,26 @@ def test_a_server_whose_launches_gave_up_twice_takes_column_launches():
             srv.close()
     assert out[0] == ref and out[1] != ref
     assert out[2] == out[1] and out[3] == out[1]
+
+
+def test_a_stream_kept_to_some_of_the_cus_takes_column_launches():
+    """A resident launch waits for workgroups that a CU mask may never let run together."""
+    import ctypes
+    import torch
+    say("a plan on a stream of half of the CUs")
+    pb = problem(810)
+    with plan_of(pb) as pl:
+        ref = spectrum(pl)
+        stall(1)
+        cols = spectrum(pl)
+        stall(0)
+    hip = ctypes.CDLL([ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln][0])
+    words = (torch.cuda.get_device_properties(0).multi_processor_count + 31) // 32
+    mask = (ctypes.c_uint32 * words)(*([0xffffffff] * (words // 2)))
+    h = ctypes.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(h), words, mask) == 0
+    try:
+        with plan_of(pb, stream=h.value) as pl:
+            assert spectrum(pl) == cols and cols != ref
+    finally:
+        assert hip.hipStreamDestroy(h) == 0
