@@ -597,7 +597,8 @@ extern "C" slrx_status slrx_set_params(slrx_plan* pl, const slrx_params* prm) {
   return SLRX_OK;
 }
 
-slrx_status slrx::enqueue_run(slrx_plan* pl) {
+slrx_status slrx::enqueue_run(slrx_plan* pl, bool columns) {
+  pl->tri_columns = columns;
   if (pl->direct() && pl->ncoils > 0) return fail(SLRX_EINVAL, "SLRX_FLAG_DIRECT is single-channel only");
   STCHK(prepare(pl));
   if (pl->direct()) STCHK(direct_setup(pl));
@@ -663,6 +664,14 @@ extern "C" slrx_status slrx_run(slrx_plan* pl) {
 }
 
 slrx_status slrx::finish(slrx_plan* pl) {
+  const bool was = pl->running;
+  slrx_status st = finish_once(pl);
+  if (!was || st != SLRX_OK || !pl->gave_up) return st;
+  st = enqueue_run(pl, true);
+  return st == SLRX_OK ? finish_once(pl) : st;
+}
+
+slrx_status slrx::finish_once(slrx_plan* pl) {
   if (!pl->running) return SLRX_OK;
   HIPCHK(hipEventSynchronize(pl->ev_run[1]));
   pl->running = false;
@@ -674,15 +683,11 @@ slrx_status slrx::finish(slrx_plan* pl) {
     // column launches, from the inputs the plan still holds
     pl->ran = false;
     tri_resident_gave_up(pl->tri_stream, info[kInfoStalled]);
-    if (pl->tri_columns || !pl->inputs_kept)
-      return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running%s",
-                  pl->tri_columns ? "" : ", and inputs were set before the result was collected");
-    pl->tri_columns = true;
-    slrx_status again = enqueue_run(pl);
-    if (again == SLRX_OK) again = finish(pl);
-    pl->tri_columns = false;
+    if (!pl->inputs_kept)
+      return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running, and inputs were set "
+                                "before the result was collected");
     pl->gave_up = true;
-    return again;
+    return SLRX_OK;
   }
   if (info[kInfoNonfinite] != 0) {
     pl->ran = false;
@@ -916,10 +921,11 @@ static slrx_status step_weights_voxel(slrx_plan* pl, double eps, double* lam_out
   return SLRX_OK;
 }
 
-// One attempt of slrx_step_weights; info: the eigensolver's status, the non-finite flag and
+// One attempt of slrx_step_weights (columns: by column launches); info: the eigensolver's status, the non-finite flag and
 // the give-up flag of the tridiagonalisation (then the outputs are to be computed again).
-static slrx_status weights_once(slrx_plan* pl, double eps, double* lam_out, void* H_out, void* E_out, slrx_mem mem,
-                                rocblas_int (&info)[3]) {
+static slrx_status weights_once(slrx_plan* pl, bool columns, double eps, double* lam_out, void* H_out, void* E_out,
+                                slrx_mem mem, rocblas_int (&info)[3]) {
+  pl->tri_columns = columns;
   HIPCHK(hipMemsetAsync(pl->info + kInfoStalled, 0, sizeof(rocblas_int), pl->stream));
   STCHK(step_gram(pl));
   STCHK(step_eigh(pl, -1));
@@ -963,13 +969,10 @@ extern "C" slrx_status slrx_step_weights(slrx_plan* pl, double eps, double* lam_
   if (pl && pl->direct()) return fail(SLRX_EINVAL, "SLRX_FLAG_DIRECT plans run whole reconstructions only");
   STCHK(ensure_prepared(pl));
   rocblas_int info[3] = {};
-  STCHK(weights_once(pl, eps, lam_out, H_out, E_out, mem, info));
+  STCHK(weights_once(pl, false, eps, lam_out, H_out, E_out, mem, info));
   if (info[2] != 0) {  // once more, by column launches
     tri_resident_gave_up(pl->stream, info[2]);
-    pl->tri_columns = true;
-    const slrx_status st = weights_once(pl, eps, lam_out, H_out, E_out, mem, info);
-    pl->tri_columns = false;
-    if (st != SLRX_OK) return st;
+    STCHK(weights_once(pl, true, eps, lam_out, H_out, E_out, mem, info));
     if (info[2] != 0) return fail(SLRX_EDEVICE, "the tridiagonalisation's workgroups were kept from running");
   }
   if (info[0] != 0) return fail(SLRX_ENUMERIC, "eigen-decomposition did not converge (info %d)", (int)info[0]);

@@ -74,8 +74,9 @@ size_t engine_problem_bytes(int n);
 // kept), after the work that reads them has finished (synchronises the engine's streams).
 slrx_status engine_trim(BatchEig& be, const std::map<int, int>& keep);
 
-// Start a problem: masked data, initial iterate, start event, iteration 0.
-slrx_status engine_begin(slrx_plan* pl);
+// Start a problem: masked data, initial iterate, start event, iteration 0.  columns: its
+// tridiagonalisations by column launches (the repeat of a run whose resident launch gave up).
+slrx_status engine_begin(slrx_plan* pl, bool columns = false);
 // Enqueue one outer iteration for every given problem that has iterations
 // left (no host synchronisation).
 slrx_status engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be);

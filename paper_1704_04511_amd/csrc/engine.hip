@@ -267,7 +267,7 @@ static slrx_status group_reserve(BatchEig& be, int n, int nb, EigGroup*& out) {
   return SLRX_OK;
 }
 
-slrx_status slrx::engine_begin(slrx_plan* pl) {
+slrx_status slrx::engine_begin(slrx_plan* pl, bool columns) {
   if (pl->direct() && pl->ncoils > 0) return fail(SLRX_EINVAL, "SLRX_FLAG_DIRECT is single-channel only");
   STCHK(prepare(pl));
   if (pl->direct()) STCHK(direct_setup(pl));
@@ -277,6 +277,7 @@ slrx_status slrx::engine_begin(slrx_plan* pl) {
   HIPCHK(hipEventRecord(pl->ev_run[0], pl->stream));
   pl->it_next = 0;
   pl->on_cg = nullptr;
+  pl->tri_columns = columns;
   pl->running = true;
   pl->ran = false;
   pl->run_irls = pl->prm.n_irls;
@@ -299,6 +300,27 @@ extern "C" void slrx_set_cg_grouping(int32_t mode) { g_cg_grouping.store(mode < 
 
 // Plans whose CG joins a grouped launch (single-channel, FFT-based operator).
 static bool cg_groupable(const slrx_plan* pl) { return pl->ncoils == 0 && !pl->direct(); }
+
+// Problems i0 .. i0 + nb - 1 of a group.
+static EighBufs sub_group(const EighBufs& e, int i0, int nb) {
+  EighBufs s = e;
+  const long o = (long)i0 * e.n;
+  s.nb = nb;
+  s.A += i0 * e.sA;
+  s.V += i0 * e.sA;
+  s.Z += i0 * e.sZ;
+  s.Q += i0 * e.sQ;
+  s.Qs += i0 * e.sQ;
+  s.U += i0 * e.sQ;
+  s.tau += o;
+  for (int k = 0; k < 2; ++k) {
+    s.triv[k] += o;
+    s.trip[k] += o;
+  }
+  s.D += o;
+  s.E += o;
+  return s;
+}
 
 // One outer iteration of one problem on its own stream (the path of a plan run
 // alone); with `deferred` the CG of a groupable plan is left to the grouped launch
@@ -427,8 +449,8 @@ struct WeightPart {
 };
 
 // The Gram matrices of the part's problems into the group's buffers.
-static slrx_status weight_part_gram(BatchEig& be, const EighBufs& e, const std::vector<slrx_plan*>& g, int part,
-                                    WeightPart& wp) {
+static slrx_status weight_part_gram(BatchEig& be, const EighBufs& e, const std::vector<slrx_plan*>& g,
+                                    const std::vector<const int*>& stall, int part, WeightPart& wp) {
   bool cg = false;
   std::vector<WeightSlice> host(wp.at.size());
   WeightGroup& G = wp.G;
@@ -455,7 +477,7 @@ static slrx_status weight_part_gram(BatchEig& be, const EighBufs& e, const std::
     c.twQ = pl->twQf;
     c.img_scale = (float)(1.0 / std::sqrt((double)d.P * d.Q));
     c.gram = gram_args(pl, e.A + (size_t)i * e.sA, true);
-    weight_args(pl, 0, false, pl->prm.gamma, e.Z + (size_t)i * e.sZ, e.D + (size_t)i * e.n, e.stall, c.w, c.spec,
+    weight_args(pl, 0, false, pl->prm.gamma, e.Z + (size_t)i * e.sZ, e.D + (size_t)i * e.n, stall[i], c.w, c.spec,
                 c.mask);
     G.ngroups = c.spec.ngroups;
     G.maxP = std::max(G.maxP, d.P);
@@ -538,15 +560,18 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
     STCHK(group_reserve(be, n, nb, G));
     EighBufs e = G->bufs;
     e.nb = nb;
+    // the problems whose run is repeated by column launches come last
+    const bool resident = tri_resident(n) && tri_resident_on(be.stream);
+    const int nres = resident ? (int)(std::stable_partition(g.begin(), g.end(),
+                                                            [](const slrx_plan* pl) { return !pl->tri_columns; }) -
+                                      g.begin())
+                              : 0;
     // column launches neither read nor clear the group's flag: the word after it stays 0
-    e.tri_columns = !tri_resident(n) || !tri_resident_on(be.stream);
-    if (e.tri_columns) {
-      e.stall += 1;
-    } else {
-      e.clear_stall = G->clear_stall;
-      G->clear_stall = false;
+    std::vector<const int*> stall(nb);
+    for (int i = 0; i < nb; ++i) {
+      stall[i] = i < nres ? e.stall : e.stall + 1;
+      g[i]->tri_stream = be.stream;
     }
-    for (slrx_plan* pl : g) pl->tri_stream = be.stream;
     // problems of one filter share launches of the weight update's kernels too (two or
     // more: one launch for all of them is never slower than their own, run at once)
     std::map<std::tuple<int, int, int>, std::vector<int>> filters;
@@ -568,7 +593,7 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
       }
     }
     // Gram matrices (row-major) into the group buffer once the previous step's readers are done
-    for (size_t k = 0; k < parts.size(); ++k) STCHK(weight_part_gram(be, e, g, (int)k, parts[k]));
+    for (size_t k = 0; k < parts.size(); ++k) STCHK(weight_part_gram(be, e, g, stall, (int)k, parts[k]));
     for (int i : alone) {
       slrx_plan* pl = g[i];
       if (be.have_free) HIPCHK(hipStreamWaitEvent(pl->stream, be.ev_free, 0));
@@ -576,7 +601,18 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
       HIPCHK(hipEventRecord(pl->ev_step, pl->stream));
       HIPCHK(hipStreamWaitEvent(be.stream, pl->ev_step, 0));
     }
-    HIPCHK(eigh_tri(e, be.stream));
+    if (nres > 0) {
+      EighBufs er = sub_group(e, 0, nres);
+      er.tri_columns = false;
+      er.clear_stall = G->clear_stall;
+      G->clear_stall = false;
+      HIPCHK(eigh_tri(er, be.stream));
+    }
+    if (nres < nb) {
+      EighBufs ec = sub_group(e, nres, nb - nres);
+      ec.tri_columns = true;
+      HIPCHK(eigh_tri(ec, be.stream));
+    }
     HIPCHK(eigh_tdeig(e, be.stream));
     HIPCHK(eigh_backtr(e, be.stream));
     HIPCHK(hipEventRecord(be.ev, be.stream));
@@ -603,7 +639,7 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
       const int it = pl->it_next;
       HIPCHK(hipStreamWaitEvent(pl->stream, be.ev, 0));
       STCHK(step_weights(pl, it, it == 0, pl->prm.gamma, e.Z + (size_t)i * e.sZ, e.D + (size_t)i * n, false,
-                         e.stall));
+                         stall[i]));
       HIPCHK(hipEventRecord(pl->ev_step, pl->stream));
       HIPCHK(hipStreamWaitEvent(be.stream, pl->ev_step, 0));
       pl->ev_weights = true;

@@ -129,10 +129,10 @@ struct slrx_plan {
 
   bool has_b = false, has_S = false, has_init = false;
   bool prepared = false, running = false, ran = false;
-  bool tri_columns = false;  // tridiagonalise by column launches (after a resident launch gave up)
+  bool tri_columns = false;  // the run (set as it starts) tridiagonalises by column launches
   bool inputs_kept = false;  // nothing was set since the run was started
   hipStream_t tri_stream = nullptr;  // the stream of the last run's tridiagonalisations
-  bool gave_up = false;      // a resident launch of the last run gave up (the run was repeated)
+  bool gave_up = false;      // a resident launch of the last run gave up (to be repeated)
   int run_irls = 0;
   bool run_timing = false;
 
@@ -206,6 +206,10 @@ slrx_status coil_pass(slrx_plan* pl);
 // concurrent streams measured slower than the launches themselves)
 slrx_status run_cg(slrx_plan* pl, int n_cg, int it, bool graph = true);
 void cg_graph_reset(slrx_plan* pl);
-slrx_status enqueue_run(slrx_plan* pl);
+// columns: tridiagonalise by column launches (the repeat of a run that gave up)
+slrx_status enqueue_run(slrx_plan* pl, bool columns = false);
 slrx_status finish(slrx_plan* pl);
+// The same without the repeat: gave_up is set when the run has to be repeated by column
+// launches (engine_begin, enqueue_run), its result not being one.
+slrx_status finish_once(slrx_plan* pl);
 }  // namespace slrx

@@ -195,10 +195,10 @@ static slrx_status start_request(Req* r) {
   return st;
 }
 
-// Results of a request whose last step has run on the device.
+// Results of a request whose run is complete.
 static slrx_status collect_request(Req* r) {
-  slrx_status st = finish(r->plan);
-  if (st == SLRX_OK && r->owned) {
+  slrx_status st = SLRX_OK;
+  if (r->owned) {
     r->result.resize((size_t)r->dims.T * r->dims.P * r->dims.Q);
     st = slrx_get_images(r->plan, r->result.data(), SLRX_MEM_HOST);
   }
@@ -316,8 +316,17 @@ static void scheduler_main(slrx_server* s) {
       Req* r = finishing[i];
       const bool must_wait = active.empty() && i == 0;
       if (must_wait || hipEventQuery(r->plan->ev_run[1]) != hipErrorNotReady) {
-        const slrx_status sr = collect_request(r);
-        if (r->plan->gave_up) engine_clear_stalls(s->eig);
+        slrx_status sr = finish_once(r->plan);
+        if (sr == SLRX_OK && r->plan->gave_up) {  // once more, among the others, by column launches
+          engine_clear_stalls(s->eig);
+          sr = engine_begin(r->plan, true);
+          if (sr == SLRX_OK) {
+            active.push_back(r);
+            finishing.erase(finishing.begin() + i);
+            continue;
+          }
+        }
+        if (sr == SLRX_OK) sr = collect_request(r);
         complete_request(s, r, sr);
         finishing.erase(finishing.begin() + i);
       } else {

@@ -186,3 +186,31 @@ def test_a_stream_kept_to_some_of_the_cus_takes_column_launches():
             assert spectrum(pl) == cols and cols != ref
     finally:
         assert hip.hipStreamDestroy(h) == 0
+
+
+def test_a_stalled_request_is_repeated_among_the_others():
+    """The repeat of a served run does not hold the scheduler: a request that is two steps behind
+    it finishes first, and one that joins its group meanwhile keeps its own bits."""
+    say("a stalled request of 60 iterations, others beside it")
+    pa, pb, pc = problem(810, n_irls=60), problem(813, n_irls=62, N=5, M=3), problem(814, n_irls=20)
+    with plan_of(pa) as a, plan_of(pb) as b, plan_of(pc) as c:
+        ref_c = spectrum(c)
+        ref_a = spectrum(a)
+        stall(1)
+        cols = spectrum(a)
+        assert cols != ref_a
+        srv = slrx.Server(1 << 30, max_slots=4)
+        try:
+            stall(1)
+            ta, tb = srv.submit(a), srv.submit(b)
+            srv.wait(tb)
+            tc = srv.submit(c)
+            for t in (ta, tc):
+                srv.wait(t)
+            ia, ib, ic = (srv.info(t) for t in (ta, tb, tc))
+        finally:
+            srv.close()
+        assert ib["t_done"] < ia["t_done"]
+        assert ic["t_admit"] < ia["t_done"]
+        assert a.stats()["lambda_max"] == cols and c.stats()["lambda_max"] == ref_c
+        assert spectrum(a) == ref_a  # alone again, on its own stream
