@@ -85,3 +85,32 @@ def test_the_per_thread_stream_is_another_stream_in_every_thread():
     together([lambda i=i: job(i) for i in range(8)])
     for a, ref in zip(out, refs):
         np.testing.assert_array_equal(a, ref)
+
+
+def test_a_run_does_not_disturb_a_capture_elsewhere():
+    """Runs enqueued while the program captures a stream of its own, in the default capture mode:
+    from another thread and from the capturing thread, on the plans' streams."""
+    import torch
+    say("runs enqueued during a capture")
+    pa, pb = plan(740), plan(741)
+    refs = []
+    for pl in (pa, pb):
+        for _ in range(2):  # the second run replays the captured CG
+            pl.run()
+            pl.sync()
+        refs.append(pl.images())
+    x = torch.ones(1 << 16, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        y = x * 2
+        together([pa.run])
+        pb.run()
+        y = y + 1
+    for pl, ref in zip((pa, pb), refs):
+        pl.sync()
+        np.testing.assert_array_equal(pl.images(), ref)
+        pl.close()
+    g.replay()
+    torch.cuda.synchronize()
+    assert float(y[0]) == 3.0
