@@ -79,6 +79,14 @@ SLRX_DEV void block_sums(double (&v)[K], double* red) {
   __syncthreads();
 }
 
+// While it lives, event queries of this thread are allowed beside captures in the default
+// mode (of any thread), which they would otherwise break.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // Raises a kernel's dynamic-LDS limit once per device: the first launches on a
 // device set it (concurrent first launches may both set it, which is harmless);
 // the flag bits are atomic, so host threads can launch concurrently.

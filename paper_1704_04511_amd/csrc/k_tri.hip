@@ -1056,10 +1056,7 @@ hipError_t res_admit(ResDevice& d, int wgs, hipStream_t s) {
   wgs = (wgs + kXcds - 1) / kXcds * kXcds;
   const std::thread::id by = res_thread(s);
   ResStream mine{s, by, nullptr, wgs};
-  // an event query is refused, and the capture lost, while any thread captures a stream in the
-  // default mode, unless the querying thread's own mode is relaxed
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  const RelaxedCapture relaxed;
   std::vector<ResStream> keep;
   for (const ResStream& t : d.streams) {
     // an event of a stream that is gone gives an error: its work has run
@@ -1074,7 +1071,6 @@ hipError_t res_admit(ResDevice& d, int wgs, hipStream_t s) {
       keep.push_back(t);
     }
   }
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
   hipError_t e = hipSuccess;
   int sum = wgs;
   for (size_t i = keep.size(); i-- > 0 && e == hipSuccess;) {

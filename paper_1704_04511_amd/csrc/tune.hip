@@ -20,6 +20,7 @@
 #include <tuple>
 #include <vector>
 
+#include "common.h"
 #include "kernels.h"
 #include "tune.h"
 #include "../../include/slrx.h"
@@ -90,6 +91,7 @@ void save_choice(const Key& k, const Entry& en) {
 
 // Read back every completed event pair of an entry (caller holds g_mu).
 void collect(Entry& en) {
+  const RelaxedCapture relaxed;
   for (size_t i = 0; i < en.pending.size();) {
     Pending& p = en.pending[i];
     const hipError_t q = p.ended ? hipEventQuery(p.e1) : hipErrorNotReady;
