@@ -69,6 +69,19 @@ hipError_t slrx::dev_malloc(void** p, size_t bytes) {
   return hipMalloc(p, bytes);
 }
 
+std::shared_mutex& slrx::capture_mutex() {
+  static std::shared_mutex mu;
+  return mu;
+}
+hipError_t slrx::copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
+  std::shared_lock<std::shared_mutex> lk(capture_mutex());
+  return hipMemcpy(dst, src, bytes, kind);
+}
+hipError_t slrx::fill_now(void* dst, int value, size_t bytes) {
+  std::shared_lock<std::shared_mutex> lk(capture_mutex());
+  return hipMemset(dst, value, bytes);
+}
+
 extern "C" void slrx_fault_alloc(int32_t n) {
   std::lock_guard<std::mutex> lk(g_alloc_mu);
   g_alloc_fault = n < 0 ? -1 : n;
@@ -280,10 +293,10 @@ static slrx_status make_twiddles(slrx_plan* pl) {
     dq[t] = make_double2(std::cos(a), std::sin(a));
     fq[t] = make_float2((float)dq[t].x, (float)dq[t].y);
   }
-  HIPCHK(hipMemcpy(pl->twPf, fp.data(), P * sizeof(float2), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(pl->twQf, fq.data(), Q * sizeof(float2), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(pl->twPd, dp.data(), P * sizeof(double2), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(pl->twQd, dq.data(), Q * sizeof(double2), hipMemcpyHostToDevice));
+  HIPCHK(copy_now(pl->twPf, fp.data(), P * sizeof(float2), hipMemcpyHostToDevice));
+  HIPCHK(copy_now(pl->twQf, fq.data(), Q * sizeof(float2), hipMemcpyHostToDevice));
+  HIPCHK(copy_now(pl->twPd, dp.data(), P * sizeof(double2), hipMemcpyHostToDevice));
+  HIPCHK(copy_now(pl->twQd, dq.data(), Q * sizeof(double2), hipMemcpyHostToDevice));
   return SLRX_OK;
 }
 
@@ -393,7 +406,7 @@ extern "C" slrx_status slrx_plan_create(const slrx_dims* dims, const slrx_params
   pl->arena_bytes = L.total;
   assign_buffers(pl, L);
   slrx_status st = SLRX_OK;
-  if (hipMemset(pl->arena, 0, L.total) != hipSuccess) st = fail(SLRX_EDEVICE, "hipMemset failed");
+  if (fill_now(pl->arena, 0, L.total) != hipSuccess) st = fail(SLRX_EDEVICE, "hipMemset failed");
   if (st == SLRX_OK) st = make_twiddles(pl);
   if (st == SLRX_OK) st = dc_prepare(pl);
   if (st == SLRX_OK) {
@@ -677,7 +690,7 @@ slrx_status slrx::finish_once(slrx_plan* pl) {
   pl->running = false;
   pl->ran = true;
   std::vector<rocblas_int> info(kInfoEntries);
-  HIPCHK(hipMemcpy(info.data(), pl->info, kInfoEntries * sizeof(rocblas_int), hipMemcpyDeviceToHost));
+  HIPCHK(copy_now(info.data(), pl->info, kInfoEntries * sizeof(rocblas_int), hipMemcpyDeviceToHost));
   if (info[kInfoStalled] != 0) {
     // a resident tridiagonalisation gave up waiting for its workgroups: once more, by
     // column launches, from the inputs the plan still holds
@@ -694,7 +707,7 @@ slrx_status slrx::finish_once(slrx_plan* pl) {
     return fail(SLRX_ENUMERIC, "non-finite Gram matrix (non-finite data, initial guess or iterate)");
   }
   std::vector<double> st(3 * SLRX_MAX_IRLS);
-  HIPCHK(hipMemcpy(st.data(), pl->stats, st.size() * sizeof(double), hipMemcpyDeviceToHost));
+  HIPCHK(copy_now(st.data(), pl->stats, st.size() * sizeof(double), hipMemcpyDeviceToHost));
   for (int it = 0; it < pl->run_irls; ++it) {
     if (info[it] != 0) {
       pl->ran = false;
@@ -788,7 +801,7 @@ extern "C" slrx_status slrx_get_stats(slrx_plan* pl, slrx_stats* out) {
   STCHK(require_done(pl));
   std::memset(out, 0, sizeof *out);
   std::vector<double> st(3 * SLRX_MAX_IRLS);
-  HIPCHK(hipMemcpy(st.data(), pl->stats, st.size() * sizeof(double), hipMemcpyDeviceToHost));
+  HIPCHK(copy_now(st.data(), pl->stats, st.size() * sizeof(double), hipMemcpyDeviceToHost));
   out->n_irls_done = pl->run_irls;
   for (int i = 0; i < pl->run_irls; ++i) {
     out->eps[i] = st[i];
@@ -916,7 +929,7 @@ static slrx_status step_weights_voxel(slrx_plan* pl, double eps, double* lam_out
   }
   HIPCHK(hipStreamSynchronize(pl->stream));
   int bad = 0;
-  HIPCHK(hipMemcpy(&bad, pl->info + kInfoNonfinite, sizeof(int), hipMemcpyDeviceToHost));
+  HIPCHK(copy_now(&bad, pl->info + kInfoNonfinite, sizeof(int), hipMemcpyDeviceToHost));
   if (bad) return fail(SLRX_ENUMERIC, "non-finite Gram matrix (non-finite data, initial guess or iterate)");
   return SLRX_OK;
 }
@@ -957,7 +970,7 @@ static slrx_status weights_once(slrx_plan* pl, bool columns, double eps, double*
   }
   HIPCHK(hipStreamSynchronize(pl->stream));
   static_assert(kInfoNonfinite == SLRX_MAX_IRLS + 1 && kInfoStalled == SLRX_MAX_IRLS + 2, "read together");
-  HIPCHK(hipMemcpy(info, pl->info + SLRX_MAX_IRLS, sizeof info, hipMemcpyDeviceToHost));
+  HIPCHK(copy_now(info, pl->info + SLRX_MAX_IRLS, sizeof info, hipMemcpyDeviceToHost));
   return SLRX_OK;
 }
 

@@ -209,7 +209,7 @@ static slrx_status group_reserve(BatchEig& be, int n, int nb, EigGroup*& out) {
       return fail(SLRX_ENOMEM, "divide-and-conquer tree");
     }
     if (!nodes.empty())
-      HIPCHK(hipMemcpy(G.tree, nodes.data(), nodes.size() * sizeof(int), hipMemcpyHostToDevice));
+      HIPCHK(copy_now(G.tree, nodes.data(), nodes.size() * sizeof(int), hipMemcpyHostToDevice));
     G.bufs.stall = G.tree + tree_ints(n);
     HIPCHK(hipMemsetAsync(G.bufs.stall, 0, 256, be.stream));  // in order with the launches that read it
     G.n = n;  // only once the tree is on the device

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
 
+#include <mutex>
+#include <shared_mutex>
 #include <string>
 #include <vector>
 
@@ -30,6 +32,12 @@ enum Buf {
 };
 
 slrx_status fail(slrx_status st, const char* fmt, ...);
+// The library's synchronous copies and fills.  HIP refuses them while any stream of the process
+// is being captured, and the capture is lost, so they and the library's own captures (of the
+// CG, on a thread's first runs) exclude each other.
+hipError_t copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
+hipError_t fill_now(void* dst, int value, size_t bytes);
+std::shared_mutex& capture_mutex();  // held exclusively by a capture
 // Every device allocation of the library (fault injection for tests: slrx_fault_alloc).
 hipError_t dev_malloc(void** p, size_t bytes);
 // What a captured CG graph depends on beyond the plan's fixed buffers.

@@ -133,7 +133,7 @@ slrx_status slrx::dc_prepare(slrx_plan* pl) {
   dc_build_tree(s, nodes, pl->dc_level_start);
   pl->dc_node_sizes.resize(nodes.size() / 4);
   for (size_t q = 0; q < nodes.size() / 4; ++q) pl->dc_node_sizes[q] = nodes[4 * q + 1];
-  if (!nodes.empty()) HIPCHK(hipMemcpy(pl->dc_tree, nodes.data(), nodes.size() * sizeof(int), hipMemcpyHostToDevice));
+  if (!nodes.empty()) HIPCHK(copy_now(pl->dc_tree, nodes.data(), nodes.size() * sizeof(int), hipMemcpyHostToDevice));
   pl->dc_tree_n = s;
   return SLRX_OK;
 }
@@ -717,13 +717,18 @@ void slrx::cg_graph_reset(slrx_plan* pl) {
 static slrx_status capture_cg(slrx_plan* pl, int n_cg, const CgGraphKey& key) {
   cg_graph_reset(pl);
   if (!pl->cap_stream) HIPCHK(hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking));
-  hipStream_t own = pl->stream;
-  pl->stream = pl->cap_stream;
-  HIPCHK(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeThreadLocal));
-  const slrx_status st = cg_body(pl, n_cg);
   hipGraph_t g = nullptr;
-  const hipError_t e = hipStreamEndCapture(pl->cap_stream, &g);
-  pl->stream = own;
+  slrx_status st = SLRX_OK;
+  hipError_t e;
+  {
+    std::unique_lock<std::shared_mutex> lk(capture_mutex());
+    HIPCHK(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeThreadLocal));
+    hipStream_t own = pl->stream;
+    pl->stream = pl->cap_stream;
+    st = cg_body(pl, n_cg);
+    e = hipStreamEndCapture(pl->cap_stream, &g);
+    pl->stream = own;
+  }
   if (st != SLRX_OK || e != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
     return st != SLRX_OK ? st : fail(SLRX_EDEVICE, "hipStreamEndCapture failed: %s", hipGetErrorString(e));
