@@ -223,7 +223,10 @@ slrx_status slrx_set_params(slrx_plan* plan, const slrx_params* params);
 /* Enqueue the whole reconstruction on the plan's stream.  The FP64
  * eigen-decomposition may synchronise the stream internally. */
 slrx_status slrx_run(slrx_plan* plan);
-/* Wait for the plan's work; reports numerical failures of the run. */
+/* Wait for the plan's work; reports numerical failures of the run.  A run whose
+ * tridiagonalisations could not run (the device kept some of their workgroups from running for
+ * 2 s) is repeated here, or by the first call that reads its outputs, from the inputs the plan
+ * holds; if inputs or parameters were set since the run ended, SLRX_EDEVICE. */
 slrx_status slrx_sync(slrx_plan* plan);
 
 /* Outputs (after slrx_sync): images F^-1 x and k-space x, complex64 [T][P][Q]. */
@@ -250,8 +253,8 @@ slrx_status slrx_fit_t2(slrx_plan* plan, const void* img, const double* te_ms, d
 /* Run several independent plans.  hip_stream NULL: in lock step, one outer
  * iteration of every plan per step; plans with equal Gram size s share one
  * launch sequence of the eigen-decomposition (every kernel covers all of them,
- * each with the arithmetic of a single plan), every other kernel runs on the
- * plan's own stream.  A plan's result is bit-identical to slrx_run on that
+ * each with the arithmetic of a single plan), plans of one filter among them the
+ * other launches of the weight update; the rest runs on the plan's own stream.  A plan's result is bit-identical to slrx_run on that
  * plan (plans using the library eigensolver take their own path).  With
  * hip_stream: the plans run back to back on it, each as slrx_run would.
  * Returns once the work is enqueued; call slrx_sync on each plan. */

@@ -841,8 +841,8 @@ extern "C" slrx_status slrx_get_stats(slrx_plan* pl, slrx_stats* out) {
 
 // Several independent problems.  With hip_stream NULL they run in lock step
 // on the engine (one outer iteration of every problem per step, one launch
-// sequence of the eigen-decomposition per Gram size, every other kernel on the
-// problem's own stream); the call returns once all work is enqueued.  With a
+// sequence of the eigen-decomposition per Gram size and of the rest of the weight
+// update per filter of it, the CG grouped or on the problem's own stream); the call returns once all work is enqueued.  With a
 // stream the plans run one after another on it, each as slrx_run would.
 static std::mutex g_batch_mu;
 static BatchEig* g_batch_eig = nullptr;  // kept for the life of the process

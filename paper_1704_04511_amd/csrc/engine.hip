@@ -442,7 +442,8 @@ static slrx_status run_cg_group(BatchEig& be, const std::vector<slrx_plan*>& g, 
 }
 
 // A part of an eigen-decomposition group whose weight updates run as grouped launches on
-// the engine's stream: problems of one filter (at least two, at most kGroupIts).
+// the engine's stream: problems of one filter, of which there are at least two, at most
+// kGroupIts to a part (the last part may be a single problem).
 struct WeightPart {
   std::vector<int> at;  // positions in the group
   WeightGroup G{};

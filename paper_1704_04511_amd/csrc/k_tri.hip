@@ -5,9 +5,9 @@
 // Column k needs a global matrix-vector product with the trailing block, and so
 // a grid-wide exchange.  Sizes whose matrix fits the registers of 256 workgroups
 // (129 to 1280) are reduced in one launch (k_tri_res, below); other sizes, calls
-// on a stream that is being captured, and runs repeated after a resident launch
-// gave up use one launch per column, the launch boundary being the exchange.  A
-// launch for column k:
+// on a stream that is being captured or kept to some of the CUs, and runs repeated
+// after a resident launch gave up use one launch per column, the launch boundary
+// being the exchange.  A launch for column k:
 //   * in every workgroup (redundantly, identical arithmetic): finishes the
 //     previous reflector's w = tau p - |tau|^2/2 (p^H v) v from the previous
 //     launch's p = A v, corrects row k with the pending rank-2 update
@@ -571,7 +571,7 @@ __global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0, const d
 //   What bounds it: the chain of a column.  Measured in cycles per column at n = 405 (135
 // workgroups) and n = 1125 (225): exchange 1680 and 2430, d 360 and 420, norm 710 and 820,
 // reflector 760 and 880, rows 980 and 1490, publishing 330 and 330 (about 2 GHz).  Whole
-// reductions with the last columns: 961 us (n = 405) and 3440 us (n = 1125), where the
+// reductions with the last columns: 905 us (n = 405) and 3350 us (n = 1125), where the
 // column launches take 1503 and 6970 us (4.4 to 11.6 us each, the longer ones bound by
 // reading and writing the trailing block).
 //   Every wait ends: a thread that has polled for `wait` ticks, or sees that another has,
@@ -679,7 +679,8 @@ SLRX_DEV bool res_columns(ResState<U, R>& st, ResLds<U, R>& q, const TriArgs& a,
       // costs the whole vector once more, from every workgroup, and delays the stores it
       // waits for: n = 1125 took 4780 us without a delay and 3440 us with it.
       // Due: about 450 cycles after the own entries, and the time that the vectors of all
-      // workgroups take; where two workgroups share a CU the others' rows come first (15
+      // workgroups take; where two workgroups share a CU the others' rows come first (as far
+      // as this launch shows: those of other streams on the same CUs are not counted; 15
       // problems of n = 405: 2060 us with 7 units of 64 cycles, 1660 with 24, 1510 with 32,
       // 1570 with 50; 6 of n = 605: 3640, 2590, 2260, 2410; 32 of n = 140: 195, 173, 179, 190).
       const int wgs = (int)(gridDim.x * gridDim.y);

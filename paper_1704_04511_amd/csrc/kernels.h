@@ -136,7 +136,7 @@ struct CgGroup {
 };
 void cg_slice_grids(CgSlice& c);        // fills the grids and partial counts from P, Q, T
 size_t group_pen_lds(int P, int Q, int T);
-// mode: ROW_PLAIN (initial residual, x) or ROW_PUPDATE (iteration k)
+// mode: ROW_PLAIN (initial residual, x), ROW_START (first iteration) or ROW_STEP (iteration k > 0)
 hipError_t launch_group_rows(const CgGroup& g, int mode, int k, hipStream_t s);
 hipError_t launch_group_pen(const CgGroup& g, hipStream_t s);
 hipError_t launch_group_fin(const CgGroup& g, int init, int k, hipStream_t s);

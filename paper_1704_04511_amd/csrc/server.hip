@@ -10,13 +10,16 @@
 // otherwise).  One scheduler thread drives
 // the lock-step engine: each step advances every active request by one outer
 // IRLS iteration, with one launch sequence of the eigen-decomposition per
-// group of equal Gram size and all other kernels on each request's own stream.  A request
+// group of equal Gram size, the other launches of the weight update per filter of
+// a group, and the CG grouped or on each request's own stream.  A request
 // that arrives while others run joins at the next step, with its own iteration
 // count and epsilon schedule.  The scheduler keeps one step in flight ahead of
 // the device, so admissions take effect within about one step.  When a request
 // finishes, its images are copied to host memory and its budget share is
 // released at once; its plan is kept idle for the next request of the same
-// shape and evicted when the budget is needed.  A result depends only on the
+// shape and evicted when the budget is needed.  A request whose tridiagonalisation
+// gave up waiting for its workgroups starts again among the others, by column
+// launches.  A result depends only on the
 // request, not on what runs beside it (bit-identical to running it alone).
 #include <hip/hip_runtime.h>
 
