@@ -567,10 +567,10 @@ slrx_status slrx::engine_step(const std::vector<slrx_plan*>& plans, BatchEig& be
                                                             [](const slrx_plan* pl) { return !pl->tri_columns; }) -
                                       g.begin())
                               : 0;
-    // column launches neither read nor clear the group's flag: the word after it stays 0
+    // column launches neither read nor clear the group's flag: the word after its own stays 0
     std::vector<const int*> stall(nb);
     for (int i = 0; i < nb; ++i) {
-      stall[i] = i < nres ? e.stall : e.stall + 1;
+      stall[i] = i < nres ? e.stall : e.stall + kStallWords;
       g[i]->tri_stream = be.stream;
     }
     // problems of one filter share launches of the weight update's kernels too (two or

@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0, const d
 //   Every wait ends: a thread that has polled for `wait` ticks, or sees that another has,
 // gives up, raises `stall`, and its workgroup leaves the kernel at the next barrier.  The
 // last-columns kernel then writes zeros for the problem, the launches of the run's later
-// decompositions leave at once, and the host, which finds the flag, repeats the run by
+// decompositions give up at their first miss, and the host, which finds the flag, repeats the run by
 // column launches.  This only happens where workgroups of the
 // launch are kept from running (the launches of this process that may run at a time are
 // limited to what fits the chip, res_admit).
@@ -620,7 +620,10 @@ __global__ __launch_bounds__(256) void k_tri_res_fill(TriResArgs x, long n2, int
     ulonglong2* C = (ulonglong2*)(x.C + b * x.sC);
     for (long i = i0; i < n2; i += stride) P[i] = C[i] = make_ulonglong2(e, e);
   }
-  if (i0 == 0 && x.clear) *x.stall = 0;
+  if (i0 == 0) {
+    if (x.clear) x.stall[0] = 0;
+    x.stall[1] = x.id;
+  }
 }
 
 // Rows per workgroup by column slots U.  One problem (or few) is split finely: a column
@@ -702,7 +705,7 @@ SLRX_DEV bool res_columns(ResState<U, R>& st, ResLds<U, R>& q, const TriArgs& a,
           if (t0 == 0) t0 = t;
           if (t - t0 > x.wait || __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
             if (lane == 0) {
-              __hip_atomic_store(x.stall, x.id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(x.stall, x.stall[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               q.dead = 1;
             }
             break;
@@ -865,13 +868,12 @@ __global__ __launch_bounds__(256) void k_tri_res(TriArgs a, TriResArgs x, int k0
   }
   st.tau = zero;
   if (tid < R) q.pown[tid] = zero;
-  if (tid == 0) {  // a launch before this one gave up, or (tests) this workgroup is the missing one
-    const bool missing = x.missing && g == G - 1;
-    q.dead = missing || __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    if (missing && x.wait == 0) __hip_atomic_store(x.stall, x.id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (tid == 0) q.dead = x.missing && g == G - 1;
   __syncthreads();
-  if (q.dead) return;
+  if (q.dead) {  // the missing one (tests)
+    if (tid == 0 && x.wait == 0) __hip_atomic_store(x.stall, x.stall[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
   if (!res_columns<U, R, 0>(st, q, a, x, g, G, b, 0, min(k0, 256))) return;
   if constexpr (U > 1)
     if (!res_columns<U, R, 1>(st, q, a, x, g, G, b, 256, min(k0, 512))) return;

@@ -300,18 +300,22 @@ hipError_t launch_tridiag(const TriArgs& a, int nbatch, hipStream_t s, int cand,
 // columns; vbuf[0] and pbuf[0] hold the pending reflector between the two.  P, C: write-once
 // vectors of the exchange, n x n elements per problem each.  stall is set when a wait was
 // given up: every output of the launch is then finite but not a result.  It stays set, and
-// launches that find it set leave at once, so that a run waits only once; it is cleared by
-// whoever starts the next run, or by a launch with `clear`.
+// launches that find it set give up at their first miss, so that a run waits only once; it is
+// cleared by whoever starts the next run, or by a launch with `clear`.  (The id goes through the
+// word after it, which the filling kernel writes, and only waits look at the flag: the
+// reduction has no scalar registers left, and an argument and a look at its start cost 0.8%
+// at s = 1125.)
 struct TriResArgs {
   double2* P;
   double2* C;
   long sP, sC;              // elements between the problems of a batch
-  int* stall;
+  int* stall;               // kStallWords words: the flag, the id
   int id;                   // this launch, what stall is set to (never 0)
   bool clear;
   bool missing;             // tests: the last workgroup of every problem leaves at once
   unsigned long long wait;  // longest wait of a thread in ticks of 10 ns (0: give up at once)
 };
+constexpr int kStallWords = 2;
 constexpr unsigned long long kTriResWait = 200000000ull;  // 2 s
 bool tri_resident(int n);
 // Whether resident launches may be made on s: not on a stream that is kept to some of the CUs

@@ -20,7 +20,7 @@ constexpr int kMaxCg = 10000;  // largest CG iteration count
 // set to the resident tridiagonalisation that gave up waiting (both for the whole run)
 constexpr int kInfoNonfinite = SLRX_MAX_IRLS + 1;
 constexpr int kInfoStalled = SLRX_MAX_IRLS + 2;
-constexpr int kInfoEntries = SLRX_MAX_IRLS + 3;
+constexpr int kInfoEntries = kInfoStalled + kStallWords;
 
 enum Buf {
   B_B, B_BM, B_X0, B_IMG, B_X, B_R, B_P, B_Q, B_T, B_S, B_ET, B_ESTAGE,
