@@ -279,7 +279,7 @@ SLRX_DEV void cols_pen_body(const PenArgs& a, const Blk& b, float2* lds, float2*
   // glast[q] frame T - 1 - q.  Inputs come from LDS through a window of 2M - 1 frames: with
   // all kTMax of them in registers one workgroup filled a CU (176 registers a thread, 218 in
   // the grouped pass), and loads, transforms and stores took turns: the grouped pass of 32
-  // problems of 96 to 256 rows takes 211 -> 143 us (1.7 -> 2.4 TB/s), 64 x 64 x 8 alone 8.2 -> 7.3 us.
+  // problems of 96 to 256 rows takes 189 -> 121 us, 64 x 64 x 8 alone 8.2 -> 7.3 us.
   float2 glast[M > 1 ? M - 1 : 1];
   if (split && has_pix) {
     const float2* x = lds + pl;
@@ -708,11 +708,9 @@ __global__ __launch_bounds__(kNT) void k_group_rows(const CgSlice* tab, int ns, 
   SLRX_SWITCH_N(c.Q, rows_t_body<N_, +1>(a, b, lds, twt, red))
 }
 
-// The code of nine transform lengths takes the registers of the worst, 160 at M = 5, which
-// leaves room for one workgroup per CU up from M = 4. Held to 128 for two of them, M = 5 spills
-// 49 (144 bytes a lane) and the 32-slice batch takes 155.8 ms against 155.1.
+// Two workgroups per CU up to M = 5 (a few spilled registers cost less than half the waves).
 template <int M>
-__global__ __launch_bounds__(kPenNT) void k_group_pen(const CgSlice* tab, int ns) {
+__global__ __launch_bounds__(kPenNT, M <= 5 ? 4 : 2) void k_group_pen(const CgSlice* tab, int ns) {
   extern __shared__ float2 lds[];
   __shared__ float2 twt[kTwMax];
   const int gb = (int)blockIdx.x;
