@@ -708,7 +708,10 @@ __global__ __launch_bounds__(kNT) void k_group_rows(const CgSlice* tab, int ns, 
   SLRX_SWITCH_N(c.Q, rows_t_body<N_, +1>(a, b, lds, twt, red))
 }
 
-// Two workgroups per CU up to M = 5 (a few spilled registers cost less than half the waves).
+// Two workgroups per CU up to M = 5: the code of nine transform lengths takes the registers of
+// the worst, 160 at M = 5; held to 128, M = 5 spills 49 (144 bytes a lane) and M = 4 14.  Batches
+// of 12 of 192 x 192 x 16 with M = 5 take 33.3 ms so and 35.1 with 160, 8 of 160 x 160 x 12 with
+// M = 4 14.0 and 14.8, the draw of 32 uneven slices the same.
 template <int M>
 __global__ __launch_bounds__(kPenNT, M <= 5 ? 4 : 2) void k_group_pen(const CgSlice* tab, int ns) {
   extern __shared__ float2 lds[];
