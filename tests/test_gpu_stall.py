@@ -62,45 +62,39 @@ def test_a_run_waits_once():
     pl.close()
 
 
-def submit(srv, pb):
-    return srv.submit_data(pb.b, pb.S, pb.N1, pb.N2, pb.M, slrx.make_params(lam=pb.lam, n_irls=pb.n_irls, n_cg=pb.n_cg))
-
-
-def test_requests_wait_once():
-    """The same for a server's group of two, and a request after them is not touched by it."""
-    say("two stalled launches of 300 ms, two requests")
-    pbs = [problem(802 + i) for i in range(3)]
-    refs = []
-    for pb in pbs:
-        with plan_of(pb) as pl:
-            refs.append(run(pl))
-    srv = slrx.Server(1 << 30, max_slots=4)
-    try:
-        stall(2, 300)  # the first two steps, whichever requests are in them
-        t0 = time.perf_counter()
-        ts = [submit(srv, pb) for pb in pbs[:2]]
-        for t in ts:
-            srv.wait(t)
-        dt = time.perf_counter() - t0
-        say(f"{dt * 1e3:.0f} ms")
-        assert 0.3 <= dt <= 0.5
-        stall(0)
-        ts.append(submit(srv, pbs[2]))
-        srv.wait(ts[2])
-        out = [srv.fetch(t, pb.b.shape) for t, pb in zip(ts, pbs)]
-    finally:
-        srv.close()
-    for img, ref in zip(out[:2], refs):
-        assert nrmse(img, ref) <= 1e-5
-    np.testing.assert_array_equal(out[2], refs[2])
-
-
 def spectrum(pl):
     """The largest eigenvalue of every iteration, in FP64: images are rounded too coarsely to tell
     column launches from resident ones."""
     pl.run()
     pl.sync()
     return pl.stats()["lambda_max"]
+
+
+def test_requests_wait_once():
+    """The same for a server's group of two, whose runs give up together: that counts once, so a
+    request after them takes resident launches (its own bits)."""
+    say("two stalled launches of 300 ms, two requests")
+    plans = [plan_of(problem(802 + i)) for i in range(3)]
+    refs = [(spectrum(pl), pl.images()) for pl in plans]
+    srv = slrx.Server(1 << 30, max_slots=4)
+    try:
+        stall(2, 300)  # the first two steps, whichever requests are in them
+        t0 = time.perf_counter()
+        for t in [srv.submit(pl) for pl in plans[:2]]:
+            srv.wait(t)
+        dt = time.perf_counter() - t0
+        say(f"{dt * 1e3:.0f} ms")
+        assert 0.3 <= dt <= 0.5
+        stall(0)
+        srv.wait(srv.submit(plans[2]))
+    finally:
+        srv.close()
+    for pl, (lam, img) in zip(plans[:2], refs):
+        assert pl.stats()["lambda_max"] != lam and nrmse(pl.images(), img) <= 1e-5
+    assert plans[2].stats()["lambda_max"] == refs[2][0]
+    np.testing.assert_array_equal(plans[2].images(), refs[2][1])
+    for pl in plans:
+        pl.close()
 
 
 def test_a_stream_whose_launches_gave_up_twice_takes_column_launches():
