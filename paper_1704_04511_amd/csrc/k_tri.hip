@@ -622,7 +622,7 @@ __global__ __launch_bounds__(256) void k_tri_res_fill(TriResArgs x, long n2, int
   }
   if (i0 == 0) {
     if (x.clear) x.stall[0] = 0;
-    x.stall[1] = x.id;
+    if (x.stall[0] == 0) x.stall[1] = x.id;  // the first launch of the run that gives up stays named
   }
 }
 
@@ -703,10 +703,9 @@ SLRX_DEV bool res_columns(ResState<U, R>& st, ResLds<U, R>& q, const TriArgs& a,
         if ((spin & 63) == 63) {  // give up after `wait` ticks, or if anybody has
           const unsigned long long t = wall_clock64();
           if (t0 == 0) t0 = t;
-          const int stall = __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (t - t0 > x.wait || stall != 0) {
-            if (lane == 0) {  // (the first launch that gave up stays named)
-              if (stall == 0) __hip_atomic_store(x.stall, x.stall[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (t - t0 > x.wait || __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+            if (lane == 0) {
+              __hip_atomic_store(x.stall, x.stall[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               q.dead = 1;
             }
             break;
@@ -872,8 +871,7 @@ __global__ __launch_bounds__(256) void k_tri_res(TriArgs a, TriResArgs x, int k0
   if (tid == 0) q.dead = x.missing && g == G - 1;
   __syncthreads();
   if (q.dead) {  // the missing one (tests)
-    if (tid == 0 && x.wait == 0 && x.stall[0] == 0)
-      __hip_atomic_store(x.stall, x.stall[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0 && x.wait == 0) __hip_atomic_store(x.stall, x.stall[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
   if (!res_columns<U, R, 0>(st, q, a, x, g, G, b, 0, min(k0, 256))) return;
