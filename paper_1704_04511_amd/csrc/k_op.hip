@@ -279,7 +279,7 @@ SLRX_DEV void cols_pen_body(const PenArgs& a, const Blk& b, float2* lds, float2*
   // glast[q] frame T - 1 - q.  Inputs come from LDS through a window of 2M - 1 frames: with
   // all kTMax of them in registers one workgroup filled a CU (176 registers a thread, 218 in
   // the grouped pass), and loads, transforms and stores took turns: the grouped pass of 32
-  // problems of 96 to 256 rows takes 189 -> 121 us, 64 x 64 x 8 alone 8.2 -> 7.3 us.
+  // problems of 96 to 256 rows takes 211 -> 143 us, 64 x 64 x 8 alone 8.2 -> 7.3 us.
   float2 glast[M > 1 ? M - 1 : 1];
   if (split && has_pix) {
     const float2* x = lds + pl;
