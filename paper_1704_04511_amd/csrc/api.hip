@@ -842,8 +842,9 @@ extern "C" slrx_status slrx_get_stats(slrx_plan* pl, slrx_stats* out) {
 // Several independent problems.  With hip_stream NULL they run in lock step
 // on the engine (one outer iteration of every problem per step, one launch
 // sequence of the eigen-decomposition per Gram size and of the rest of the weight
-// update per filter of it, the CG grouped or on the problem's own stream); the call returns once all work is enqueued.  With a
-// stream the plans run one after another on it, each as slrx_run would.
+// update per filter of it, the CG grouped or on the problem's own stream); the call
+// returns once all work is enqueued.  With a stream the plans run one after another on
+// it, each as slrx_run would.
 static std::mutex g_batch_mu;
 static BatchEig* g_batch_eig = nullptr;  // kept for the life of the process
 
@@ -934,8 +935,9 @@ static slrx_status step_weights_voxel(slrx_plan* pl, double eps, double* lam_out
   return SLRX_OK;
 }
 
-// One attempt of slrx_step_weights (columns: by column launches); info: the eigensolver's status, the non-finite flag and
-// the give-up flag of the tridiagonalisation (then the outputs are to be computed again).
+// One attempt of slrx_step_weights (columns: by column launches); info: the eigensolver's
+// status, the non-finite flag and the give-up flag of the tridiagonalisation (then the
+// outputs are to be computed again).
 static slrx_status weights_once(slrx_plan* pl, bool columns, double eps, double* lam_out, void* H_out, void* E_out,
                                 slrx_mem mem, rocblas_int (&info)[3]) {
   pl->tri_columns = columns;

@@ -577,10 +577,10 @@ __global__ __launch_bounds__(kTailNT) void k_tri_tail(TriArgs a, int k0, const d
 //   Every wait ends: a thread that has polled for `wait` ticks, or sees that another has,
 // gives up, raises `stall`, and its workgroup leaves the kernel at the next barrier.  The
 // last-columns kernel then writes zeros for the problem, the launches of the run's later
-// decompositions give up at their first miss, and the host, which finds the flag, repeats the run by
-// column launches.  This only happens where workgroups of the
-// launch are kept from running (the launches of this process that may run at a time are
-// limited to what fits the chip, res_admit).
+// decompositions give up at their first miss, and the host, which finds the flag, repeats
+// the run by column launches.  This only happens where workgroups of the launch are kept
+// from running (the launches of this process that may run at a time are limited to what
+// fits the chip, res_admit).
 constexpr int kTriResMin = 128;   // largest n left to the column launches
 constexpr unsigned long long kResEmpty = ~0ull;
 
